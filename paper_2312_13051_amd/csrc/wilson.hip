@@ -63,6 +63,14 @@ __device__ __forceinline__ double arg_pi(double2 z) {
   return t <= -M_PI ? M_PI : t;
 }
 
+// LDS ordering between the lanes of one wave (the wave's LDS operations
+// complete in program order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------- small kernels
 __global__ void k_zero_u32(uint32_t *p, int64_t n) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -170,6 +178,146 @@ __global__ void k_carry_last(const double2 *src, int n_src, double2 *dst, int n_
     const double2 *s = src + (line * n_src + n_src - 1) * mm;
     double2 *d = dst + (line * n_dst + n_dst - 1) * mm;
     for (int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; k < mm; k += int64_t(gridDim.x) * blockDim.x) d[k] = s[k];
+  }
+}
+
+// ---------------------------------------------------------------- loops of few bands
+// The whole loop stage of one line for m <= 8 bands in one launch: overlaps,
+// Newton-Schulz polar factors and the ordered product. A group of P lanes
+// (P >= m*m, one wave or a part of it) takes a link at a time, a lane per
+// matrix element, and iterates its link to its own convergence with the
+// iterate in a private LDS slot; the line's factors stay in LDS, where the
+// groups multiply them pairwise as a tree. Such loops are bound by launches
+// and by the half-empty 16 x 16 tiles of the MFMA products: the general path
+// takes ~20 launches with a read-back every other step. Measured, whole calls
+// (general -> this path): Wilson loop of 1 band on 64 x 64 points 757 -> 540 us,
+// nested loop of 2 bands on 100 x 100 points 2.45 -> 1.20 ms, on 21 such planes
+// 27.0 -> 17.8 ms (with k_transport_small). Same steps, tests and flags as
+// k_ns_prep. Fout (optional) receives the factors; theta/phase outputs for m = 1.
+constexpr int kSmallM = 8;           // bands
+constexpr int kSmallN = 64;          // orbitals: a lane sums a whole overlap element
+constexpr int kSmallEntries = 3072;  // matrix entries of a line's factors held in LDS (48 KB)
+constexpr int kSmallThreads = 256;
+
+__host__ __device__ inline bool small_loop_fits(int N, int m, int n_loop) {
+  return m <= kSmallM && N <= kSmallN && int64_t(n_loop) * m * m <= kSmallEntries;
+}
+
+template <int P>
+__global__ __launch_bounds__(kSmallThreads) void k_small_loop(Grid U, int N, int m, int n_loop, int polar,
+                                                              double2 *Fout, double2 *W, uint32_t *line_st) {
+  extern __shared__ double2 sL[];  // the line's factors (n_loop x m*m), then 2 m*m entries per group
+  constexpr int NG = kSmallThreads / P;
+  const int64_t line = blockIdx.x;
+  const int tid = threadIdx.x, g = tid / P, e = tid % P, mm = m * m;
+  const bool own = e < mm;  // this lane holds element (r, c)
+  const int r = own ? e % m : 0, c = own ? e / m : 0;
+  double2 *sX = sL + int64_t(n_loop) * mm + 2 * g * mm, *sG = sX + mm;
+  const double dl = r == c ? 1.0 : 0.0;
+  bool bad = false;
+  for (int j0 = 0; j0 < n_loop; j0 += NG) {
+    const int j = j0 + g;
+    const bool live = j < n_loop;
+    double2 x = make_double2(0.0, 0.0);
+    if (live && own) {
+      const double2 *a = U.base + (line * n_loop + (j + 1 == n_loop ? 0 : j + 1)) * U.stride + int64_t(r) * U.ld;
+      const double2 *b = U.base + (line * n_loop + j) * U.stride + int64_t(c) * U.ld;
+#pragma unroll 4
+      for (int k = 0; k < N; ++k) x = be::cadd(x, be::cmulc(a[k], b[k]));
+    }
+    bool act = live && polar;
+    double err = 0.0;
+    for (int it = 0; it < 51 && __any(act); ++it) {
+      if (own) sX[e] = x;
+      wave_lds_sync();
+      double2 gm = make_double2(0.0, 0.0);
+      for (int k = 0; k < m; ++k) gm = be::cadd(gm, be::cmulc(sX[k + r * m], sX[k + c * m]));
+      double v = own ? fmax(fabs(gm.x - dl), fabs(gm.y)) : 0.0;
+      if (!(v == v) || !(gm.x == gm.x) || !(gm.y == gm.y)) v = INFINITY;
+#pragma unroll
+      for (int o = P / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+      if (own) sG[e] = make_double2(1.5 * dl - 0.5 * gm.x, -0.5 * gm.y);
+      wave_lds_sync();
+      double2 y = make_double2(0.0, 0.0);
+      for (int k = 0; k < m; ++k) y = be::cadd(y, be::cmul(sX[r + k * m], sG[k + c * m]));
+      if (act) {
+        err = v;
+        if (v >= 1e-30) x = y;
+        act = v >= 1e-7;  // below it this was the last step (it leaves ~(3/4) err^2)
+      }
+      wave_lds_sync();
+    }
+    bad = bad || !(err <= 1e-7 * (1.0 - 1e-12));
+    if (live && own) {
+      sL[int64_t(j) * mm + e] = x;
+      if (Fout) Fout[(line * n_loop + j) * int64_t(mm) + e] = x;
+    }
+  }
+  if (bad && e == 0) atomicOr(&line_st[line], BE_ST_OVERLAP_SINGULAR);
+  __syncthreads();
+  for (int s = 1; s < n_loop; s *= 2) {  // L[i] <- L[i + s] L[i]
+    for (int i0 = 0; i0 + s < n_loop; i0 += 2 * s * NG) {
+      const int i = i0 + 2 * s * g;
+      const bool live = own && i + s < n_loop;
+      double2 y = make_double2(0.0, 0.0);
+      if (live) {
+        const double2 *a = sL + int64_t(i + s) * mm, *b = sL + int64_t(i) * mm;
+        for (int k = 0; k < m; ++k) y = be::cadd(y, be::cmul(a[r + k * m], b[k + c * m]));
+      }
+      wave_lds_sync();
+      if (live) sL[int64_t(i) * mm + e] = y;
+    }
+    __syncthreads();
+  }
+  if (tid < mm) W[line * mm + tid] = sL[tid];
+}
+
+// Phases of 1 x 1 Wilson matrices (and their trivial eigenvectors).
+__global__ void k_phase_1(const double2 *W, int64_t n_lines, double *theta, int ldt, double *theta_raw, double2 *Z) {
+  const int64_t l = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (l >= n_lines) return;
+  const double th = arg_pi(W[l]);
+  theta[l * ldt] = th;
+  if (theta_raw) theta_raw[l] = th;
+  if (Z) Z[l] = make_double2(1.0, 0.0);
+}
+
+// Carries the Wannier sector of a line along its loop, nu_{j+1} = F_j nu_j,
+// for m <= 8: one wave per line, a lane per element of nu (m x sc), which
+// takes its row of F_j from memory PF links ahead and the other elements by
+// lane permutes. A batched product per link takes n_par - 1 launches of 6 us
+// each, 0.72 ms for 100 links whatever the number of lines.
+template <int M>
+__global__ __launch_bounds__(64) void k_transport_small(const double2 *F, double2 *nu, int m, int sc, int n_par) {
+  constexpr int PF = 4;
+  const int64_t line = blockIdx.x;
+  const int lane = threadIdx.x, r = lane % m, c = lane / m;
+  const bool own = c < sc;
+  const int64_t mm = int64_t(m) * m, nus = int64_t(m) * sc;
+  const double2 *Fl = F + line * n_par * mm;
+  double2 *nl = nu + line * n_par * nus;
+  double2 x = own ? nl[r + int64_t(c) * m] : make_double2(0.0, 0.0);
+  for (int j0 = 0; j0 + 1 < n_par; j0 += PF) {
+    double2 f[PF][M];
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        f[u][k] = (j0 + u + 1 < n_par && k < m) ? Fl[(j0 + u) * mm + r + int64_t(k) * m] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      if (j0 + u + 1 >= n_par) break;
+      double2 y = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        if (k < m) {
+          const int src = k + min(c, sc - 1) * m;
+          const double2 b = make_double2(__shfl(x.x, src, 64), __shfl(x.y, src, 64));
+          y = be::cadd(y, be::cmul(f[u][k], b));
+        }
+      x = y;
+      if (own) nl[(j0 + u + 1) * nus + r + int64_t(c) * m] = x;
+    }
   }
 }
 
@@ -382,14 +530,6 @@ __global__ __launch_bounds__(64) void k_unitary_eig(const double2 *W, int m, int
     theta_sorted[q * int64_t(ldt) + rank] = th;
   }
   if (failed && lane == 0) atomicOr(&flags[q / flag_div], BE_ST_NONCONVERGED);
-}
-
-// LDS ordering between the lanes of one wave (the wave's LDS operations
-// complete in program order; this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Window of the QR sweep held in LDS: rows and columns rb .. rb + QW - 1.
@@ -838,36 +978,53 @@ __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uin
   if (tid == 0) fb[q] = s_bad;
 }
 
-// Chern winding of each system from theta [line][ldt] (first m valid).
-__global__ void k_winding(const double *theta, int ldt, int m, int n_sys, int n_perp, double *phi, int32_t *winding,
-                          uint32_t *status) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
+// Chern winding of each system from theta [line][ldt] (first m valid): one
+// wave per system, a lane per transverse line (one thread per system waited
+// out a memory access per phase: 118 us for 32 lines of 48 phases).
+__global__ __launch_bounds__(64) void k_winding(const double *theta, int ldt, int m, int n_sys, int n_perp, double *phi,
+                                                int32_t *winding, uint32_t *status) {
+  const int s = blockIdx.x, lane = threadIdx.x;
   if (s >= n_sys) return;
+  auto phase_sum = [&](int i) {
+    double acc = 0.0;
+    const double *th = theta + (int64_t(s) * n_perp + i) * ldt;
+#pragma unroll 8
+    for (int n = 0; n < m; ++n) acc += th[n];
+    double ph = acc - TWO_PI * floor(acc / TWO_PI);
+    if (ph >= TWO_PI) ph -= TWO_PI;
+    return ph;
+  };
   double total = 0.0, dmax = 0.0;
-  double prev = 0.0, first = 0.0;
-  for (int i = 0; i <= n_perp; ++i) {
-    double ph;
-    if (i < n_perp) {
-      double acc = 0.0;
-      const double *th = theta + (int64_t(s) * n_perp + i) * ldt;
-      for (int n = 0; n < m; ++n) acc += th[n];
-      ph = acc - TWO_PI * floor(acc / TWO_PI);
-      if (ph >= TWO_PI) ph -= TWO_PI;
-      if (phi) phi[int64_t(s) * n_perp + i] = ph;
-      if (i == 0) first = ph;
-    } else {
-      ph = first;
-    }
-    if (i > 0) {
+  const double first = phase_sum(0);
+  double carry = first;  // phase of the line before this round's first
+  for (int i0 = 0; i0 < n_perp; i0 += 64) {
+    const int i = i0 + lane;
+    const double ph = i < n_perp ? phase_sum(i) : first;
+    if (i < n_perp && phi) phi[int64_t(s) * n_perp + i] = ph;
+    double prev = __shfl_up(ph, 1, 64);
+    if (lane == 0) prev = carry;
+    carry = __shfl(ph, 63, 64);
+    // the step into line i, and from the last line back to the first
+    if (i <= n_perp && i > 0) {
       double d = ph - prev;
       d -= TWO_PI * rint(d / TWO_PI);
       total += d;
       dmax = fmax(dmax, fabs(d));
     }
-    prev = ph;
   }
-  double c = total / TWO_PI;
-  int ci = int(rint(c));
+  if (n_perp % 64 == 0 && lane == 0) {  // the closing step fell outside the last round
+    double d = first - carry;
+    d -= TWO_PI * rint(d / TWO_PI);
+    total += d;
+    dmax = fmax(dmax, fabs(d));
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    total += __shfl_xor(total, o, 64);
+    dmax = fmax(dmax, __shfl_xor(dmax, o, 64));
+  }
+  if (lane != 0) return;
+  const double c = total / TWO_PI;
+  const int ci = int(rint(c));
   winding[s] = ci;
   if (dmax > 0.8 * M_PI || fabs(c - ci) > 1e-6) atomicOr(&status[s], BE_ST_WINDING_UNRESOLVED);
 }
@@ -887,6 +1044,42 @@ namespace be {
 static int unitary_phases(be_ctx *ctx, const double2 *cur, int m, int64_t n_lines, double2 *Hs, double2 *Zout,
                           double *theta_sorted, int ldt, double *theta_raw, uint32_t *line_status, hipStream_t stream, bool unitary = true);
 
+// wilson_core for loops of few bands (small_loop_fits), as described there.
+static int small_loop(be_ctx *ctx, Grid U, int N, int m, int64_t n_lines, int n_loop, int mode, double *theta_sorted,
+                      int ldt, double2 *Zout, double *theta_raw, uint32_t *line_status, const double2 **Fkeep,
+                      hipStream_t stream, double2 *Wout) {
+  const int64_t mm = int64_t(m) * m;
+  double2 *F = nullptr, *W = Wout, *Hs = nullptr;
+  Carve cv;
+  if (Fkeep) cv.add(&F, size_t(n_lines * n_loop * mm));
+  if (!Wout) cv.add(&W, size_t(n_lines * mm));
+  cv.add(&Hs, size_t(n_lines * mm));
+  BE_RET_IF(cv.commit(ctx, stream, WS_WILSON));
+  {
+    ProfScope prof(ctx, "small_loop", stream);
+    const dim3 grid(static_cast<uint32_t>(n_lines)), block(kSmallThreads);
+    const int P = m == 1 ? 1 : m == 2 ? 4 : m <= 4 ? 16 : 64;
+    const size_t sm = size_t(n_loop * mm + 2 * (kSmallThreads / P) * mm) * sizeof(double2);
+    const int polar = mode == BE_OVL_POLAR;
+    if (P == 1) hipLaunchKernelGGL(k_small_loop<1>, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, line_status);
+    if (P == 4) hipLaunchKernelGGL(k_small_loop<4>, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, line_status);
+    if (P == 16)
+      hipLaunchKernelGGL(k_small_loop<16>, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, line_status);
+    if (P == 64)
+      hipLaunchKernelGGL(k_small_loop<64>, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, line_status);
+    BE_RET_IF(check_launch(ctx, "small_loop"));
+  }
+  if (Fkeep) *Fkeep = F;
+  if (Wout) return BE_OK;
+  if (m == 1) {
+    hipLaunchKernelGGL(k_phase_1, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, W, n_lines,
+                       theta_sorted, ldt, theta_raw, Zout);
+    return check_launch(ctx, "phase_1");
+  }
+  return unitary_phases(ctx, W, m, n_lines, Hs, Zout, theta_sorted, ldt, theta_raw, line_status, stream,
+                        mode == BE_OVL_POLAR);
+}
+
 // Wilson loops of n_lines closed lines of a grid of N x m matrices.
 // theta_sorted: [line][ldt]; Zout/theta_raw: optional eigenvectors of each W
 // (m x m per line) and the phase of each column. Fkeep: if non-null receives
@@ -899,6 +1092,9 @@ static int wilson_core(be_ctx *ctx, Grid U, int N, int m, int64_t n_lines, int n
   if (m == 0) return BE_OK;
   const int64_t mm = int64_t(m) * m;
   const int64_t nm = n_lines * n_loop;
+  if (small_loop_fits(N, m, n_loop))
+    return small_loop(ctx, U, N, m, n_lines, n_loop, mode, theta_sorted, ldt, Zout, theta_raw, line_status, Fkeep,
+                      stream, Wout);
   double2 *F = nullptr, *B1 = nullptr, *B2 = nullptr, *Hs = nullptr;
   double *err = nullptr;
   int *act = nullptr, *n_left = nullptr;
@@ -1000,8 +1196,9 @@ static int wilson_core(be_ctx *ctx, Grid U, int N, int m, int64_t n_lines, int n
       }
     }
     // every matrix's latest iterate into F
-    hipLaunchKernelGGL(k_copy_mats_loc, dim3(64, static_cast<uint32_t>(std::min<int64_t>(nm, 65535))), dim3(256), 0,
-                       stream, B2, F, mm, nm, loc);
+    hipLaunchKernelGGL(k_copy_mats_loc, dim3(static_cast<uint32_t>(std::min<int64_t>((mm + 255) / 256, 64)),
+                                             static_cast<uint32_t>(std::min<int64_t>(nm, 65535))),
+                       dim3(256), 0, stream, B2, F, mm, nm, loc);
     BE_RET_IF(check_launch(ctx, "copy_mats_loc"));
     // matrices whose last Gram error stayed at or above 1e-7 did not
     // converge: (near) singular overlaps
@@ -1224,7 +1421,7 @@ extern "C" int be_wilson_loop(be_ctx *ctx, const void *U, int32_t N, int32_t m, 
   }
   hipLaunchKernelGGL(k_or_lines, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, line_st,
                      n_lines, n_perp, status);
-  hipLaunchKernelGGL(k_winding, dim3((n_sys + 63) / 64), dim3(64), 0, stream, theta, m, m, n_sys, n_perp, phi, winding,
+  hipLaunchKernelGGL(k_winding, dim3(n_sys), dim3(64), 0, stream, theta, m, m, n_sys, n_perp, phi, winding,
                      status);
   return check_launch(ctx, "winding");
 }
@@ -1249,14 +1446,16 @@ __global__ void k_sector_count(const double *theta_raw, int m, int64_t n_lines, 
   if (edge) line_st[line] |= BE_ST_WANNIER_GAP;
 }
 
-// Per system: sector size of line 0; WANNIER_GAP if any line differs.
-__global__ void k_sector_sys(const int32_t *s_line, int n_sys, int n_perp, int32_t *s_sys, uint32_t *status) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
+// Per system (one wave): sector size of line 0; WANNIER_GAP if any line differs.
+__global__ __launch_bounds__(64) void k_sector_sys(const int32_t *s_line, int n_sys, int n_perp, int32_t *s_sys,
+                                                   uint32_t *status) {
+  const int s = blockIdx.x;
   if (s >= n_sys) return;
-  int s0 = s_line[int64_t(s) * n_perp];
-  for (int i = 1; i < n_perp; ++i)
-    if (s_line[int64_t(s) * n_perp + i] != s0) atomicOr(&status[s], BE_ST_WANNIER_GAP);
-  s_sys[s] = s0;
+  const int s0 = s_line[int64_t(s) * n_perp];
+  bool differ = false;
+  for (int i = threadIdx.x; i < n_perp; i += 64) differ = differ || s_line[int64_t(s) * n_perp + i] != s0;
+  if (__any(differ) && threadIdx.x == 0) atomicOr(&status[s], BE_ST_WANNIER_GAP);
+  if (threadIdx.x == 0) s_sys[s] = s0;
 }
 
 // nu[line][0] = Z_line[:, sector] (m x sc, ld m), in the order of the columns.
@@ -1276,32 +1475,41 @@ __global__ void k_gather_sector(const double2 *Z, const double *theta_raw, int m
   }
 }
 
-// p[s][j] and p_mean[s] from nested theta [s][j][ldt] (first sc valid).
-__global__ void k_nested_p(const double *th, int ldt, int sc, int n_sys, int n_par, double *p, double *p_mean) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
+// p[s][j] and p_mean[s] from nested theta [s][j][ldt] (first sc valid): one
+// wave per system. With the wrapped steps d_j between neighbouring base
+// points, the mean of the unwrapped p is p_0 + sum_j d_j (n - j) / n.
+__global__ __launch_bounds__(64) void k_nested_p(const double *th, int ldt, int sc, int n_sys, int n_par, double *p,
+                                                 double *p_mean) {
+  const int s = blockIdx.x, lane = threadIdx.x;
   if (s >= n_sys) return;
-  double prev = 0.0, acc_u = 0.0, sum = 0.0;
-  for (int j = 0; j < n_par; ++j) {
-    double a = 0.0;
-    const double *t = th + (int64_t(s) * n_par + j) * ldt;
-    for (int n = 0; n < sc; ++n) a += t[n];
-    double pj = a / TWO_PI;
-    pj -= rint(pj);
-    if (pj <= -0.5) pj += 1.0;
-    if (pj > 0.5) pj -= 1.0;
-    if (fabs(fabs(pj) - 0.5) < 1e-15) pj = 0.5;
-    p[int64_t(s) * n_par + j] = pj;
-    if (j == 0) {
-      acc_u = pj;
-    } else {
+  double carry = 0.0, p0 = 0.0, sum = 0.0;
+  for (int j0 = 0; j0 < n_par; j0 += 64) {
+    const int j = j0 + lane;
+    double pj = 0.0;
+    if (j < n_par) {
+      double a = 0.0;
+      const double *t = th + (int64_t(s) * n_par + j) * ldt;
+      for (int n = 0; n < sc; ++n) a += t[n];
+      pj = a / TWO_PI;
+      pj -= rint(pj);
+      if (pj <= -0.5) pj += 1.0;
+      if (pj > 0.5) pj -= 1.0;
+      if (fabs(fabs(pj) - 0.5) < 1e-15) pj = 0.5;
+      p[int64_t(s) * n_par + j] = pj;
+    }
+    double prev = __shfl_up(pj, 1, 64);
+    if (lane == 0) prev = carry;
+    carry = __shfl(pj, 63, 64);
+    if (j == 0) p0 = pj;
+    if (j > 0 && j < n_par) {
       double d = pj - prev;
       d -= rint(d);
-      acc_u += d;
+      sum += d * double(n_par - j);
     }
-    sum += acc_u;
-    prev = pj;
   }
-  double mean = sum / n_par;
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if (lane != 0) return;
+  double mean = p0 + sum / n_par;
   mean -= floor(mean);
   if (mean >= 1.0) mean -= 1.0;
   p_mean[s] = mean;
@@ -1359,7 +1567,7 @@ extern "C" int be_nested_wilson(be_ctx *ctx, const void *U, int32_t N, int32_t m
                      n_lines, win_lo, win_hi, s_line, line_st);
   hipLaunchKernelGGL(k_or_lines, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, line_st,
                      n_lines, n_perp, status);
-  hipLaunchKernelGGL(k_sector_sys, dim3((n_sys + 63) / 64), dim3(64), 0, stream, s_line, n_sys, n_perp, s_sys, status);
+  hipLaunchKernelGGL(k_sector_sys, dim3(n_sys), dim3(64), 0, stream, s_line, n_sys, n_perp, s_sys, status);
   BE_RET_IF(check_launch(ctx, "sector"));
   int32_t *hs = static_cast<int32_t *>(ctx->pinned);
   BE_CHECK_ARG(ctx, n_sys <= 1024, "be_nested_wilson: at most 1024 systems per call");
@@ -1384,7 +1592,16 @@ extern "C" int be_nested_wilson(be_ctx *ctx, const void *U, int32_t N, int32_t m
                        nl, win_lo, win_hi, sc, n_par, nu);
     BE_RET_IF(check_launch(ctx, "gather_sector"));
     // transport nu[line][j+1] = F[line][j] nu[line][j]
-    for (int j = 0; j + 1 < n_par; ++j) {
+    if (m <= kSmallM) {
+      ProfScope prof(ctx, "transport", stream);
+      const dim3 grid(static_cast<uint32_t>(nl)), block(64);
+      const double2 *Fl = F + l0 * n_par * mm;
+      if (m <= 2) hipLaunchKernelGGL(k_transport_small<2>, grid, block, 0, stream, Fl, nu, m, sc, n_par);
+      else if (m <= 4) hipLaunchKernelGGL(k_transport_small<4>, grid, block, 0, stream, Fl, nu, m, sc, n_par);
+      else hipLaunchKernelGGL(k_transport_small<8>, grid, block, 0, stream, Fl, nu, m, sc, n_par);
+      BE_RET_IF(check_launch(ctx, "transport"));
+    }
+    for (int j = 0; m > kSmallM && j + 1 < n_par; ++j) {
       ZGemm t;
       t.M = m;
       t.N = sc;
@@ -1444,7 +1661,7 @@ extern "C" int be_nested_wilson(be_ctx *ctx, const void *U, int32_t N, int32_t m
                           line_st2 + int64_t(s0) * n_par, nullptr, stream));
     hipLaunchKernelGGL(k_or_lines, dim3(static_cast<uint32_t>((nl2 + 255) / 256)), dim3(256), 0, stream,
                        line_st2 + int64_t(s0) * n_par, nl2, n_par, status + s0);
-    hipLaunchKernelGGL(k_nested_p, dim3((s1 - s0 + 63) / 64), dim3(64), 0, stream, nested_theta + int64_t(s0) * n_par * m, m,
+    hipLaunchKernelGGL(k_nested_p, dim3(s1 - s0), dim3(64), 0, stream, nested_theta + int64_t(s0) * n_par * m, m,
                        sc, s1 - s0, n_par, p + int64_t(s0) * n_par, p_mean + s0);
     BE_RET_IF(check_launch(ctx, "nested_p"));
     s0 = s1;
@@ -1481,16 +1698,16 @@ __global__ void k_pso_post(const double *ev, const uint32_t *eig_st, int m, int6
   if (es) atomicOr(&status[k / k_per_sys], es);
 }
 
-__global__ void k_pso_sys(const int32_t *cnt, int n_sys, int64_t k_per_sys, int32_t *m_dn, uint32_t *status) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
+// Per system (one wave): spin-down count of its first k-point; PSO_GAP if any k-point differs.
+__global__ __launch_bounds__(64) void k_pso_sys(const int32_t *cnt, int n_sys, int64_t k_per_sys, int32_t *m_dn,
+                                                uint32_t *status) {
+  const int s = blockIdx.x;
   if (s >= n_sys) return;
-  int c0 = cnt[int64_t(s) * k_per_sys];
-  for (int64_t k = 1; k < k_per_sys; ++k)
-    if (cnt[int64_t(s) * k_per_sys + k] != c0) {
-      atomicOr(&status[s], BE_ST_PSO_GAP);
-      break;
-    }
-  m_dn[s] = c0;
+  const int c0 = cnt[int64_t(s) * k_per_sys];
+  bool differ = false;
+  for (int64_t k = threadIdx.x; k < k_per_sys; k += 64) differ = differ || cnt[int64_t(s) * k_per_sys + k] != c0;
+  if (__any(differ) && threadIdx.x == 0) atomicOr(&status[s], BE_ST_PSO_GAP);
+  if (threadIdx.x == 0) m_dn[s] = c0;
 }
 
 // Sector sizes given by the caller for a captured call (at most 256 systems).
@@ -1577,7 +1794,7 @@ int spin_operator_eig(be_ctx *ctx, const void *U, int32_t N, int32_t m, int32_t 
   BE_RET_IF(erc);
   hipLaunchKernelGGL(k_pso_post, dim3(static_cast<uint32_t>((n_k + 255) / 256)), dim3(256), 0, stream, ev, kst, m, n_k,
                      kps, pso_evals, cnt, status);
-  hipLaunchKernelGGL(k_pso_sys, dim3((n_sys + 63) / 64), dim3(64), 0, stream, cnt, n_sys, kps, mdn, status);
+  hipLaunchKernelGGL(k_pso_sys, dim3(n_sys), dim3(64), 0, stream, cnt, n_sys, kps, mdn, status);
   BE_RET_IF(check_launch(ctx, "pso"));
   if (stream_capturing(stream)) {
     BE_CHECK_ARG(ctx, n_sys <= 256, "spin sectors under graph capture: at most 256 systems per call");
@@ -1687,7 +1904,7 @@ extern "C" int be_spin_resolved_wilson(be_ctx *ctx, const void *U, int32_t N, in
       BE_RET_IF(wilson_core(ctx, gv, N, ms, nl, n_par, mode, th, m, nullptr, nullptr, ls, nullptr, stream));
       hipLaunchKernelGGL(k_or_lines, dim3(static_cast<uint32_t>((nl + 255) / 256)), dim3(256), 0, stream, ls, nl, n_perp,
                          status + s0);
-      hipLaunchKernelGGL(k_winding, dim3((s1 - s0 + 63) / 64), dim3(64), 0, stream, th, m, ms, s1 - s0, n_perp, nullptr,
+      hipLaunchKernelGGL(k_winding, dim3(s1 - s0), dim3(64), 0, stream, th, m, ms, s1 - s0, n_perp, nullptr,
                          (sector == 0 ? C_dn : C_up) + s0, status + s0);
       BE_RET_IF(check_launch(ctx, "spin winding"));
     }

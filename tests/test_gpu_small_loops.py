@@ -1,0 +1,92 @@
+"""Loop stage for few bands (m <= 8): the one-launch path and the sizes at its edges against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import berry as orc
+from tests.phase_metrics import phase_set_error
+
+pytestmark = pytest.mark.gpu
+
+# phases of a product of n <= 64 polar factors of order <= 9, each within
+# ~10 m eps / sigma_min of its limit (sigma_min > 0.02 here): below 64 * 10 *
+# 9 * 2.2e-16 / 0.02 = 6e-11
+TOL = 6e-11
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from tests import gpu_util
+    gpu_util.need_gpu()
+    return gpu_util.ctx()
+
+
+def smooth_grid(n_perp, n_par, N, m, seed):
+    """Random orthonormal bases that turn slowly along both directions."""
+    rng = np.random.default_rng(seed)
+    a = rng.standard_normal((5, N, m)) + 1j * rng.standard_normal((5, N, m))
+    U = np.empty((n_perp, n_par, N, m), dtype=np.complex128)
+    for i in range(n_perp):
+        for j in range(n_par):
+            x, y = 2 * np.pi * j / n_par, 2 * np.pi * i / n_perp
+            U[i, j] = np.linalg.qr(1.5 * a[0] + np.cos(x) * a[1] + np.sin(x) * a[2] + np.cos(y) * a[3] + np.sin(y) * a[4])[0]
+    return U
+
+
+def on_device(U, pad=1):
+    """U-grid [n_perp, n_par, N, m] as column-major matrices of leading dimension N + pad."""
+    import torch
+    n_perp, n_par, N, m = U.shape
+    t = torch.zeros((n_perp * n_par, m, N + pad), dtype=torch.complex128, device="cuda")
+    t[:, :, :N] = torch.from_numpy(np.ascontiguousarray(U.reshape(-1, N, m).transpose(0, 2, 1))).cuda()
+    return t
+
+
+# m: 1 and each edge of the lane groups (1, 4, 16, 64 lanes per link) up to the first order past them; N: the largest
+# order of the path and the next; n_par: one link, fewer and more links than groups, the longest line (48 KB) and the next
+@pytest.mark.parametrize("m, N, n_par", [(1, 2, 1), (1, 64, 300), (2, 4, 3), (2, 7, 65), (3, 64, 17), (4, 9, 16),
+                                         (5, 12, 5), (8, 64, 48), (8, 64, 49), (8, 65, 6), (9, 20, 7)])
+@pytest.mark.parametrize("mode", ["polar", "raw"])
+def test_wilson_loop_of_few_bands(ctx, m, N, n_par, mode):
+    import torch
+    from paper_2312_13051_amd._lib import BE_OVL_POLAR, BE_OVL_RAW
+    n_perp = 5
+    U = smooth_grid(n_perp, n_par, N, m, [m, N, n_par])
+    Ud = on_device(U)
+    f8 = dict(dtype=torch.float64, device="cuda")
+    th, ph = torch.empty((1, n_perp, m), **f8), torch.empty((1, n_perp), **f8)
+    wn, st = (torch.empty(1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ctx.wilson_loop(Ud, N, m, N + 1, Ud.stride(0), 1, n_par, n_perp, BE_OVL_POLAR if mode == "polar" else BE_OVL_RAW,
+                    th, ph, wn, st)
+    theta, phi, C, status = orc.wilson_loop_grid(U, mode)
+    assert phase_set_error(th[0].cpu().numpy(), theta) < TOL
+    d = ph[0].cpu().numpy() - phi
+    assert np.abs(d - 2 * np.pi * np.round(d / (2 * np.pi))).max() < m * TOL
+    assert int(st[0]) == status
+    assert int(wn[0]) == C
+
+
+# the winding takes 64 lines a round: one line, a full round and one past it
+@pytest.mark.parametrize("n_perp", [1, 63, 64, 65, 130])
+def test_winding_over_many_lines(ctx, n_perp):
+    import synthetic as syn
+    from paper_2312_13051_amd import pipeline
+    hl, kg = syn.qwz(1.5), syn.kplane(12, n_perp, k0=(0.1, 0.2, 0.0))
+    out, ref = pipeline.wsurf(ctx, [hl], kg, 0, 1), orc.wilson_surface(hl, kg, 0, 1)
+    assert int(out["winding"][0]) == ref["winding"]
+    assert int(out["status"][0]) == ref["status"]
+
+
+# nested loop: sectors carried along the line a wave per line (m <= 8) for odd and even lengths around its prefetch
+@pytest.mark.parametrize("n_par, n_perp", [(3, 6), (4, 7), (5, 64), (6, 5), (9, 65)])
+def test_nested_loop_of_few_bands(ctx, n_par, n_perp):
+    import synthetic as syn
+    from paper_2312_13051_amd import pipeline
+    hl, kg = syn.bbh(0.4, 1.0), syn.kplane(n_par, n_perp, k0=(0.07, 0.11, 0.0))
+    # two decoupled copies at different couplings: four bands, two Wannier bands in the window
+    for h, m in ((hl, 2), (syn.concat_hops([hl, syn.bbh(0.55, 1.0)]), 4)):
+        ref = orc.nested_wilson(h, kg, 0, m)
+        out = pipeline.wnwl(ctx, [h], kg, 0, m)
+        assert out["s"][0] == ref["s"]
+        assert int(out["status"][0]) == ref["status"]
+        if ref["theta"] is not None:
+            assert phase_set_error(out["theta"][0, :, :ref["s"]].cpu().numpy(), ref["theta"]) < TOL
