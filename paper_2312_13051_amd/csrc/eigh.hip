@@ -34,6 +34,8 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "eigh_small.hpp"
+#include "tridiag.hpp"
 
 namespace {
 
@@ -336,8 +338,9 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? (NT == 1024 ? 1 : CW == 4 ? 6 
 #pragma unroll 1
           for (int k = 0; k < gw; k += CW) chunk(k, std::true_type{});
         } else {
+          // columns past the matrix (the last block's) add nothing and are not read back
 #pragma unroll 1
-          for (int k = 0; k < gw; k += CW) chunk(k, std::false_type{});
+          for (int k = 0; k < gw && cb0 + k < N; k += CW) chunk(k, std::false_type{});
         }
         part[(bi * nslot + bj * S + g) * 64 + lane] = mk<C>(yr, yi);
         it += nw;
@@ -445,58 +448,6 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? (NT == 1024 ? 1 : CW == 4 ? 6 
 }
 
 // ---------------------------------------------------------------- tridiagonal solver
-// a / b as a times the hardware reciprocal of b refined by one Newton-Raphson
-// step: within a few ulps of the rounded quotient, for normal b (the Sturm
-// recurrence keeps |b| >= pivmin >= DBL_MIN, so 1/b and a/b stay finite).
-__device__ __forceinline__ double div_nr(double a, double b) {
-  double r = __builtin_amdgcn_rcp(b);
-  r = fma(fma(-b, r, 1.0), r, r);
-  return a * r;
-}
-
-// Number of eigenvalues of T below x (Sturm sequence of the LDL^T
-// factorization of T - x I). The quotient uses div_nr: the count is that of a
-// matrix within a few ulps of T, the same kind of backward error the
-// correctly rounded division gives.
-__device__ __forceinline__ int sturm_count(const double *sd, const double *se2, int N, double x, double pivmin) {
-  int cnt = 0;
-  double qv = sd[0] - x;
-  if (fabs(qv) < pivmin) qv = -pivmin;
-  cnt += qv < 0.0;
-  for (int i = 1; i < N; ++i) {
-    qv = (sd[i] - x) - div_nr(se2[i - 1], qv);
-    if (fabs(qv) < pivmin) qv = -pivmin;
-    cnt += qv < 0.0;
-  }
-  return cnt;
-}
-
-// The same count from the interleaved pairs sde[i] = (d_i, e_{i-1}^2): one
-// LDS read per step, four steps' reads issued together.
-__device__ __forceinline__ int sturm_count_i(const double2 *sde, int N, double x, double pivmin) {
-  int cnt = 0;
-  double qv = sde[0].x - x;
-  if (fabs(qv) < pivmin) qv = -pivmin;
-  cnt += qv < 0.0;
-#pragma unroll 4
-  for (int i = 1; i < N; ++i) {
-    const double2 de = sde[i];
-    qv = (de.x - x) - div_nr(de.y, qv);
-    if (fabs(qv) < pivmin) qv = -pivmin;
-    cnt += qv < 0.0;
-  }
-  return cnt;
-}
-
-__device__ __forceinline__ double hash_unit(uint64_t a, uint64_t b) {
-  // splitmix64 of (a, b) -> uniform in (-1, 1)
-  uint64_t z = a * 0x9E3779B97F4A7C15ull + b + 0x632BE59BD9B4E019ull;
-  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-  z ^= z >> 31;
-  return (double)(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;
-}
-
 // Per-matrix scratch of the tridiagonal solver: lam [m + 1] = (||T||, selected
 // eigenvalues), Zs: 4 arrays [N][mp] (the diagonals met by the elimination of
 // inverse iteration, two arrays of orthonormalization scratch, x) with the
@@ -636,23 +587,6 @@ __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *
   }
 }
 
-// Tolerances relative to ||T||: split < block window < cluster gap, so a
-// cluster's window never reaches the next cluster. Eigenvalues closer than
-// the cluster tolerance (clu_rel, by default kCluRel = 1e-12) form a cluster, whose vectors are
-// computed as one invariant subspace (any orthonormal basis of it): inverse
-// iteration separates two eigenvalues only to about eps ||T|| / gap, so
-// below that gap their vectors can come out nearly parallel (a cluster of
-// eigenvalues spread over 1e-12 ||T|| - e.g. the projected spin operator's
-// +-1 clusters computed from refined eigenvectors, whose T splits into many
-// blocks - would otherwise have lanes pick blocks by windows narrower than
-// the cluster, and leave an orthonormalization that cannot converge). A
-// caller that needs the vectors of nearly equal eigenvalues resolved one by
-// one (and validates them) may pass a smaller tolerance.
-constexpr double kCluRel = 1e-12;
-__device__ __forceinline__ double tol_split(double tnorm) { return 16.0 * DBL_EPSILON * tnorm; }
-__device__ __forceinline__ double tol_window(double tnorm, double clu_rel) { return 0.5 * clu_rel * tnorm; }
-__device__ __forceinline__ double tol_cluster(double tnorm, double clu_rel) { return clu_rel * tnorm; }
-
 // (a4) eigenvectors by inverse iteration, one lane per eigenvector. T is
 // split where an off-diagonal is negligible; the k lanes of a k-fold
 // eigenvalue (equal within the cluster tolerance) take k distinct blocks that
@@ -698,151 +632,19 @@ __global__ __launch_bounds__(PT) void tri_invit(const double *d, const double *e
   double *Z0 = Zs + q * sZ;
   double *X = Z0 + int64_t(3) * N * mp;  // the fourth array (arrays 1 and 2 unused here)
   const double tiny = eps * fmax(tnorm, DBL_MIN);
-  const double dblk = tol_window(tnorm, clu_rel), dclu = tol_cluster(tnorm, clu_rel);
+  const double dclu = tol_cluster(tnorm, clu_rel);
   bool lane_bad = false;
   for (int c = tid; c < m; c += PT) {
-    int c0 = c, c1 = c + 1;
-    while (c0 > 0 && lam[c0] - lam[c0 - 1] <= dclu) --c0;
-    while (c1 < m && lam[c1] - lam[c1 - 1] <= dclu) ++c1;
-    const double wlo = lam[c0] - dblk, whi = lam[c1 - 1] + dblk;
-    const int jr = c - c0;
-    int bs = 0, bt = N, cnt = 0;
-    bool found = false, shared = false;
-    for (int b = 0; b < nblk && !found; ++b) {
-      const int s0 = sblk[b], t0 = sblk[b + 1];
-      const int nb = sturm_count(sd + s0, se2 + s0, t0 - s0, whi, pivmin) -
-                     sturm_count(sd + s0, se2 + s0, t0 - s0, wlo, pivmin);
-      if (nb > 0 && cnt + nb > jr) {
-        bs = s0;
-        bt = t0;
-        found = true;
-        shared = nb > 1;
-      }
-      cnt += nb;
-    }
+    const InvitBlock ib = invit_block(sd, se2, lam, m, c, sblk, nblk, N, tnorm, clu_rel, pivmin);
     // group id of the lane for the orthonormalization: lanes sharing a block
     // (block start + 2); a lane that found no block makes its whole cluster
     // one group (id 1, set below)
-    if (shared) smark[c] = bs + 2;
-    if (!found) sbad[c0] = 1;
-    // Lanes that share a block with other members of their cluster take
-    // shifts a few eps ||T|| apart: far larger than the splitting of a
-    // degenerate pair (so neither member dominates a lane's solve and each
-    // lane returns an independent combination of the cluster's vectors),
-    // far smaller than the distance to the next cluster.
-    const double lm = (!found || shared) ? lam[c] + (jr - 0.5 * (c1 - c0 - 1)) * 2.0 * eps * tnorm : lam[c];
+    if (ib.shared) smark[c] = ib.bs + 2;
+    if (!ib.found) sbad[ib.c0] = 1;
+    const int bs = ib.bs, bt = ib.bt;
     for (int i = 0; i < N; ++i)
       if (i < bs || i >= bt) X[int64_t(i) * mp + c] = 0.0;
-    // two solves: from a pseudo-random start the first already amplifies the
-    // wanted direction by ~1/(eps ||T||) against ~1/gap for the others. The
-    // second solve recomputes the same factorization (same operations, same
-    // factors) instead of storing it again, and takes the first solution's
-    // normalization as it reads it. Of the factorization only the diagonal
-    // a_i met at each elimination step is stored: the pivot choice of row i
-    // (|a_i| < |e_i|) and every factor entry follow from a_i, a_{i-1} and T,
-    // recomputed by the same operations in the back substitution.
-    // The loads of each sweep are issued PF rows ahead of the recurrence that
-    // consumes them, so the serial chain waits on memory once per PF rows.
-    // The start vector depends on the column only, not on the matrix's place
-    // in the batch: a matrix gets the same eigenvectors, bit for bit, in any
-    // batch (inside a degenerate cluster the start decides the basis).
-    constexpr int PF = 4;
-    double scale = 1.0;
-    for (int it = 0; it < 2; ++it) {
-      // forward elimination with partial pivoting on [T_block - lm I | rhs]
-      double a = sd[bs] - lm, b = bt - bs > 1 ? se[bs] : 0.0;
-      double r = it == 0 ? hash_unit(uint64_t(c) + 1, bs) : X[int64_t(bs) * mp + c] * scale;
-      // one elimination step at row i (i + 1 < bt) with right-hand side entry rn of row i + 1
-      auto step = [&](int i, double rn) {
-        const double ei = se[i], Dn = sd[i + 1] - lm, en = (i + 2 < bt) ? se[i + 1] : 0.0;
-        const int64_t o = int64_t(i) * mp + c;
-        if (it == 0) Z0[o] = a;
-        // without interchange: l = e_i / a (a = 0 only with e_i = 0, then
-        // taken as tiny), row i keeps (a, b); with interchange: l = a / e_i
-        const bool keep = fabs(a) >= fabs(ei);
-        const double ad = (keep && a == 0.0) ? tiny : a;
-        const double l = (keep ? ei : ad) / (keep ? ad : ei);
-        X[o] = keep ? r : rn;
-        const double p1 = keep ? Dn : b, p2 = keep ? b : Dn;
-        const double q1 = keep ? rn : r, q2 = keep ? r : rn;
-        a = p1 - l * p2;
-        b = keep ? en : -l * en;
-        r = q1 - l * q2;
-      };
-      if (it == 0) {
-        for (int i = bs; i + 1 < bt; ++i) step(i, hash_unit(uint64_t(c) + 1, i + 1));
-      } else {
-        for (int i0 = bs; i0 + 1 < bt; i0 += PF) {
-          double rv[PF];
-#pragma unroll
-          for (int u = 0; u < PF; ++u) rv[u] = i0 + u + 1 < bt ? X[int64_t(i0 + u + 1) * mp + c] : 0.0;
-#pragma unroll
-          for (int u = 0; u < PF; ++u)
-            if (i0 + u + 1 < bt) step(i0 + u, rv[u] * scale);
-        }
-      }
-      {
-        const int64_t o = int64_t(bt - 1) * mp + c;
-        if (it == 0) Z0[o] = a;
-        X[o] = r;
-      }
-      // back substitution: row i of the triangular factor is (e_i, D_{i+1},
-      // e_{i+1}) where row i was interchanged, else (a_i, b_i, 0) with b_i =
-      // e_i, or -(a_{i-1} / e_{i-1}) e_i after an interchange at row i-1
-      double x1 = 0.0, x2 = 0.0, nrm = 0.0;
-      double ai = Z0[int64_t(bt - 1) * mp + c];
-      for (int i0 = bt - 1; i0 >= bs; i0 -= PF) {
-        double xv[PF], av[PF];
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-          const int i = i0 - u;
-          xv[u] = i >= bs ? X[int64_t(i) * mp + c] : 0.0;
-          av[u] = i > bs ? Z0[int64_t(i - 1) * mp + c] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-          const int i = i0 - u;
-          if (i >= bs) {
-            const double ap = av[u];
-            double z0, z1 = 0.0, z2 = 0.0;
-            if (i == bt - 1) {
-              z0 = ai == 0.0 ? tiny : ai;
-            } else if (fabs(ai) >= fabs(se[i])) {
-              z0 = ai == 0.0 ? tiny : ai;
-              z1 = se[i];
-              if (i > bs && !(fabs(ap) >= fabs(se[i - 1]))) {
-                const double l = ap / se[i - 1];
-                z1 = -l * se[i];
-              }
-            } else {
-              z0 = se[i];
-              z1 = sd[i + 1] - lm;
-              z2 = (i + 2 < bt) ? se[i + 1] : 0.0;
-            }
-            const double xi = (xv[u] - z1 * x1 - z2 * x2) / z0;
-            X[int64_t(i) * mp + c] = xi;
-            x2 = x1;
-            x1 = xi;
-            nrm = fma(xi, xi, nrm);
-            ai = ap;
-          }
-        }
-      }
-      const double inv = 1.0 / sqrt(nrm);
-      if (!isfinite(inv) || inv == 0.0) lane_bad = true;
-      if (it == 0) {
-        scale = inv;
-      } else {
-        for (int i0 = bs; i0 < bt; i0 += PF) {
-          double xv[PF];
-#pragma unroll
-          for (int u = 0; u < PF; ++u) xv[u] = i0 + u < bt ? X[int64_t(i0 + u) * mp + c] : 0.0;
-#pragma unroll
-          for (int u = 0; u < PF; ++u)
-            if (i0 + u < bt) X[int64_t(i0 + u) * mp + c] = xv[u] * inv;
-        }
-      }
-    }
+    if (!invit_vector<true>(sd, se, bs, bt, ib.lm, tiny, c, X, Z0, mp)) lane_bad = true;
   }
   __syncthreads();
   for (int c = tid; c < m; c += PT) {
@@ -851,15 +653,6 @@ __global__ __launch_bounds__(PT) void tri_invit(const double *d, const double *e
     marks[q * m + c] = sbad[c0] ? 1 : smark[c];
   }
   if (lane_bad) atomicOr(&status[q], uint32_t(BE_ST_NONCONVERGED));
-}
-
-// End of the orthonormalization group starting at c0: the following lanes of
-// the same cluster with the same group id (0: no group, a group of one).
-__device__ __forceinline__ int group_end(const double *lam, const int *mk, int m, int c0, double dclu) {
-  int c1 = c0 + 1;
-  if (mk[c0] == 0) return c1;
-  while (c1 < m && mk[c1] == mk[c0] && lam[c1] - lam[c1 - 1] <= dclu) ++c1;
-  return c1;
 }
 
 // Groups of vectors that share a block of T (inside a cluster of equal
@@ -1263,6 +1056,10 @@ __global__ void assemble_tpair(const C *T1, const C *T2, int64_t sT, C *Tb, int 
   }
 }
 
+// Workgroups per matrix of an elementwise copy of n values (256 threads each):
+// small matrices take one, so that large batches of them do not launch empty ones.
+uint32_t copy_blocks(int64_t n) { return static_cast<uint32_t>(std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 64))); }
+
 size_t panel_smem(int N, size_t csize, int nt) { return panel_part_offset(N, csize, nt) + 64; }
 
 // Bytes of the matrix-vector product's partial vectors for trailing matrices
@@ -1297,6 +1094,7 @@ using PanelFn = void (*)(typename CT<T>::c *, int64_t, int, int, int, int, typen
 template <typename T, bool PL>
 PanelFn<T> panel_kernel_pl(int nt, int cw) {
   constexpr bool f32 = sizeof(T) == 4;
+  if (nt == 64) return &hetrd_panel<T, 64, PL, 4>;
   if (nt == 256) return &hetrd_panel<T, 256, PL, 4>;
   if (nt == 512) return (f32 && cw == 8) ? &hetrd_panel<T, 512, PL, f32 ? 8 : 4> : &hetrd_panel<T, 512, PL, 4>;
   return &hetrd_panel<T, 1024, PL, f32 ? 8 : 4>;
@@ -1518,7 +1316,8 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
   cv.add(&Tm, size_t(nb_mat) * P * NB * NB);
   cv.add(&dd, size_t(nb_mat) * N);
   cv.add(&ee, size_t(nb_mat) * N);
-  cv.add(&Zs, size_t(nb_mat) * 4 * N * mp);
+  const bool small = N <= kSmallOrder;  // the tridiagonal part in one launch, in LDS
+  if (!small) cv.add(&Zs, size_t(nb_mat) * 4 * N * mp);
   double *lamg = nullptr;
   int *marks = nullptr;
   cv.add(&lamg, size_t(nb_mat) * (m + 1));
@@ -1526,7 +1325,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
   double *Gm = nullptr, *oerr = nullptr;
   int *nact = nullptr, *n_left = nullptr;
   unsigned char *nloc = nullptr;
-  cv.add(&Gm, size_t(nb_mat) * std::max(m, 1) * std::max(m, 1));
+  if (!small) cv.add(&Gm, size_t(nb_mat) * std::max(m, 1) * std::max(m, 1));
   cv.add(&oerr, size_t(nb_mat));
   cv.add(&nact, size_t(nb_mat));
   cv.add(&nloc, size_t(nb_mat));
@@ -1591,7 +1390,18 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
       BE_RET_IF(GemmOf<T>::run(ctx, g, stream));
     }
   }
+  // back-transformation target: the output itself (FP64) or an FP32 copy (mixed)
+  C *Ut = mixed ? Uw : reinterpret_cast<C *>(U);
+  const int ldt = mixed ? N : ldu;
+  const int64_t ust = mixed ? int64_t(N) * m : us;
+  if constexpr (sizeof(T) == sizeof(float)) {
+    if (small) {
+      BE_RET_IF(tri_small_c64(ctx, dd, ee, N, nb_mat, lo, hi, evals, Ut, ldt, ust, status, stream, clu_rel, 2e-7));
+      if (m == 0) return BE_OK;
+    }
+  }
   // ---- tridiagonal eigenpairs: bisection, inverse iteration, Gram-Schmidt of shared-block clusters
+  if (!small) {
   {
     const size_t smb = (4 * size_t(N) + m + 4) * sizeof(double);
     if (smb > 65536)
@@ -1626,10 +1436,6 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
                        clu_rel, status);
   }
   BE_RET_IF(check_launch(ctx, "tri_gs"));
-  // back-transformation target: the output itself (FP64) or an FP32 copy (mixed)
-  C *Ut = mixed ? Uw : reinterpret_cast<C *>(U);
-  const int ldt = mixed ? N : ldu;
-  const int64_t ust = mixed ? int64_t(N) * m : us;
   // ---- symmetric orthonormalization of Z (Newton-Schulz on the Gram matrix),
   // Z held as X = Z^T (m x N, leading dim mp), each matrix until max |X X^T - I|
   // is below 1e-14 (FP64 path), or 2e-7 on the mixed path, whose FP32
@@ -1707,6 +1513,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
                        X0, X1, nloc, sZ, mp, N, m, Ut, ldt, ust);
     BE_RET_IF(check_launch(ctx, "z_to_u"));
   }
+  }
   // ---- back-transformation by pairs of panels (pa, pb = pa + 1), last pair
   // first; with an odd panel count the first panel runs alone at the end.
   // Columns p0 .. p0 + nbc of H hold V = [V1 V2] explicitly (zeros above the
@@ -1779,7 +1586,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
                    -1.0, 1.0));
   }
   if (mixed) {
-    hipLaunchKernelGGL(widen_u, dim3(64, static_cast<uint32_t>(nb_mat)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(widen_u, dim3(copy_blocks(int64_t(N) * m), static_cast<uint32_t>(nb_mat)), dim3(256), 0, stream,
                        reinterpret_cast<const float2 *>(Uw), int64_t(N) * m, N, m, U, ldu, us);
     BE_RET_IF(check_launch(ctx, "widen_u"));
   }
@@ -1824,8 +1631,8 @@ static size_t eigh_chunk_bytes(be_ctx *ctx, int N, int m) {
   return cs * (size_t(N) * 3 * NB + size_t(P) * NB * NB + 4 * size_t(NB) * std::max(m, 1) + 6 * size_t(NB) * NB +
                size_t(N) * std::max(m, 1)) +
          (panel_part_lds(N, cs, panel_threads(ctx, N, cs)) ? 0 : panel_part_bytes(N - 1, cs)) +
-         sizeof(double) * (3 * size_t(N) + 4 * size_t(N) * mp + size_t(std::max(m, 1)) * std::max(m, 1) + size_t(m) +
-                           1) +
+         sizeof(double) * (3 * size_t(N) + size_t(m) + 1 +
+                           (N <= kSmallOrder ? 0 : 4 * size_t(N) * mp + size_t(std::max(m, 1)) * std::max(m, 1))) +
          sizeof(int) * size_t(std::max(m, 1)) + 16 * 256;
 }
 
@@ -1863,6 +1670,11 @@ static int eigh_run(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t ma
   const int m = band_hi - band_lo;
   BE_RET_IF(check_eigh_lds(ctx, N, m, sizeof(typename CT<T>::c)));
   if (n_mat == 0) return BE_OK;
+  if constexpr (sizeof(T) == sizeof(double)) {
+    if (N <= kSmallOrder)
+      return eigh_small_fp64(ctx, H, N, ld, mat_stride, n_mat, band_lo, band_hi, evals, U, ldu, u_stride, status, stream,
+                             clu_rel);
+  }
   const size_t per = eigh_chunk_bytes<T>(ctx, N, m);
   const int64_t cap = eigh_sub_batch<T>(ctx, N, per, ctx->ws_bytes[WS_EIGH], n_mat);
   for (int64_t b0 = 0; b0 < n_mat; b0 += cap) {
@@ -1936,7 +1748,7 @@ static int eigh_refined_chunk(be_ctx *ctx, const double2 *H, int N, int ld, int6
     return zgemm(ctx, g, stream);
   };
   if (m > 0) {
-    hipLaunchKernelGGL(refine_copy_u, dim3(64, gy), dim3(256), 0, stream, Uall, N, lo, m, nb, GU, U, ldu, us);
+    hipLaunchKernelGGL(refine_copy_u, dim3(copy_blocks(int64_t(N) * m), gy), dim3(256), 0, stream, Uall, N, lo, m, nb, GU, U, ldu, us);
     BE_RET_IF(check_launch(ctx, "refine_copy_u"));
     // G = H U_w into the left half of GU
     BE_RET_IF(zg(N, m, N, 0, Hf, N, NN, Uall + int64_t(lo) * N, N, NN, GU, N, sGU, 0.0, "refine_hu"));
@@ -2033,7 +1845,7 @@ static int eigh_refined_chunk(be_ctx *ctx, const double2 *H, int N, int ld, int6
   }
   hipLaunchKernelGGL(flag_nonorth, dim3(static_cast<uint32_t>((nb + 255) / 256)), dim3(256), 0, stream, err, nb, 1e-10,
                      status);
-  hipLaunchKernelGGL(refine_copy_back, dim3(64, gy), dim3(256), 0, stream, GU, sGU, N, m, loc, nb, U, ldu, us);
+  hipLaunchKernelGGL(refine_copy_back, dim3(copy_blocks(int64_t(N) * m), gy), dim3(256), 0, stream, GU, sGU, N, m, loc, nb, U, ldu, us);
   return check_launch(ctx, "refine_copy_back");
 }
 

@@ -1,0 +1,385 @@
+// Batched Hermitian eigensolver for small orders: one launch, several
+// matrices per wave, everything in LDS.
+//
+// A group of TPM lanes (8, 16 or 64) takes a matrix through the steps of the
+// general solver (Householder reduction, bisection, inverse iteration,
+// orthonormalization inside clusters, Newton-Schulz orthonormalization of
+// all vectors, back-transformation) without leaving LDS. Only lanes of one
+// wave cooperate, so there are no workgroup barriers. The general path gives
+// such a matrix four workgroups of 256 threads one after another, a padded
+// 16 x 16 tile in each of five MFMA products and ~12 launches with a
+// read-back. Bound by the latency of the serial recurrences (FP64 division
+// chains of the Sturm counts, one lane per eigenvalue), hence as many matrices
+// per wave as have rows for its lanes. FP64, half the bands, general path ->
+// this one: order 4, 10,000 matrices 945 -> 72 us; 8, 4,096: 765 -> 92; 16,
+// 4,096: 1,416 -> 172; 32, 64: 604 -> 301, 8,192: 6,547 -> 2,104.
+// Tridiagonal part of the mixed path: order 8, 4,096: 345 -> 60; 32, 4,096:
+// 810 -> 463.
+//
+// FULL (FP64): from H to U. Otherwise (mixed paths) the reduction has been
+// done in FP32 by the panel kernel, and the back-transformation follows as
+// FP32 products: the kernel takes d, e and writes Z (as complex FP32).
+#include <algorithm>
+
+#include "common.hpp"
+#include "eigh_small.hpp"
+#include "tridiag.hpp"
+
+namespace {
+
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int TPM>
+__device__ __forceinline__ double grp_sum(double v) {
+#pragma unroll
+  for (int o = TPM / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+template <int TPM>
+__device__ __forceinline__ double grp_max(double v) {
+#pragma unroll
+  for (int o = TPM / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
+// LDS of one matrix, in doubles: d, e, e^2 (N each), eigenvalues (m + 4),
+// block starts, group ids and marks (N + 1 + 2 m ints), X (N m), scratch for the
+// elimination's diagonals and the Gram matrix or, later, U (2 (N + 1) m),
+// and with FULL the matrix, v, w and tau (N N + 3 N complex).
+__host__ __device__ inline int small_doubles(int N, int m, bool full) {
+  const int d = 3 * N + (m + 4) + (2 * m + N + 2) / 2 + N * m + 2 * (N + 1) * m;
+  return (d + 1 + (full ? 2 * (N * N + 3 * N) : 0)) & ~1;  // even: the complex part is 16-byte aligned
+}
+
+template <int TPM, bool FULL, typename OUT>
+__global__ __launch_bounds__(64) void eigh_small_kernel(double2 *H, int64_t sH, int ld, const double *dg,
+                                                        const double *eg, int64_t sDE, int N, int lo, int m,
+                                                        int64_t n_mat, double clu_rel, double tol_orth, int max_it,
+                                                        double *evals, OUT *U, int ldu, int64_t sU, uint32_t *status) {
+  extern __shared__ double2 sm2[];
+  constexpr int MPB = 64 / TPM;
+  const int lane = threadIdx.x, t = lane % TPM;
+  const int64_t q = int64_t(blockIdx.x) * MPB + lane / TPM;
+  const bool live = q < n_mat;
+  const int per = small_doubles(N, m, FULL);
+  double *base = reinterpret_cast<double *>(sm2) + (lane / TPM) * per;
+  double2 *A = reinterpret_cast<double2 *>(base);  // FULL: N x N, then v, w, tau (N each)
+  double2 *sv = A + (FULL ? N * N : 0), *sw = sv + (FULL ? N : 0), *stau = sw + (FULL ? N : 0);
+  double *sd = reinterpret_cast<double *>(stau + (FULL ? N : 0)), *se = sd + N, *se2 = se + N, *slam = se2 + N;
+  double *X0 = slam + m + 4, *ZG = X0 + N * m;
+  int *sblk = reinterpret_cast<int *>(ZG + 2 * (N + 1) * m), *smark = sblk + N + 1, *sbad = smark + m;
+  const double eps = DBL_EPSILON;
+  uint32_t st = 0;
+
+  // ---- Householder reduction (the panel kernel's reflectors), unblocked
+  if constexpr (FULL) {
+    constexpr int RW = TPM < 32 ? TPM : 32, KS = TPM / RW;  // rows at once, column strides per row
+    const int i0 = t % RW, k0 = t / RW;
+    double2 *Hq = H + (live ? q : 0) * sH;
+    for (int e = t; e < N * N; e += TPM) {
+      const int r = e % N, c = e / N;
+      double2 v = r >= c ? Hq[r + int64_t(c) * ld] : be::cconj(Hq[c + int64_t(r) * ld]);
+      if (r == c) v.y = 0.0;
+      A[e] = v;
+    }
+    wave_lds_sync();
+    for (int j = 0; j + 1 < N; ++j) {
+      double xn = 0.0;
+      for (int r = j + 2 + t; r < N; r += TPM) {
+        const double2 a = A[r + j * N];
+        xn += a.x * a.x + a.y * a.y;
+      }
+      xn = grp_sum<TPM>(xn);
+      const double2 alpha = A[j + 1 + j * N];
+      double2 tau = make_double2(0.0, 0.0), scal = tau;
+      double beta = alpha.x;
+      if (xn != 0.0 || alpha.y != 0.0) {
+        const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn);
+        beta = alpha.x >= 0.0 ? -nrm : nrm;
+        tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
+        const double dr = alpha.x - beta, di = alpha.y, den = dr * dr + di * di;
+        scal = make_double2(dr / den, -di / den);
+      }
+      for (int r = j + 1 + t; r < N; r += TPM) sv[r] = r == j + 1 ? make_double2(1.0, 0.0) : be::cmul(A[r + j * N], scal);
+      if (t == 0) {
+        sd[j] = A[j + j * N].x;
+        se[j] = beta;
+        stau[j] = tau;
+      }
+      wave_lds_sync();
+      // w = tau A v, then w -= tau (w^H v) / 2 v
+      double dr = 0.0, di = 0.0;
+      double2 w = make_double2(0.0, 0.0);
+      const int i = i0;  // N <= RW: one row per lane
+      if (i > j && i < N)
+        for (int k = j + 1 + k0; k < N; k += KS) w = be::cadd(w, be::cmul(A[i + k * N], sv[k]));
+      if (KS == 2) {
+        w.x += __shfl_xor(w.x, 32, 64);
+        w.y += __shfl_xor(w.y, 32, 64);
+      }
+      w = be::cmul(tau, w);
+      const double2 vi = (i > j && i < N) ? sv[i] : make_double2(0.0, 0.0);
+      if (k0 == 0) {
+        dr = w.x * vi.x + w.y * vi.y;
+        di = w.x * vi.y - w.y * vi.x;
+      }
+      dr = grp_sum<TPM>(dr);
+      di = grp_sum<TPM>(di);
+      const double2 al = make_double2(-0.5 * (tau.x * dr - tau.y * di), -0.5 * (tau.x * di + tau.y * dr));
+      w = be::cadd(w, be::cmul(al, vi));
+      if (k0 == 0 && i > j && i < N) sw[i] = w;
+      wave_lds_sync();
+      // A -= v w^H + w v^H; column j keeps v
+      if (i > j && i < N) {
+        for (int k = j + 1 + k0; k < N; k += KS) {
+          const double2 u = be::cadd(be::cmulc(sw[k], vi), be::cmulc(sv[k], w));
+          A[i + k * N] = be::csub(A[i + k * N], u);
+        }
+        if (k0 == 0) A[i + j * N] = vi;
+      }
+      wave_lds_sync();
+    }
+    if (t == 0) {
+      sd[N - 1] = A[N * N - 1].x;
+      se[N - 1] = 0.0;
+    }
+    if (live)  // H's columns hold the reflectors, as the panel kernel leaves them
+      for (int e = t; e < N * N; e += TPM) {
+        const int r = e % N, c = e / N;
+        Hq[r + int64_t(c) * ld] = r > c ? A[e] : make_double2(0.0, 0.0);
+      }
+  } else {
+    for (int i = t; i < N; i += TPM) {
+      sd[i] = live ? dg[q * sDE + i] : 0.0;
+      se[i] = live && i < N - 1 ? eg[q * sDE + i] : 0.0;
+    }
+  }
+  wave_lds_sync();
+  // ---- non-finite input: NaN outputs; the steps below then run on zeros
+  double nonfin = 0.0;
+  for (int i = t; i < N; i += TPM)
+    if (!isfinite(sd[i]) || !isfinite(se[i])) nonfin = 1.0;
+  const bool bad = grp_max<TPM>(nonfin) != 0.0;
+  for (int i = t; i < N; i += TPM) {
+    if (bad) sd[i] = se[i] = 0.0;
+    se2[i] = se[i] * se[i];
+  }
+  wave_lds_sync();
+  // ---- bisection, a lane per eigenvalue (as tri_bisect, from the Gershgorin interval)
+  double gl = INFINITY, gu = -INFINITY, emax2 = 0.0;
+  for (int i = t; i < N; i += TPM) {
+    const double rad = fabs(se[i]) + (i > 0 ? fabs(se[i - 1]) : 0.0);
+    gl = fmin(gl, sd[i] - rad);
+    gu = fmax(gu, sd[i] + rad);
+    emax2 = fmax(emax2, se2[i]);
+  }
+  gl = -grp_max<TPM>(-gl);
+  gu = grp_max<TPM>(gu);
+  emax2 = grp_max<TPM>(emax2);
+  const double tnorm = fmax(fabs(gl), fabs(gu)), pivmin = DBL_MIN * fmax(1.0, emax2);
+  gl -= 2.0 * eps * tnorm + 2.0 * pivmin;
+  gu += 2.0 * eps * tnorm + 2.0 * pivmin;
+  const double tol_abs = eps * eps * tnorm;
+  const int hi = lo + m;
+  for (int k0 = t; k0 < m + 4; k0 += TPM) {  // [lambda_0, lambda_{N-1}, lambda_{lo-1}, lambda_hi, lambda_lo ..]
+    const int k = k0 == 0 ? 0 : k0 == 1 ? N - 1 : k0 == 2 ? lo - 1 : k0 == 3 ? (hi < N ? hi : -1) : lo + k0 - 4;
+    double val = NAN;
+    if (k >= 0) {
+      double a = gl, b = gu;
+      bool conv = false;
+      for (int it = 0; it <= max_it; ++it) {
+        const double mid = 0.5 * (a + b);
+        conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + pivmin, tol_abs) || mid <= a || mid >= b;
+        if (conv || it == max_it) break;
+        int cnt = 0;  // Sturm count (as sturm_count), loads four steps ahead
+        double qv = sd[0] - mid;
+        if (fabs(qv) < pivmin) qv = -pivmin;
+        cnt += qv < 0.0;
+#pragma unroll 4
+        for (int i = 1; i < N; ++i) {
+          qv = (sd[i] - mid) - div_nr(se2[i - 1], qv);
+          if (fabs(qv) < pivmin) qv = -pivmin;
+          cnt += qv < 0.0;
+        }
+        if (cnt > k) b = mid;
+        else a = mid;
+      }
+      if (!conv) st |= BE_ST_NONCONVERGED;
+      val = 0.5 * (a + b);
+    }
+    slam[k0] = val;
+  }
+  wave_lds_sync();
+  const double *lam = slam + 4;
+  if (live)
+    for (int c = t; c < m + 2; c += TPM)
+      evals[q * (m + 2) + c] = bad ? NAN : c == 0 ? slam[2] : c == m + 1 ? slam[3] : lam[c - 1];
+  if (m > 0) {
+    const double scale = fmax(1.0, fmax(fabs(slam[0]), fabs(slam[1])));
+    double g = INFINITY;
+    if (lo > 0) g = fmin(g, lam[0] - slam[2]);
+    if (hi < N) g = fmin(g, slam[3] - lam[m - 1]);
+    if (g < 1e-9 * scale) st |= BE_ST_GAP_CLOSED;
+  }
+  if (m > 0) {
+    // ---- inverse iteration, a lane per vector (as tri_invit)
+    int nblk = 0;
+    if (t == 0) {
+      const double splittol = tol_split(tnorm);
+      sblk[nblk++] = 0;
+      for (int i = 1; i < N; ++i)
+        if (fabs(se[i - 1]) <= splittol) sblk[nblk++] = i;
+      sblk[nblk] = N;
+    }
+    nblk = __shfl(nblk, lane - t, 64);
+    for (int c = t; c < m; c += TPM) smark[c] = sbad[c] = 0;
+    wave_lds_sync();
+    const double tiny = eps * fmax(tnorm, DBL_MIN), dclu = tol_cluster(tnorm, clu_rel);
+    for (int c = t; c < m; c += TPM) {
+      const InvitBlock ib = invit_block(sd, se2, lam, m, c, sblk, nblk, N, tnorm, clu_rel, pivmin);
+      if (ib.shared) smark[c] = ib.bs + 2;
+      if (!ib.found) sbad[ib.c0] = 1;
+      for (int i = 0; i < N; ++i)
+        if (i < ib.bs || i >= ib.bt) X0[i * m + c] = 0.0;
+      if (!invit_vector<false>(sd, se, ib.bs, ib.bt, ib.lm, tiny, c, X0, ZG, m)) st |= BE_ST_NONCONVERGED;
+    }
+    wave_lds_sync();
+    for (int c = t; c < m; c += TPM) {  // a cluster with a lane that found no block is one group
+      int c0 = c;
+      while (c0 > 0 && lam[c0] - lam[c0 - 1] <= dclu) --c0;
+      if (sbad[c0]) smark[c] = 1;
+    }
+    wave_lds_sync();
+    // ---- groups of a cluster that share a block: modified Gram-Schmidt, two passes, lanes over rows
+    for (int c0 = 0; c0 < m;) {
+      const int c1 = group_end(lam, smark, m, c0, dclu);
+      if (c1 - c0 > 1)
+        for (int pass = 0; pass < 2; ++pass)
+          for (int c = c0; c < c1; ++c) {
+            for (int s2 = c0; s2 <= c; ++s2) {  // s2 == c: normalize
+              double d = 0.0;
+              for (int i = t; i < N; i += TPM) d = fma(X0[i * m + s2], X0[i * m + c], d);
+              d = grp_sum<TPM>(d);
+              const double inv = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
+              for (int i = t; i < N; i += TPM)
+                X0[i * m + c] = s2 == c ? X0[i * m + c] * inv : X0[i * m + c] - d * X0[i * m + s2];
+              wave_lds_sync();
+            }
+          }
+      c0 = c1;
+    }
+    wave_lds_sync();
+    // ---- symmetric orthonormalization (as the general path's Newton-Schulz steps)
+    double *G = ZG + N * m;  // m x m, beside the second iterate
+    double err = 0.0;
+    bool act = true, done2 = false;
+    for (int it = 0; it < 8 && __any(act); ++it) {
+      double e2 = 0.0;
+      for (int e = t; e < m * m; e += TPM) {
+        const int r = e % m, c = e / m;
+        double g = 0.0;
+        for (int i = 0; i < N; ++i) g = fma(X0[i * m + r], X0[i * m + c], g);
+        const double off = fabs(g - (r == c ? 1.0 : 0.0));
+        e2 = off == off ? fmax(e2, off) : INFINITY;
+        if (act) G[e] = (r == c ? 1.5 : 0.0) - 0.5 * g;
+      }
+      e2 = grp_max<TPM>(e2);
+      if (act) {
+        err = e2;
+        done2 = err < 1e-8;
+        act = err > tol_orth && !(err > 1.0);
+      }
+      wave_lds_sync();
+      const bool step = act;
+      for (int e = t; e < N * m; e += TPM) {
+        const int c = e % m, i = e / m;
+        double x = 0.0;
+        for (int k = 0; k < m; ++k) x = fma(G[c + k * m], X0[i * m + k], x);
+        if (step) ZG[e] = x;
+      }
+      wave_lds_sync();
+      if (step) {
+        for (int e = t; e < N * m; e += TPM) X0[e] = ZG[e];
+        if (done2) {
+          act = false;
+          err = 0.0;
+        }
+      }
+      wave_lds_sync();
+    }
+    if (!(err <= fmax(tol_orth, 1e-10))) st |= BE_ST_NONCONVERGED;
+    // ---- U = H_0 ... H_{N-2} Z, a lane per column; written coalesced
+    if constexpr (FULL) {
+      double2 *Uc = reinterpret_cast<double2 *>(ZG);  // column c at c (N + 1)
+      if ((reinterpret_cast<uintptr_t>(ZG) & 15) != 0) Uc = reinterpret_cast<double2 *>(ZG + 1);
+      for (int c = t; c < m; c += TPM) {
+        double2 *u = Uc + c * (N + 1);
+        for (int i = 0; i < N; ++i) u[i] = make_double2(X0[i * m + c], 0.0);
+        for (int j = N - 2; j >= 0; --j) {
+          double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+          for (int i = j + 1; i < N; ++i) s = be::cadd(s, be::cmulc(A[i + j * N], u[i]));
+          s = be::cmul(stau[j], s);
+#pragma unroll 4
+          for (int i = j + 1; i < N; ++i) u[i] = be::csub(u[i], be::cmul(A[i + j * N], s));
+        }
+      }
+      wave_lds_sync();
+      if (live)
+        for (int e = t; e < N * m; e += TPM) {
+          const int r = e % N, c = e / N;
+          U[q * sU + r + int64_t(c) * ldu] = bad ? OUT{NAN, NAN} : OUT{Uc[c * (N + 1) + r].x, Uc[c * (N + 1) + r].y};
+        }
+    } else if (live) {
+      typedef decltype(OUT{}.x) F;
+      for (int e = t; e < N * m; e += TPM) {
+        const int r = e % N, c = e / N;
+        U[q * sU + r + int64_t(c) * ldu] = bad ? OUT{F(NAN), F(NAN)} : OUT{F(X0[r * m + c]), F(0)};
+      }
+    }
+  }
+  if (bad) st = BE_ST_NAN_INF;
+#pragma unroll
+  for (int o = TPM / 2; o > 0; o >>= 1) st |= uint32_t(__shfl_xor(int(st), o, 64));
+  if (live && t == 0) status[q] = st;
+}
+
+template <int TPM, bool FULL, typename OUT>
+int launch_small(be_ctx *ctx, double2 *H, int64_t sH, int ld, const double *d, const double *e, int64_t sDE, int N,
+                 int lo, int m, int64_t n_mat, double clu_rel, double tol_orth, double *evals, OUT *U, int ldu,
+                 int64_t sU, uint32_t *status, hipStream_t stream) {
+  constexpr int MPB = 64 / TPM;
+  const size_t lds = size_t(MPB) * small_doubles(N, m, FULL) * sizeof(double) + 16;
+  auto kern = &eigh_small_kernel<TPM, FULL, OUT>;
+  hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>((n_mat + MPB - 1) / MPB)), dim3(64), lds, stream, H, sH, ld, d, e,
+                     sDE, N, lo, m, n_mat, clu_rel, tol_orth, ctx->dbg_bisect_max_iter, evals, U, ldu, sU, status);
+  return be::check_launch(ctx, "eigh_small");
+}
+
+}  // namespace
+
+namespace be {
+
+int eigh_small_fp64(be_ctx *ctx, double2 *H, int N, int ld, int64_t ms, int64_t n_mat, int lo, int hi, double *evals,
+                    double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream, double clu_rel) {
+  ProfScope prof(ctx, "eigh_small", stream);
+  auto go = N <= 8    ? &launch_small<8, true, double2>
+            : N <= 16 ? &launch_small<16, true, double2>
+                      : &launch_small<64, true, double2>;
+  return go(ctx, H, ms, ld, nullptr, nullptr, 0, N, lo, hi - lo, n_mat, clu_rel, 1e-14, evals, U, ldu, us, status, stream);
+}
+
+int tri_small_c64(be_ctx *ctx, const double *d, const double *e, int N, int64_t n_mat, int lo, int hi, double *evals,
+                  float2 *Z, int ldz, int64_t sz, uint32_t *status, hipStream_t stream, double clu_rel, double tol_orth) {
+  ProfScope prof(ctx, "tri_small", stream);
+  auto go = N <= 8    ? &launch_small<8, false, float2>
+            : N <= 16 ? &launch_small<16, false, float2>
+                      : &launch_small<64, false, float2>;
+  return go(ctx, nullptr, 0, 0, d, e, N, N, lo, hi - lo, n_mat, clu_rel, tol_orth, evals, Z, ldz, sz, status, stream);
+}
+
+}  // namespace be

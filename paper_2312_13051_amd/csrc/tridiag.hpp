@@ -1,0 +1,255 @@
+// Device functions of the FP64 tridiagonal eigensolver shared by its kernels:
+// Sturm counts, the tolerances of splits and clusters, the choice of the block
+// that carries an eigenvector, and inverse iteration for one vector.
+#pragma once
+
+#include <cfloat>
+#include <cmath>
+
+#include "common.hpp"
+
+namespace {
+
+// a / b as a times the hardware reciprocal of b refined by one Newton-Raphson
+// step: within a few ulps of the rounded quotient, for normal b (the Sturm
+// recurrence keeps |b| >= pivmin >= DBL_MIN, so 1/b and a/b stay finite).
+__device__ __forceinline__ double div_nr(double a, double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = fma(fma(-b, r, 1.0), r, r);
+  return a * r;
+}
+
+// Number of eigenvalues of T below x (Sturm sequence of the LDL^T
+// factorization of T - x I). The quotient uses div_nr: the count is that of a
+// matrix within a few ulps of T, the same kind of backward error the
+// correctly rounded division gives.
+__device__ __forceinline__ int sturm_count(const double *sd, const double *se2, int N, double x, double pivmin) {
+  int cnt = 0;
+  double qv = sd[0] - x;
+  if (fabs(qv) < pivmin) qv = -pivmin;
+  cnt += qv < 0.0;
+  for (int i = 1; i < N; ++i) {
+    qv = (sd[i] - x) - div_nr(se2[i - 1], qv);
+    if (fabs(qv) < pivmin) qv = -pivmin;
+    cnt += qv < 0.0;
+  }
+  return cnt;
+}
+
+// The same count from the interleaved pairs sde[i] = (d_i, e_{i-1}^2): one
+// LDS read per step, four steps' reads issued together.
+__device__ __forceinline__ int sturm_count_i(const double2 *sde, int N, double x, double pivmin) {
+  int cnt = 0;
+  double qv = sde[0].x - x;
+  if (fabs(qv) < pivmin) qv = -pivmin;
+  cnt += qv < 0.0;
+#pragma unroll 4
+  for (int i = 1; i < N; ++i) {
+    const double2 de = sde[i];
+    qv = (de.x - x) - div_nr(de.y, qv);
+    if (fabs(qv) < pivmin) qv = -pivmin;
+    cnt += qv < 0.0;
+  }
+  return cnt;
+}
+
+__device__ __forceinline__ double hash_unit(uint64_t a, uint64_t b) {
+  // splitmix64 of (a, b) -> uniform in (-1, 1)
+  uint64_t z = a * 0x9E3779B97F4A7C15ull + b + 0x632BE59BD9B4E019ull;
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  z ^= z >> 31;
+  return (double)(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;
+}
+
+// Tolerances relative to ||T||: split < block window < cluster gap, so a
+// cluster's window never reaches the next cluster. Eigenvalues closer than
+// the cluster tolerance (clu_rel, by default kCluRel = 1e-12) form a cluster, whose vectors are
+// computed as one invariant subspace (any orthonormal basis of it): inverse
+// iteration separates two eigenvalues only to about eps ||T|| / gap, so
+// below that gap their vectors can come out nearly parallel (a cluster of
+// eigenvalues spread over 1e-12 ||T|| - e.g. the projected spin operator's
+// +-1 clusters computed from refined eigenvectors, whose T splits into many
+// blocks - would otherwise have lanes pick blocks by windows narrower than
+// the cluster, and leave an orthonormalization that cannot converge). A
+// caller that needs the vectors of nearly equal eigenvalues resolved one by
+// one (and validates them) may pass a smaller tolerance.
+constexpr double kCluRel = 1e-12;
+__device__ __forceinline__ double tol_split(double tnorm) { return 16.0 * DBL_EPSILON * tnorm; }
+__device__ __forceinline__ double tol_window(double tnorm, double clu_rel) { return 0.5 * clu_rel * tnorm; }
+__device__ __forceinline__ double tol_cluster(double tnorm, double clu_rel) { return clu_rel * tnorm; }
+
+// Block of T that carries the eigenvector of lane c, and its shift. The k
+// members of a cluster (consecutive eigenvalues within the cluster tolerance)
+// take the k distinct blocks that hold it, in order; lanes whose block holds
+// several of them share it.
+struct InvitBlock {
+  int c0;      // first member of the lane's cluster
+  int bs, bt;  // the block's rows
+  bool found, shared;
+  double lm;  // shift
+};
+__device__ __forceinline__ InvitBlock invit_block(const double *sd, const double *se2, const double *lam, int m, int c,
+                                                  const int *sblk, int nblk, int N, double tnorm, double clu_rel,
+                                                  double pivmin) {
+  const double dblk = tol_window(tnorm, clu_rel), dclu = tol_cluster(tnorm, clu_rel);
+  int c0 = c, c1 = c + 1;
+  while (c0 > 0 && lam[c0] - lam[c0 - 1] <= dclu) --c0;
+  while (c1 < m && lam[c1] - lam[c1 - 1] <= dclu) ++c1;
+  const double wlo = lam[c0] - dblk, whi = lam[c1 - 1] + dblk;
+  const int jr = c - c0;
+  int bs = 0, bt = N, cnt = 0;
+  bool found = false, shared = false;
+  for (int b = 0; b < nblk && !found; ++b) {
+    const int s0 = sblk[b], t0 = sblk[b + 1];
+    const int nb = sturm_count(sd + s0, se2 + s0, t0 - s0, whi, pivmin) -
+                   sturm_count(sd + s0, se2 + s0, t0 - s0, wlo, pivmin);
+    if (nb > 0 && cnt + nb > jr) {
+      bs = s0;
+      bt = t0;
+      found = true;
+      shared = nb > 1;
+    }
+    cnt += nb;
+  }
+  // Lanes that share a block with other members of their cluster take
+  // shifts a few eps ||T|| apart: far larger than the splitting of a
+  // degenerate pair (so neither member dominates a lane's solve and each
+  // lane returns an independent combination of the cluster's vectors),
+  // far smaller than the distance to the next cluster.
+  const double lm =
+      (!found || shared) ? lam[c] + (jr - 0.5 * (c1 - c0 - 1)) * 2.0 * DBL_EPSILON * tnorm : lam[c];
+  return InvitBlock{c0, bs, bt, found, shared, lm};
+}
+
+// Inverse iteration for vector c (normalized, two solves) on rows bs .. bt - 1
+// of T with shift lm: X[i * mp + c] receives it, Z0 is scratch of the same
+// layout. AHEAD: loads four rows ahead of their use (arrays in memory; in LDS
+// one at a time). False when the vector did not come out finite.
+template <bool AHEAD>
+__device__ __forceinline__ bool invit_vector(const double *sd, const double *se, int bs, int bt, double lm, double tiny,
+                                             int c, double *X, double *Z0, int mp) {
+  // two solves: from a pseudo-random start the first already amplifies the
+  // wanted direction by ~1/(eps ||T||) against ~1/gap for the others. The
+  // second solve recomputes the same factorization (same operations, same
+  // factors) instead of storing it again, and takes the first solution's
+  // normalization as it reads it. Of the factorization only the diagonal
+  // a_i met at each elimination step is stored: the pivot choice of row i
+  // (|a_i| < |e_i|) and every factor entry follow from a_i, a_{i-1} and T,
+  // recomputed by the same operations in the back substitution.
+  // The loads of each sweep are issued PF rows ahead of the recurrence that
+  // consumes them, so the serial chain waits on memory once per PF rows.
+  // The start vector depends on the column only, not on the matrix's place
+  // in the batch: a matrix gets the same eigenvectors, bit for bit, in any
+  // batch (inside a degenerate cluster the start decides the basis).
+  constexpr int PF = AHEAD ? 4 : 1;
+  double scale = 1.0;
+  bool ok = true;
+  for (int it = 0; it < 2; ++it) {
+    // forward elimination with partial pivoting on [T_block - lm I | rhs]
+    double a = sd[bs] - lm, b = bt - bs > 1 ? se[bs] : 0.0;
+    double r = it == 0 ? hash_unit(uint64_t(c) + 1, bs) : X[int64_t(bs) * mp + c] * scale;
+    // one elimination step at row i (i + 1 < bt) with right-hand side entry rn of row i + 1
+    auto step = [&](int i, double rn) {
+      const double ei = se[i], Dn = sd[i + 1] - lm, en = (i + 2 < bt) ? se[i + 1] : 0.0;
+      const int64_t o = int64_t(i) * mp + c;
+      if (it == 0) Z0[o] = a;
+      // without interchange: l = e_i / a (a = 0 only with e_i = 0, then
+      // taken as tiny), row i keeps (a, b); with interchange: l = a / e_i
+      const bool keep = fabs(a) >= fabs(ei);
+      const double ad = (keep && a == 0.0) ? tiny : a;
+      const double l = (keep ? ei : ad) / (keep ? ad : ei);
+      X[o] = keep ? r : rn;
+      const double p1 = keep ? Dn : b, p2 = keep ? b : Dn;
+      const double q1 = keep ? rn : r, q2 = keep ? r : rn;
+      a = p1 - l * p2;
+      b = keep ? en : -l * en;
+      r = q1 - l * q2;
+    };
+    if (it == 0) {
+      for (int i = bs; i + 1 < bt; ++i) step(i, hash_unit(uint64_t(c) + 1, i + 1));
+    } else {
+      for (int i0 = bs; i0 + 1 < bt; i0 += PF) {
+        double rv[PF];
+#pragma unroll
+        for (int u = 0; u < PF; ++u) rv[u] = i0 + u + 1 < bt ? X[int64_t(i0 + u + 1) * mp + c] : 0.0;
+#pragma unroll
+        for (int u = 0; u < PF; ++u)
+          if (i0 + u + 1 < bt) step(i0 + u, rv[u] * scale);
+      }
+    }
+    {
+      const int64_t o = int64_t(bt - 1) * mp + c;
+      if (it == 0) Z0[o] = a;
+      X[o] = r;
+    }
+    // back substitution: row i of the triangular factor is (e_i, D_{i+1},
+    // e_{i+1}) where row i was interchanged, else (a_i, b_i, 0) with b_i =
+    // e_i, or -(a_{i-1} / e_{i-1}) e_i after an interchange at row i-1
+    double x1 = 0.0, x2 = 0.0, nrm = 0.0;
+    double ai = Z0[int64_t(bt - 1) * mp + c];
+    for (int i0 = bt - 1; i0 >= bs; i0 -= PF) {
+      double xv[PF], av[PF];
+#pragma unroll
+      for (int u = 0; u < PF; ++u) {
+        const int i = i0 - u;
+        xv[u] = i >= bs ? X[int64_t(i) * mp + c] : 0.0;
+        av[u] = i > bs ? Z0[int64_t(i - 1) * mp + c] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < PF; ++u) {
+        const int i = i0 - u;
+        if (i >= bs) {
+          const double ap = av[u];
+          double z0, z1 = 0.0, z2 = 0.0;
+          if (i == bt - 1) {
+            z0 = ai == 0.0 ? tiny : ai;
+          } else if (fabs(ai) >= fabs(se[i])) {
+            z0 = ai == 0.0 ? tiny : ai;
+            z1 = se[i];
+            if (i > bs && !(fabs(ap) >= fabs(se[i - 1]))) {
+              const double l = ap / se[i - 1];
+              z1 = -l * se[i];
+            }
+          } else {
+            z0 = se[i];
+            z1 = sd[i + 1] - lm;
+            z2 = (i + 2 < bt) ? se[i + 1] : 0.0;
+          }
+          const double xi = (xv[u] - z1 * x1 - z2 * x2) / z0;
+          X[int64_t(i) * mp + c] = xi;
+          x2 = x1;
+          x1 = xi;
+          nrm = fma(xi, xi, nrm);
+          ai = ap;
+        }
+      }
+    }
+    const double inv = 1.0 / sqrt(nrm);
+    if (!isfinite(inv) || inv == 0.0) ok = false;
+    if (it == 0) {
+      scale = inv;
+    } else {
+      for (int i0 = bs; i0 < bt; i0 += PF) {
+        double xv[PF];
+#pragma unroll
+        for (int u = 0; u < PF; ++u) xv[u] = i0 + u < bt ? X[int64_t(i0 + u) * mp + c] : 0.0;
+#pragma unroll
+        for (int u = 0; u < PF; ++u)
+          if (i0 + u < bt) X[int64_t(i0 + u) * mp + c] = xv[u] * inv;
+      }
+    }
+  }
+  return ok;
+}
+
+// End of the orthonormalization group starting at c0: the following lanes of
+// the same cluster with the same group id (0: no group, a group of one).
+__device__ __forceinline__ int group_end(const double *lam, const int *mk, int m, int c0, double dclu) {
+  int c1 = c0 + 1;
+  if (mk[c0] == 0) return c1;
+  while (c1 < m && mk[c1] == mk[c0] && lam[c1] - lam[c1 - 1] <= dclu) ++c1;
+  return c1;
+}
+
+}  // namespace

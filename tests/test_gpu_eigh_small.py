@@ -1,0 +1,61 @@
+"""Small-order eigensolver (one launch per batch, several matrices per wave) against LAPACK at the edges of its lane
+groups (orders 8, 16, 32), for batches that do not fill a wave, narrow and full windows and degenerate spectra."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from tests import gpu_util as gu  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def hermitian(n, N, seed, degenerate):
+    rng = np.random.default_rng([seed, N])
+    A = rng.standard_normal((n, N, N)) + 1j * rng.standard_normal((n, N, N))
+    H = A + np.conj(np.swapaxes(A, 1, 2))
+    if degenerate:  # levels in threes
+        w, V = np.linalg.eigh(H)
+        w = np.arange(N)[None] // 3 * 1.5 - 2.0 + 0 * w
+        H = (V * w[:, None, :]) @ np.conj(np.swapaxes(V, 1, 2))
+        H = 0.5 * (H + np.conj(np.swapaxes(H, 1, 2)))
+    return H
+
+
+# bounds: those of the general solver's tests (FP64: eigenvalues 1e-12 ||H||, orthonormality 2e-11, projector 1e-10 at
+# gaps >= 1e-3 ||H||; mixed: 2e-5, 1e-5 and 1e-4, the FP32 reduction's)
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("degenerate", [False, True])
+@pytest.mark.parametrize("N, lo, hi, n", [(1, 0, 1, 5), (2, 0, 1, 9), (4, 0, 2, 17), (8, 3, 8, 7), (9, 0, 9, 6), (16, 6, 10, 5),
+                                          (17, 0, 8, 3), (31, 9, 30, 2), (32, 0, 32, 3), (32, 15, 15, 2), (33, 0, 16, 2),
+                                          (64, 0, 32, 2), (65, 3, 60, 2)])
+def test_small_orders(N, lo, hi, n, degenerate, precision):
+    gu.need_gpu()
+    from paper_2312_13051_amd import _lib as L
+    H = hermitian(n, N, 3, degenerate)
+    m, ld = hi - lo, N + 1
+    mixed = precision == "mixed"
+    bound = (2e-5, 1e-5, 1e-4) if mixed else (1e-12, 2e-11, 1e-10)
+    c = gu.ctx()
+    try:
+        dH = gu.from_np(np.tril(H) + np.triu(np.full((N, N), 7.0), 1), ld, torch.complex64 if mixed else torch.complex128)
+        U = gu.colmajor(n, N, max(m, 1), N + 2, fill=0)
+        ev = torch.empty((n, m + 2), dtype=torch.float64, device="cuda")
+        st = torch.full((n,), 77, dtype=torch.int32, device="cuda")
+        c.eigh_batched(dH, L.BE_C64 if mixed else L.BE_C128, N, ld, dH.stride(0), n, lo, hi,
+                       L.BE_MIXED_FP32 if mixed else L.BE_FP64, ev, U, N + 2, U.stride(0), st)
+        ev, U, st = ev.cpu().numpy(), gu.to_np(U, N)[:, :, :m], st.cpu().numpy()
+    finally:
+        c.close()
+    for q in range(n):
+        w, V = np.linalg.eigh(H[q])
+        nrm = max(1.0, np.abs(w).max())
+        gaps = [w[k] - w[k - 1] for k in (lo, hi) if m and 0 < k < N]
+        if not mixed:
+            assert st[q] == (1 if gaps and min(gaps) < 1e-9 * nrm else 0)
+        assert np.abs(ev[q, 1:m + 1] - w[lo:hi]).max(initial=0.0) <= bound[0] * nrm
+        assert (ev[q, 0] == ev[q, 0]) == (lo > 0) and (ev[q, m + 1] == ev[q, m + 1]) == (hi < N)
+        assert np.abs(U[q].conj().T @ U[q] - np.eye(m)).max(initial=0.0) < bound[1]
+        if m and (not gaps or min(gaps) > 1e-3 * nrm):
+            P = U[q] @ U[q].conj().T - V[:, lo:hi] @ V[:, lo:hi].conj().T
+            assert np.abs(P).max() < bound[2] * (1 if not gaps else max(1.0, 0.05 * nrm / min(gaps)))
