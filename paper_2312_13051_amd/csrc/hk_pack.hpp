@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstdint>
 #include <limits>
+#include <map>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -26,7 +27,7 @@ namespace hkpack {
 struct PairRC {  // layout of int2: (row, col), row <= col
   int32_t r, c;
 };
-struct EntR {  // layout of int4: lattice vector (x, y, z), w = 0
+struct EntR {  // layout of int4: lattice vector (x, y, z), w: see index_vectors
   int32_t x, y, z, w;
 };
 struct EntT {  // layout of double2: amplitude (re, im)
@@ -130,6 +131,45 @@ inline std::string pack_system(int32_t N, int32_t dim, int64_t nnz, const int32_
   }
   *n_pairs = np;
   return std::string();
+}
+
+// Distinct lattice vectors of every system (vectors off[s] .. off[s] + count[s]
+// of R), and w of each entry set to its vector's index among its system's.
+// Consecutive entries mostly continue the order of the previous pair, so the
+// next vector is tried first; others are looked up.
+struct DistinctR {
+  std::vector<EntR> R;
+  std::vector<int64_t> off;
+  std::vector<int32_t> count;
+};
+inline DistinctR index_vectors(Packed &pk, const std::vector<int64_t> &pair_off, const std::vector<int32_t> &n_pairs) {
+  DistinctR d;
+  for (size_t s = 0; s < pair_off.size(); ++s) {
+    const int64_t base = static_cast<int64_t>(d.R.size());
+    std::map<std::tuple<int32_t, int32_t, int32_t>, int32_t> at;
+    const size_t e0 = static_cast<size_t>(pk.start[static_cast<size_t>(pair_off[s])]);
+    const size_t e1 = static_cast<size_t>(pk.start[static_cast<size_t>(pair_off[s] + n_pairs[s])]);
+    int32_t next = 0;
+    for (size_t e = e0; e < e1; ++e) {
+      EntR &r = pk.R[e];
+      const int32_t n = static_cast<int32_t>(static_cast<int64_t>(d.R.size()) - base);
+      auto same = [&](int32_t k) {
+        const EntR &u = d.R[static_cast<size_t>(base + k)];
+        return u.x == r.x && u.y == r.y && u.z == r.z;
+      };
+      int32_t k = next;
+      if (k >= n || !same(k)) {
+        const auto ins = at.emplace(std::make_tuple(r.x, r.y, r.z), n);
+        k = ins.first->second;
+        if (ins.second) d.R.push_back({r.x, r.y, r.z, 0});
+      }
+      r.w = k;
+      next = k + 1 < static_cast<int32_t>(static_cast<int64_t>(d.R.size()) - base) ? k + 1 : 0;
+    }
+    d.off.push_back(base);
+    d.count.push_back(static_cast<int32_t>(static_cast<int64_t>(d.R.size()) - base));
+  }
+  return d;
 }
 
 }  // namespace hkpack
