@@ -35,6 +35,8 @@
 
 #include "common.hpp"
 #include "eigh_small.hpp"
+#include "hetrd_resident.hpp"
+#include "lanes.hpp"
 #include "tridiag.hpp"
 
 namespace {
@@ -74,61 +76,6 @@ __host__ __device__ inline size_t panel_part_offset(int N, size_t csize, int nt)
 __host__ __device__ inline int panel_split(int nrb) { return nrb >= 5 ? 1 : nrb >= 3 ? 2 : 4; }
 
 // ---------------------------------------------------------------- reductions
-// Values of the lanes L ^ o of a wave, by VALU lane moves instead of LDS
-// permutes (which __shfl_xor takes): o = 32 and 16 by the half and row swaps of
-// CDNA4, 8 .. 1 by DPP. The sums below add the same pairs in the same order,
-// so results keep their bits. The panel's column sums kept the LDS pipe busy
-// beside the loads; panel time with permutes -> without: FP32 order 96, 1,024
-// matrices 1.75 -> 1.49 ms; 400, 4,608: 121.8 -> 113.3 ms (5.75 TB/s of the 6.2
-// that a read reaches on this device); FP64 400, 2,304: 126.8 -> 117.0 ms; 1024,
-// 256: 196.5 -> 173.8 ms.
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_mov(double v) {
-  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
-                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
-}
-// v of lane L ^ O, O = 8, 4, 2 or 1
-template <int O, typename T>
-__device__ __forceinline__ T lane_xor(T v) {
-  if constexpr (O == 8) return dpp_mov<0x128>(v);                         // row_ror:8
-  else if constexpr (O == 4) return dpp_mov<0x1B>(dpp_mov<0x141>(v));    // row_half_mirror, quad_perm [3,2,1,0]
-  else if constexpr (O == 2) return dpp_mov<0x4E>(v);                     // quad_perm [2,3,0,1]
-  else return dpp_mov<0xB1>(v);                                           // quad_perm [1,0,3,2]
-}
-// lanes with bit O of L clear: a(L) + a(L ^ O); set: b(L) + b(L ^ O); O = 32 or 16
-template <int O>
-__device__ __forceinline__ uint2 lane_swap(uint32_t a, uint32_t b) {
-  const auto r = O == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
-                         : __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  return make_uint2(r[0], r[1]);
-}
-template <int O>
-__device__ __forceinline__ float fold(float a, float b) {
-  const uint2 r = lane_swap<O>(__float_as_uint(a), __float_as_uint(b));
-  return __uint_as_float(r.x) + __uint_as_float(r.y);
-}
-template <int O>
-__device__ __forceinline__ double fold(double a, double b) {
-  const uint2 l = lane_swap<O>(uint32_t(__double2loint(a)), uint32_t(__double2loint(b)));
-  const uint2 h = lane_swap<O>(uint32_t(__double2hiint(a)), uint32_t(__double2hiint(b)));
-  return __hiloint2double(int(h.x), int(l.x)) + __hiloint2double(int(h.y), int(l.y));
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-  v = fold<32>(v, v);
-  v = fold<16>(v, v);
-  v += lane_xor<8>(v);
-  v += lane_xor<4>(v);
-  v += lane_xor<2>(v);
-  v += lane_xor<1>(v);
-  return v;
-}
-
 // Block-wide sum of two values (all threads get the result).
 template <typename T>
 __device__ __forceinline__ void block_sum2(T &a, T &b, T *red) {
@@ -1348,6 +1295,10 @@ struct GemmOf<float> {
   static int run(be_ctx *ctx, const CGemm &g, hipStream_t s) { return cgemm(ctx, g, s); }
 };
 
+// Panels that the panel kernel takes before the trailing matrix fits the
+// on-chip reduction (FP64).
+static int panels_before_resident(int N) { return N <= kResidentOrder ? 0 : (N - kResidentOrder + NB - 1) / NB; }
+
 // One sub-batch of nb_mat matrices. T is the working precision of the
 // Householder reduction and back-transformation (double: FP64 path, float:
 // mixed path); the tridiagonal solve and the re-orthonormalization are FP64.
@@ -1367,8 +1318,13 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
   C *VW = nullptr, *Tm = nullptr, *Xb = nullptr, *Yb = nullptr, *Uw = nullptr;
   double *dd = nullptr, *ee = nullptr, *Zs = nullptr;
   Carve cv;
-  cv.add(&VW, size_t(nb_mat) * N * 3 * NB);
+  // FP64: the last columns (all of them for orders up to kResidentOrder) are
+  // reduced on chip; panels p < p_res by the panel kernel
+  const int p_res = mixed ? P : panels_before_resident(N);
+  double2 *taus = nullptr;
+  if (p_res > 0) cv.add(&VW, size_t(nb_mat) * N * 3 * NB);
   cv.add(&Tm, size_t(nb_mat) * P * NB * NB);
+  if (p_res < P) cv.add(&taus, size_t(nb_mat) * N);
   cv.add(&dd, size_t(nb_mat) * N);
   cv.add(&ee, size_t(nb_mat) * N);
   const bool small = N <= kSmallOrder;  // the tridiagonal part in one launch, in LDS
@@ -1399,7 +1355,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
   const size_t psm = panel_lds(N, sizeof(C), pnt);
   const int64_t sPg = pl ? 0 : int64_t(panel_part_bytes(N - 1, 1));
   C *Pg = nullptr;
-  if (!pl) cv.add(&Pg, size_t(nb_mat) * sPg);
+  if (!pl && p_res > 0) cv.add(&Pg, size_t(nb_mat) * sPg);
   BE_RET_IF(cv.commit(ctx, stream, WS_EIGH));
   hipLaunchKernelGGL(zero_u32, dim3((nb_mat + 255) / 256), dim3(256), 0, stream, status, nb_mat);
   BE_RET_IF(check_launch(ctx, "zero_u32"));
@@ -1410,7 +1366,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
     BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(panel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, int(psm)));
   // ---- Householder reduction
-  for (int p = 0; p < P; ++p) {
+  for (int p = 0; p < p_res; ++p) {
     const int p0 = p * NB, nbp = std::min(NB, N - p0);
     {
       ProfScope prof(ctx, "hetrd_panel", stream);
@@ -1443,6 +1399,12 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
       g.herm_mirror = false;  // the panel reads the lower triangle only
       if constexpr (std::is_same<G, CGemm>::value) g.bf16x3 = bf16x3;
       BE_RET_IF(GemmOf<T>::run(ctx, g, stream));
+    }
+  }
+  if constexpr (sizeof(T) == sizeof(double)) {
+    if (p_res < P) {
+      BE_RET_IF(hetrd_resident(ctx, H, ms, ld, N, p_res * NB, nb_mat, dd, ee, int64_t(N), taus, stream));
+      if (m > 0) BE_RET_IF(larft(ctx, H, ms, ld, N, p_res, nb_mat, taus, Tm, sT, stream));
     }
   }
   // back-transformation target: the output itself (FP64) or an FP32 copy (mixed)
@@ -1653,6 +1615,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
 template <typename T>
 static int64_t panel_slots(be_ctx *ctx, int N) {
   typedef typename CT<T>::c C;
+  if (sizeof(T) == sizeof(double) && N <= kResidentOrder) return resident_slots(ctx, N);
   const int pnt = panel_threads(ctx, N, sizeof(C));
   const size_t psm = panel_lds(N, sizeof(C), pnt);
   PanelFn<T> panel = panel_kernel<T>(pnt, panel_loads(ctx, N, sizeof(C), pnt), panel_part_lds(N, sizeof(C), pnt));
@@ -1683,9 +1646,11 @@ static size_t eigh_chunk_bytes(be_ctx *ctx, int N, int m) {
   const int P = (N + NB - 1) / NB;
   const int mp = std::max(64, (m + 63) / 64 * 64);
   const size_t cs = sizeof(typename CT<T>::c);
-  return cs * (size_t(N) * 3 * NB + size_t(P) * NB * NB + 4 * size_t(NB) * std::max(m, 1) + 6 * size_t(NB) * NB +
+  const bool panels = sizeof(T) == sizeof(float) || panels_before_resident(N) > 0;
+  return cs * ((panels ? size_t(N) * 3 * NB : 0) + (sizeof(T) == sizeof(double) ? size_t(N) : 0) +
+               size_t(P) * NB * NB + 4 * size_t(NB) * std::max(m, 1) + 6 * size_t(NB) * NB +
                size_t(N) * std::max(m, 1)) +
-         (panel_part_lds(N, cs, panel_threads(ctx, N, cs)) ? 0 : panel_part_bytes(N - 1, cs)) +
+         (!panels || panel_part_lds(N, cs, panel_threads(ctx, N, cs)) ? 0 : panel_part_bytes(N - 1, cs)) +
          sizeof(double) * (3 * size_t(N) + size_t(m) + 1 +
                            (N <= kSmallOrder ? 0 : 4 * size_t(N) * mp + size_t(std::max(m, 1)) * std::max(m, 1))) +
          sizeof(int) * size_t(std::max(m, 1)) + 16 * 256;
