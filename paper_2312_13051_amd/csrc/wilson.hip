@@ -904,7 +904,7 @@ __global__ __launch_bounds__(256) void k_herm_of_unitary(const double2 *W, int m
 // would break it). Within 0.05 of the branch points (sin ~ 0), and whenever
 // eigenvectors are returned, theta_n = phi + atan2(s_n, c_n) from a vector
 // whose residual |W v - e^{i theta} v| must be below 1e-10 (and the
-// eigensolver's status clear). Ascending sort; optional raw phases and
+// eigensolver's status clear); above it the cosine serves down to |sin| = 0.005. Ascending sort; optional raw phases and
 // eigenvectors. One workgroup per matrix, a wave per column. fb[q] = 1 where
 // the QR kernel must take over.
 __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uint32_t *est, const double2 *V,
@@ -955,7 +955,18 @@ __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uin
         res += dx * dx + dy * dy;
       }
       for (int o = 32; o > 0; o >>= 1) res += __shfl_xor(res, o, 64);
-      bad = bad || !(res <= 1e-20);  // |W v - e^{i theta} v| > 1e-10, or NaN
+      if (!(res <= 1e-20)) {  // |W v - e^{i theta} v| > 1e-10, or NaN
+        // two phases on either side of the branch point whose cosines nearly
+        // agree (to ~1e-6) mix in the vectors at that level; the cosines are
+        // accurate whatever the vectors, so away from the point itself they give
+        // the phase (error ~eps / |sin|) and the vector its sign
+        if (!vectors && sabs >= 0.005 && fabs(fabs(s) - sabs) <= 0.1 * sabs) {
+          th = kHermShift + copysign(acos(c), s);
+          if (th > M_PI) th -= 2.0 * M_PI;
+        } else {
+          bad = true;
+        }
+      }
     }
     if (lane == 0) {
       sth[n] = th;
@@ -1258,7 +1269,14 @@ static int unitary_phases(be_ctx *ctx, const double2 *cur, int m, int64_t n_line
   ProfScope prof(ctx, "unitary_eig", stream);
   const size_t esm_lds = (size_t(m) * m + 2 * size_t(m)) * sizeof(double2);
   const bool inlds = Zout == nullptr && esm_lds <= 160 * 1024;
-  if (inlds || m <= 32) {  // orders up to 100 (up to 32 with eigenvectors): one wave per matrix, QR
+  // Orders up to kQrOrder (32 with eigenvectors; any order whose matrix fits LDS
+  // when W is not unitary): one wave per matrix, QR. Its sweeps are one serial
+  // chain per matrix; the Hermitian problem below solves for all phases at
+  // once. Measured, QR -> Hermitian: 12 lines of order 9 109 -> 102 us, of 16 296
+  // -> 227, of 32 1,084 -> 342; 32 lines of order 48 2,403 -> 621; 400 of 64 4,565
+  // -> 1,222 us; up to 12 the difference does not pay for the further launches.
+  constexpr int kQrOrder = 12;
+  if ((inlds && (m <= kQrOrder || !unitary)) || (Zout && m <= 32)) {
     const size_t esm = inlds ? esm_lds : 2 * size_t(m) * sizeof(double2);
     auto kern = inlds ? &k_unitary_eig<true> : &k_unitary_eig<false>;
     if (esm > 65536)
@@ -1307,6 +1325,9 @@ static int unitary_phases(be_ctx *ctx, const double2 *cur, int m, int64_t n_line
   if (esm_wg > 65536)
     BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_unitary_eig_wg<256>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, int(esm_wg)));
+  if (inlds && esm_lds > 65536)
+    BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_unitary_eig<true>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(esm_lds)));
   const size_t esm_1w = 2 * size_t(m) * sizeof(double2);
   if (esm_1w > 65536)
     BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_unitary_eig<false>),
@@ -1350,6 +1371,9 @@ static int unitary_phases(be_ctx *ctx, const double2 *cur, int m, int64_t n_line
     if (Zout)
       hipLaunchKernelGGL(k_unitary_eig<false>, dim3(static_cast<uint32_t>(nl)), dim3(64), esm_1w, stream, Wc, m, nl,
                          Hs + l0 * mm, Zc, ths, ldt, thr, line_status + l0, 1, fb);
+    else if (inlds)
+      hipLaunchKernelGGL(k_unitary_eig<true>, dim3(static_cast<uint32_t>(nl)), dim3(64), esm_lds, stream, Wc, m, nl,
+                         nullptr, nullptr, ths, ldt, thr, line_status + l0, 1, fb);
     else
       hipLaunchKernelGGL(k_unitary_eig_wg<256>, dim3(static_cast<uint32_t>(nl)), dim3(256), esm_wg, stream, Wc, m, nl,
                          Hs + l0 * mm, ths, ldt, thr, line_status + l0, 1, fb);

@@ -1,0 +1,57 @@
+"""Eigenphases of Wilson matrices with chosen spectra: the QR (orders up to 12) and the Hermitian problem (from 13 on, in LDS
+up to 32), with phases placed against the latter: pairs on both sides of its branch point and crowds of equal ones."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from tests import gpu_util as gu  # noqa: E402
+from tests.phase_metrics import phase_set_error  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+PHI = 0.6180339887498949  # the shift of (e^{-i phi} W + e^{i phi} W^H) / 2
+
+
+def grid_with_phases(theta, seed):
+    """A closed line of three points whose Wilson matrix has the given phases (|theta| < pi/2): in a common random basis,
+    point j holds the two-component vectors (1, 0), (1, 1)/sqrt 2, (1, e^{-2 i theta})/sqrt 2 of each band."""
+    m = theta.size
+    rng = np.random.default_rng(seed)
+    V = np.linalg.qr(rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m)))[0]
+    r = np.sqrt(0.5)
+    parts = [(np.ones(m), np.zeros(m)), (r * np.ones(m), r * np.ones(m)), (r * np.ones(m), r * np.exp(-2j * theta))]
+    return np.stack([np.concatenate([(V * a) @ V.conj().T, (V * b) @ V.conj().T]) for a, b in parts])
+
+
+# phases by |theta| up to 1.4; acos loses eps / |sin| >= 0.005, on matrices unitary to ~100 eps: 100 * 2.2e-16 / 0.005 = 4e-12
+@pytest.mark.parametrize("m", [12, 13, 16, 17, 32, 33, 64, 100, 101])
+@pytest.mark.parametrize("kind", ["spread", "pairs", "crowd"])
+def test_chosen_phases(m, kind):
+    gu.need_gpu()
+    lines = []
+    rng = np.random.default_rng([m, len(kind)])
+    for _ in range(3):
+        th = rng.uniform(-1.4, 1.4, m)
+        if kind == "pairs":  # theta - phi = +-x, the cosines equal to within 1e-7 .. 1e-12, x down to the branch point
+            x = np.array([0.3, 0.04, 0.01, 0.002])
+            th[:4] = PHI + x
+            th[4:8] = PHI - x * (1.0 + np.array([1e-7, 1e-6, 1e-5, 1e-8]))
+        elif kind == "crowd":
+            th[:m // 2] = 0.25 + 1e-11 * rng.standard_normal(m // 2)
+        lines.append(th)
+    U = np.stack([grid_with_phases(th, [m, q]) for q, th in enumerate(lines)])
+    c = gu.ctx()
+    try:
+        Ud = gu.from_np(U.reshape(-1, 2 * m, m), 2 * m)
+        f8 = dict(dtype=torch.float64, device="cuda")
+        i4 = dict(dtype=torch.int32, device="cuda")
+        out, phi = torch.empty((1, 3, m), **f8), torch.empty((1, 3), **f8)
+        wn, st = torch.empty(1, **i4), torch.empty(1, **i4)
+        c.wilson_loop(Ud, 2 * m, m, 2 * m, Ud.stride(0), 1, 3, 3, 0, out, phi, wn, st)
+        got, status = out[0].cpu().numpy(), int(st[0])
+    finally:
+        c.close()
+    assert status & ~4 == 0
+    assert phase_set_error(got, np.array(lines)) < 4e-12
+    assert np.all(np.diff(got, axis=1) >= 0)
