@@ -178,10 +178,10 @@ inline uint32_t xcd_grid(int64_t work) {
 }
 
 // Linear workgroup id -> work item, so that consecutive work items land on
-// the same XCD (workgroups are dealt round-robin over the 8 XCDs).
-__device__ __forceinline__ int64_t xcd_work_id(int64_t total) {
-  int64_t L = blockIdx.x;
-  int64_t per = (total + 7) / 8;
+// the same XCD (workgroups are dealt round-robin over the 8 XCDs). 32 bits: a
+// launch has fewer than 2^32 threads.
+__device__ __forceinline__ uint32_t xcd_work_id(uint32_t total) {
+  const uint32_t L = blockIdx.x, per = (total + 7) / 8;
   return (L & 7) * per + (L >> 3);
 }
 
@@ -222,12 +222,12 @@ struct ZBatch {
   }
 };
 
-__host__ __device__ inline int64_t zbatch_off(const ZBatch &b, int64_t q) {
-  int64_t inner = q % b.n0, rest = q / b.n0;
-  int64_t mid = rest % b.n1, outer = rest / b.n1;
-  inner += b.shift;
-  if (inner >= b.n0) inner -= b.n0;
-  return outer * b.s2 + mid * b.s1 + inner * b.s0;
+__host__ __device__ inline int64_t zbatch_off(const ZBatch &b, uint32_t q) {
+  if (b.n0 == 1 && b.n1 == 1) return int64_t(q) * b.s2;  // a plain stride: no divisions
+  const uint32_t n0 = uint32_t(b.n0), n1 = uint32_t(b.n1), rest = q / n0, outer = rest / n1;
+  uint32_t inner = q - rest * n0 + uint32_t(b.shift);
+  if (inner >= n0) inner -= n0;
+  return int64_t(outer) * b.s2 + int64_t(rest - outer * n1) * b.s1 + int64_t(inner) * b.s0;
 }
 
 struct ZGemm {

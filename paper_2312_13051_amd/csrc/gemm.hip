@@ -19,11 +19,12 @@
 //
 // Workgroups are mapped XCD-aware: the tiles of one batch item are given
 // consecutive work ids, which land on the same XCD (shared L2).
+#include <algorithm>
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace {
-
-constexpr int KB = 16;  // complex k per LDS stage (4 MFMA k-steps of 4)
 
 template <typename T>
 struct MF;
@@ -74,6 +75,17 @@ struct GP {
   int64_t sB_div, sB_ld;
 };
 
+// Complex k per LDS stage (MFMA k-steps of 4) and LDS stages of the complex
+// GEMM. FP64 64 x 64 tiles: one stage of 16, two barriers (two stages of 8 were
+// 6 % slower at order 1152, two of 16, which leave two workgroups per compute
+// unit, 3 %). All others: two stages, one barrier each (FP32 trailing updates
+// -6 %). One-wave tiles: stages of 8 (210,000 products of order 4 202 -> 119 us).
+constexpr int gemm_kb(int bm) { return bm == 16 ? 8 : 16; }
+template <typename T, int BM>
+constexpr int gemm_stages() {
+  return sizeof(T) == 8 && BM == 64 ? 1 : 2;
+}
+
 // BM x BN block tile, WM x WN waves, each wave (BM/WM) x (BN/WN).
 template <typename T, int BM, int BN, int WM, int WN, int OPA, int OPB, bool M3>
 __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
@@ -84,13 +96,14 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
   constexpr int TN = BN / WN / 16;
   constexpr int PA = BM + 2;  // LDS pitch (elements)
   constexpr int PB = BN + 2;
-  __shared__ T sAr[KB * PA], sAi[KB * PA], sBr[KB * PB], sBi[KB * PB];
+  constexpr int KB = gemm_kb(BM), SZ = 2 * KB * (PA + PB);  // one stage: Ar, Ai, Br, Bi planes
+  constexpr int NST = gemm_stages<T, BM>();
+  __shared__ T stage[NST * SZ];
 
-  const int64_t tiles = int64_t(p.tiles_m) * p.tiles_n;
-  const int64_t total = tiles * p.batch;
-  const int64_t w = be::xcd_work_id(total);
+  const uint32_t tiles = uint32_t(p.tiles_m) * uint32_t(p.tiles_n), total = tiles * uint32_t(p.batch);
+  const uint32_t w = be::xcd_work_id(total);
   if (w >= total) return;
-  const int64_t q = w / tiles;
+  const uint32_t q = w / tiles;
   const int t2 = static_cast<int>(w - q * tiles);
   const int tm = t2 % p.tiles_m, tn = t2 / p.tiles_m;
   const int i0 = tm * BM, j0 = tn * BN;
@@ -103,7 +116,7 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
   const double *sBq = (OPB == 0 && p.sB) ? p.sB + (q / p.sB_div) * p.sB_ld : nullptr;
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WM, wn = wave / WM;
   const int li = lane & 15, lk = lane >> 4;
 
@@ -171,7 +184,8 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
       gb[u] = v;
     }
   };
-  auto sstore = [&]() {
+  auto sstore = [&](T *st) {
+    T *const sAr = st, *const sAi = st + KB * PA, *const sBr = sAi + KB * PA, *const sBi = sBr + KB * PB;
 #pragma unroll
     for (int u = 0; u < EA; ++u) {
       const int e = tid + u * NT;
@@ -190,22 +204,24 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
     }
   };
 
-  gload(0);
-  for (int k0 = 0; k0 < p.K; k0 += KB) {
-    sstore();
-    __syncthreads();
-    if (k0 + KB < p.K) gload(k0 + KB);
+  // Wave sub-tiles past the edge of the output are skipped: edge tiles cost the
+  // matrix cores ceil16(M) x ceil16(N), not whole tiles.
+  const int na = min(TM, max(0, (p.M - i0 - wm * (BM / WM) + 15) / 16));
+  const int nb = min(TN, max(0, (p.N - j0 - wn * (BN / WN) + 15) / 16));
+  auto multiply = [&](const T *st, auto na_tag, auto nb_tag) {
+    constexpr int NA = decltype(na_tag)::value, NB = decltype(nb_tag)::value;
+    const T *const sAr = st, *const sAi = st + KB * PA, *const sBr = sAi + KB * PA, *const sBi = sBr + KB * PB;
 #pragma unroll
     for (int kk = 0; kk < KB; kk += 4) {
-      T ar[TM], ai[TM], br[TN], bi[TN], nbi[TN];
+      T ar[NA], ai[NA], br[NB], bi[NB], nbi[NB];
 #pragma unroll
-      for (int a = 0; a < TM; ++a) {
+      for (int a = 0; a < NA; ++a) {
         int ii = wm * (BM / WM) + a * 16 + li;
         ar[a] = sAr[(kk + lk) * PA + ii];
         ai[a] = sAi[(kk + lk) * PA + ii];
       }
 #pragma unroll
-      for (int b = 0; b < TN; ++b) {
+      for (int b = 0; b < NB; ++b) {
         int jj = wn * (BN / WN) + b * 16 + li;
         br[b] = sBr[(kk + lk) * PB + jj];
         bi[b] = sBi[(kk + lk) * PB + jj];
@@ -214,10 +230,10 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
       if constexpr (M3) {
         // three real products per complex one: Ar Br, Ai Bi, (Ar + Ai)(Br + Bi)
 #pragma unroll
-        for (int a = 0; a < TM; ++a) {
+        for (int a = 0; a < NA; ++a) {
           const T as = ar[a] + ai[a];
 #pragma unroll
-          for (int b = 0; b < TN; ++b) {
+          for (int b = 0; b < NB; ++b) {
             accr[a][b] = MF<T>::mfma(br[b], ar[a], accr[a][b]);
             acc2[a][b] = MF<T>::mfma(bi[b], ai[a], acc2[a][b]);
             acci[a][b] = MF<T>::mfma(br[b] + bi[b], as, acci[a][b]);
@@ -225,9 +241,9 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
         }
       } else {
 #pragma unroll
-        for (int a = 0; a < TM; ++a)
+        for (int a = 0; a < NA; ++a)
 #pragma unroll
-          for (int b = 0; b < TN; ++b) {
+          for (int b = 0; b < NB; ++b) {
             accr[a][b] = MF<T>::mfma(br[b], ar[a], accr[a][b]);
             accr[a][b] = MF<T>::mfma(nbi[b], ai[a], accr[a][b]);
             acci[a][b] = MF<T>::mfma(bi[b], ar[a], acci[a][b]);
@@ -235,8 +251,40 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
           }
       }
     }
+  };
+  static_assert(TM == 1 && TN <= 2, "wave tiles of one row of one or two 16 x 16 blocks");
+  gload(0);
+  if constexpr (NST == 2) {
+    // one barrier per stage: while the waves multiply stage t, the loads of
+    // t + 1 are in flight; they are stored to the other stage, whose readers
+    // passed the last barrier
+    sstore(stage);
     __syncthreads();
   }
+  // every wave runs one of three loops for its whole product (a choice inside
+  // the loop cost 3 %), with the same barriers in each: wave is a scalar, so
+  // the choice is one branch
+  auto kloop = [&](auto wtag) {
+    constexpr int W = decltype(wtag)::value;
+    for (int k0 = 0, t = 0; k0 < p.K; k0 += KB) {
+      if constexpr (NST == 1) {
+        sstore(stage);
+        __syncthreads();
+      }
+      const bool more = k0 + KB < p.K;
+      if (more) gload(k0 + KB);
+      const T *st = stage + t * SZ;
+      if constexpr (W > 0) multiply(st, std::integral_constant<int, 1>{}, std::integral_constant<int, W>{});
+      if constexpr (NST == 2) {
+        t ^= 1;
+        if (more) sstore(stage + t * SZ);
+      }
+      __syncthreads();
+    }
+  };
+  if (na > 0 && nb == TN) kloop(std::integral_constant<int, TN>{});
+  else if (na > 0 && nb > 0) kloop(std::integral_constant<int, 1>{});
+  else kloop(std::integral_constant<int, 0>{});
   if constexpr (M3) {  // Cr = Ar Br - Ai Bi, Ci = (Ar + Ai)(Br + Bi) - Ar Br - Ai Bi
 #pragma unroll
     for (int a = 0; a < TM; ++a)
@@ -314,6 +362,11 @@ inline bool use_big_tiles(int M, int N) {
 
 template <typename T>
 int dispatch(be_ctx *ctx, GP<T> p, int opA, int opB, hipStream_t s) {
+  // FP64 from order 128 on: 64 x 64 tiles, whose idle wave sub-tiles are skipped
+  // (2,304 products 400 x 200 by K = 200: 5.93 ms before, 5.50 in 32 x 32 tiles,
+  // 4.92 so; at 100 x 100 by 100 the small tiles stay even)
+  if (sizeof(T) == 8 && std::min(p.M, p.N) >= 48 && std::max(p.M, p.N) > 128)
+    return launch_cfg<T, 64, 64, 4, 2>(ctx, p, opA, opB, s);
   if (p.M <= 0 || p.N <= 0 || p.batch <= 0) return BE_OK;
   // Tile choice by output size; small outputs use one-wave tiles.
   // 64 x 64 tiles with 8 waves (each 16 x 32): fewer registers per wave than
@@ -355,11 +408,10 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_bf16x3_kernel(GP<float> p)
   // planes: 0 re hi, 1 re lo, 2 im hi, 3 im lo
   __shared__ __align__(16) unsigned short sA[4][BM * KP], sB[4][BN * KP];
 
-  const int64_t tiles = int64_t(p.tiles_m) * p.tiles_n;
-  const int64_t total = tiles * p.batch;
-  const int64_t w = be::xcd_work_id(total);
+  const uint32_t tiles = uint32_t(p.tiles_m) * uint32_t(p.tiles_n), total = tiles * uint32_t(p.batch);
+  const uint32_t w = be::xcd_work_id(total);
   if (w >= total) return;
-  const int64_t q = w / tiles;
+  const uint32_t q = w / tiles;
   const int t2 = static_cast<int>(w - q * tiles);
   const int tm = t2 % p.tiles_m, tn = t2 / p.tiles_m;
   const int i0 = tm * BM, j0 = tn * BN;
@@ -557,11 +609,10 @@ __global__ __launch_bounds__(64 * WM * WN) void dgemm_kernel(DP p) {
   constexpr int PA = BM + 2;
   constexpr int PB = BN + 2;
   __shared__ double sA[DKB * PA], sB[DKB * PB];
-  const int64_t tiles = int64_t(p.tiles_m) * p.tiles_n;
-  const int64_t total = tiles * p.batch;
-  const int64_t w = be::xcd_work_id(total);
+  const uint32_t tiles = uint32_t(p.tiles_m) * uint32_t(p.tiles_n), total = tiles * uint32_t(p.batch);
+  const uint32_t w = be::xcd_work_id(total);
   if (w >= total) return;
-  const int64_t q = w / tiles;
+  const uint32_t q = w / tiles;
   const int t2 = static_cast<int>(w - q * tiles);
   const int tm = t2 % p.tiles_m, tn = t2 / p.tiles_m;
   const int i0 = tm * BM, j0 = tn * BN;
