@@ -63,11 +63,15 @@ __host__ __device__ __forceinline__ C mk(double x, double y) {
   return r;
 }
 
+// Columns of the T factor that a panel of an order-N matrix can fill (small
+// orders keep the LDS for more matrices per compute unit).
+__host__ __device__ inline int panel_cols(int N) { return N < NB ? N : NB; }
+
 // Byte offset of the panel kernel's partial vectors in its dynamic LDS: after
-// v, y (N each), four NB vectors, the NB x NB T factor and the reduction
+// v, y (N each), four NB vectors, the NB x panel_cols(N) T factor and the reduction
 // scratch (2 values per wave), 64-byte aligned.
 __host__ __device__ inline size_t panel_part_offset(int N, size_t csize, int nt) {
-  return ((2 * size_t(N) + 4 * NB + NB * NB) * csize + 2 * size_t(nt / 64) * (csize / 2) + 63) & ~size_t(63);
+  return ((2 * size_t(N) + 4 * NB + NB * panel_cols(N)) * csize + 2 * size_t(nt / 64) * (csize / 2) + 63) & ~size_t(63);
 }
 
 // Column groups per tile of the panel's matrix-vector product for a trailing
@@ -165,8 +169,9 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? (NT == 1024 ? 1 : CW == 4 ? 6 
   C *sWr = sVr + NB;                        // row j of W (NB)
   C *st1 = sWr + NB;                        // W^H v (NB)
   C *st2 = st1 + NB;                        // V^H v (NB)
-  C *sT = st2 + NB;                         // NB x NB, column-major
-  T *red = reinterpret_cast<T *>(sT + NB * NB);  // 2 * waves
+  C *sT = st2 + NB;                         // NB x panel_cols(N), column-major
+  const int nT = NB * panel_cols(N);
+  T *red = reinterpret_cast<T *>(sT + nT);  // 2 * waves
   __shared__ C s_tau, s_scal;
   __shared__ T s_beta;
 
@@ -178,7 +183,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? (NT == 1024 ? 1 : CW == 4 ? 6 
   C *V2 = W + int64_t(NB) * N;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = NT / 64;
 
-  for (int e2 = tid; e2 < NB * NB; e2 += NT) sT[e2] = mk<C>(0, 0);
+  for (int e2 = tid; e2 < nT; e2 += NT) sT[e2] = mk<C>(0, 0);
   __syncthreads();
 
   for (int jj = 0; jj < nbp; ++jj) {
@@ -445,7 +450,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? (NT == 1024 ? 1 : CW == 4 ? 6 
   }
   // ---- write the panel's T factor
   C *Tq = Tm + q * sTm;
-  for (int e2 = tid; e2 < NB * NB; e2 += NT) Tq[e2] = sT[e2];
+  for (int e2 = tid; e2 < NB * NB; e2 += NT) Tq[e2] = e2 < nT ? sT[e2] : mk<C>(0, 0);
   (void)status;
 }
 
