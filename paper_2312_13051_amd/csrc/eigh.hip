@@ -487,8 +487,8 @@ __device__ bool load_tridiag(const double *d, const double *e, int64_t q, int64_
 // eigenvalue left wider than its tolerance flags the matrix
 // BE_ST_NONCONVERGED.
 __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *e, int64_t sDE, int N, int lo, int hi,
-                                                 double bis_rel, int max_it, double *evals, double *lamg, double2 *U,
-                                                 int ldu, int64_t sU, uint32_t *status) {
+                                                 double bis_rel, double qwidth, int max_it, double *evals,
+                                                 double *lamg, double2 *U, int ldu, int64_t sU, uint32_t *status) {
   extern __shared__ double2 tsm2[];
   double2 *sde = tsm2;                                // N: (d_i, e_{i-1}^2)
   double *sd = reinterpret_cast<double *>(sde + N);  // N
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *
   double *slam = se2 + N;  // m + 4: [lambda_0, lambda_{N-1}, lambda_{lo-1}, lambda_{hi}, lambda_lo..]
   const int m = hi - lo;
   __shared__ int s_bad;
-  __shared__ double mm[3 * (PT / 64)];
+  __shared__ double mm[2 * (PT / 64)];
   const int64_t q = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = PT / 64;
   if (!load_tridiag(d, e, q, sDE, N, sd, nullptr, se2, &s_bad)) {
@@ -509,50 +509,49 @@ __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *
     }
     return;
   }
-  for (int i = tid; i < N; i += PT) sde[i] = make_double2(sd[i], i > 0 ? se2[i - 1] : 0.0);
-  // Gershgorin interval and pivot threshold
-  double gl = INFINITY, gu = -INFINITY, emax2 = 0.0;
+  // Gershgorin interval
+  double gl = INFINITY, gu = -INFINITY;
   for (int i = tid; i < N; i += PT) {
     const double rad = sqrt(se2[i]) + (i > 0 ? sqrt(se2[i - 1]) : 0.0);
     gl = fmin(gl, sd[i] - rad);
     gu = fmax(gu, sd[i] + rad);
-    emax2 = fmax(emax2, se2[i]);
   }
   for (int o = 32; o > 0; o >>= 1) {
     gl = fmin(gl, __shfl_xor(gl, o, 64));
     gu = fmax(gu, __shfl_xor(gu, o, 64));
-    emax2 = fmax(emax2, __shfl_xor(emax2, o, 64));
   }
   if (lane == 0) {
-    mm[3 * wave] = gl;
-    mm[3 * wave + 1] = gu;
-    mm[3 * wave + 2] = emax2;
+    mm[2 * wave] = gl;
+    mm[2 * wave + 1] = gu;
   }
   __syncthreads();
   gl = mm[0];
   gu = mm[1];
-  emax2 = mm[2];
   for (int w = 1; w < nw; ++w) {
-    gl = fmin(gl, mm[3 * w]);
-    gu = fmax(gu, mm[3 * w + 1]);
-    emax2 = fmax(emax2, mm[3 * w + 2]);
+    gl = fmin(gl, mm[2 * w]);
+    gu = fmax(gu, mm[2 * w + 1]);
   }
   const double tnorm = fmax(fabs(gl), fabs(gu));
-  const double pivmin = DBL_MIN * fmax(1.0, emax2);
   const double eps = DBL_EPSILON;
-  gl -= 2.0 * eps * tnorm + 2.0 * pivmin;
-  gu += 2.0 * eps * tnorm + 2.0 * pivmin;
+  // the scaled matrix (norm in [1/2, 1]) and its interval
+  const double sc = sturm_scale(tnorm), isc = 1.0 / sc, tn = tnorm * sc;
+  for (int i = tid; i < N; i += PT) {
+    sde[i] = make_double2(sd[i] * sc, fmax(i > 0 ? se2[i - 1] * sc * sc : 0.0, kSturmE2));
+  }
+  gl = gl * sc - 2.0 * eps * tn - DBL_MIN;
+  gu = gu * sc + 2.0 * eps * tn + DBL_MIN;
   // absolute floor eps^2 ||T||: far below any attainable accuracy, it only
   // ends the halving at an eigenvalue (near) zero, where eps |lambda| alone
   // would ask for ~1000 steps; from an interval of 1/257 of the Gershgorin
   // width it takes at most ~97 steps
-  const double tol_abs = fmax(bis_rel, DBL_EPSILON * DBL_EPSILON) * tnorm;
+  const double tol_abs = fmax(bis_rel, DBL_EPSILON * DBL_EPSILON) * tn;
   // multisection: Sturm counts at PT points spread over the Gershgorin
   // interval (one per thread) bracket every eigenvalue to one of PT + 1
   // subintervals, which replaces the first ~8 bisection steps of every lane
   __shared__ int s_cnt[PT];
   const double hstep = (gu - gl) / double(PT + 1);
-  s_cnt[tid] = sturm_count_i(sde, N, gl + double(tid + 1) * hstep, pivmin);
+  __syncthreads();
+  s_cnt[tid] = sturm_count_p(sde, N, gl + double(tid + 1) * hstep);
   __syncthreads();
   const int nidx = m + 4;
   for (int t = tid; t < nidx; t += PT) {
@@ -571,13 +570,13 @@ __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *
       bool conv = false;
       for (int it = 0; it <= max_it; ++it) {
         const double mid = 0.5 * (a + b);
-        conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + pivmin, tol_abs) || mid <= a || mid >= b;
+        conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + DBL_MIN, tol_abs) || mid <= a || mid >= b;
         if (conv || it == max_it) break;
-        if (sturm_count_i(sde, N, mid, pivmin) > k) b = mid;
+        if ((b - a > qwidth ? sturm_count_p(sde, N, mid) : sturm_count_i(sde, N, mid)) > k) b = mid;
         else a = mid;
       }
       if (!conv) atomicOr(&status[q], BE_ST_NONCONVERGED);
-      val = 0.5 * (a + b);
+      val = 0.5 * (a + b) * isc;
     }
     slam[t] = val;
   }
@@ -1434,7 +1433,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
     // closely spaced ones (bis_rel > 0 would stop at bis_rel ||T||)
     const double bis_rel = 0.0;
     hipLaunchKernelGGL(tri_bisect, dim3(nb_mat), dim3(PT), smb, stream, dd, ee, int64_t(N), N, lo, hi, bis_rel,
-                       ctx->dbg_bisect_max_iter, evals, lamg, U, ldu, us, status);
+                       mixed ? kQuotientWidth : 0.0, ctx->dbg_bisect_max_iter, evals, lamg, U, ldu, us, status);
   }
   BE_RET_IF(check_launch(ctx, "tri_bisect"));
   if (m == 0) return BE_OK;

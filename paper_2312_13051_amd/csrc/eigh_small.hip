@@ -8,13 +8,13 @@
 // wave cooperate, so there are no workgroup barriers. The general path gives
 // such a matrix four workgroups of 256 threads one after another, a padded
 // 16 x 16 tile in each of five MFMA products and ~12 launches with a
-// read-back. Bound by the latency of the serial recurrences (FP64 division
-// chains of the Sturm counts, one lane per eigenvalue), hence as many matrices
+// read-back. Bound by the latency of the serial recurrences (Sturm counts, one
+// lane per eigenvalue, and the columns of the reduction), hence as many matrices
 // per wave as have rows for its lanes. FP64, half the bands, general path ->
-// this one: order 4, 10,000 matrices 945 -> 72 us; 8, 4,096: 765 -> 92; 16,
-// 4,096: 1,416 -> 172; 32, 64: 604 -> 301, 8,192: 6,547 -> 2,104.
-// Tridiagonal part of the mixed path: order 8, 4,096: 345 -> 60; 32, 4,096:
-// 810 -> 463.
+// this one: order 4, 10,000 matrices 945 -> 62 us; 16, 4,096: 1,416 -> 158; 32,
+// 64: 604 -> 269, 8,192: 6,547 -> 1,837.
+// Tridiagonal part of the mixed path: order 8, 4,096: 345 -> 54; 32, 4,096:
+// 810 -> 377.
 //
 // FULL (FP64): from H to U. Otherwise (mixed paths) the reduction has been
 // done in FP32 by the panel kernel, and the back-transformation follows as
@@ -48,11 +48,12 @@ __device__ __forceinline__ double grp_max(double v) {
 
 // LDS of one matrix, in doubles: d, e, e^2 (N each), eigenvalues (m + 4),
 // block starts, group ids and marks (N + 1 + 2 m ints), X (N m), scratch for the
-// elimination's diagonals and the Gram matrix or, later, U (2 (N + 1) m),
-// and with FULL the matrix, v, w and tau (N N + 3 N complex).
+// elimination's diagonals and the Gram matrix or, later, U (2 (N + 1) m), and
+// with FULL the matrix, v, w and tau (N N + 3 N complex), otherwise the scaled
+// pairs of the Sturm counts (2 N), which with FULL lie where w was.
 __host__ __device__ inline int small_doubles(int N, int m, bool full) {
   const int d = 3 * N + (m + 4) + (2 * m + N + 2) / 2 + N * m + 2 * (N + 1) * m;
-  return (d + 1 + (full ? 2 * (N * N + 3 * N) : 0)) & ~1;  // even: the complex part is 16-byte aligned
+  return (d + 1 + 2 * (full ? N * N + 3 * N : N)) & ~1;  // even: the complex part is 16-byte aligned
 }
 
 template <int TPM, bool FULL, typename OUT>
@@ -69,7 +70,8 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(double2 *H, int64_t sH, 
   double *base = reinterpret_cast<double *>(sm2) + (lane / TPM) * per;
   double2 *A = reinterpret_cast<double2 *>(base);  // FULL: N x N, then v, w, tau (N each)
   double2 *sv = A + (FULL ? N * N : 0), *sw = sv + (FULL ? N : 0), *stau = sw + (FULL ? N : 0);
-  double *sd = reinterpret_cast<double *>(stau + (FULL ? N : 0)), *se = sd + N, *se2 = se + N, *slam = se2 + N;
+  double2 *sde = FULL ? sw : stau;  // w is done with when the counts begin
+  double *sd = reinterpret_cast<double *>(FULL ? stau + N : sde + N), *se = sd + N, *se2 = se + N, *slam = se2 + N;
   double *X0 = slam + m + 4, *ZG = X0 + N * m;
   int *sblk = reinterpret_cast<int *>(ZG + 2 * (N + 1) * m), *smark = sblk + N + 1, *sbad = smark + m;
   const double eps = DBL_EPSILON;
@@ -181,9 +183,14 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(double2 *H, int64_t sH, 
   gu = grp_max<TPM>(gu);
   emax2 = grp_max<TPM>(emax2);
   const double tnorm = fmax(fabs(gl), fabs(gu)), pivmin = DBL_MIN * fmax(1.0, emax2);
-  gl -= 2.0 * eps * tnorm + 2.0 * pivmin;
-  gu += 2.0 * eps * tnorm + 2.0 * pivmin;
-  const double tol_abs = eps * eps * tnorm;
+  const double sc = sturm_scale(tnorm), isc = 1.0 / sc, tn = tnorm * sc;
+  for (int i = t; i < N; i += TPM) {
+    sde[i] = make_double2(sd[i] * sc, fmax(i > 0 ? se2[i - 1] * sc * sc : 0.0, kSturmE2));
+  }
+  wave_lds_sync();
+  gl = gl * sc - 2.0 * eps * tn - DBL_MIN;
+  gu = gu * sc + 2.0 * eps * tn + DBL_MIN;
+  const double tol_abs = eps * eps * tn;
   const int hi = lo + m;
   for (int k0 = t; k0 < m + 4; k0 += TPM) {  // [lambda_0, lambda_{N-1}, lambda_{lo-1}, lambda_hi, lambda_lo ..]
     const int k = k0 == 0 ? 0 : k0 == 1 ? N - 1 : k0 == 2 ? lo - 1 : k0 == 3 ? (hi < N ? hi : -1) : lo + k0 - 4;
@@ -193,23 +200,13 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(double2 *H, int64_t sH, 
       bool conv = false;
       for (int it = 0; it <= max_it; ++it) {
         const double mid = 0.5 * (a + b);
-        conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + pivmin, tol_abs) || mid <= a || mid >= b;
+        conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + DBL_MIN, tol_abs) || mid <= a || mid >= b;
         if (conv || it == max_it) break;
-        int cnt = 0;  // Sturm count (as sturm_count), loads four steps ahead
-        double qv = sd[0] - mid;
-        if (fabs(qv) < pivmin) qv = -pivmin;
-        cnt += qv < 0.0;
-#pragma unroll 4
-        for (int i = 1; i < N; ++i) {
-          qv = (sd[i] - mid) - div_nr(se2[i - 1], qv);
-          if (fabs(qv) < pivmin) qv = -pivmin;
-          cnt += qv < 0.0;
-        }
-        if (cnt > k) b = mid;
+        if ((FULL || b - a > kQuotientWidth ? sturm_count_p(sde, N, mid) : sturm_count_i(sde, N, mid)) > k) b = mid;
         else a = mid;
       }
       if (!conv) st |= BE_ST_NONCONVERGED;
-      val = 0.5 * (a + b);
+      val = 0.5 * (a + b) * isc;
     }
     slam[k0] = val;
   }

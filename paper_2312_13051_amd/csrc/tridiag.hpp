@@ -36,21 +36,75 @@ __device__ __forceinline__ int sturm_count(const double *sd, const double *se2, 
   return cnt;
 }
 
-// The same count from the interleaved pairs sde[i] = (d_i, e_{i-1}^2): one
-// LDS read per step, four steps' reads issued together.
-__device__ __forceinline__ int sturm_count_i(const double2 *sde, int N, double x, double pivmin) {
+// The same count for bisection, from the principal minors' recurrence
+// p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}: its sign changes count the
+// eigenvalues below x, as the negative quotients p_i / p_{i-1} do, with the same
+// backward error (a few ulps of d_i - x and e^2), but each step is one multiply
+// and one fused multiply-add instead of a reciprocal, its refinement and four
+// more operations in one dependent chain. T comes scaled (sturm_scale) with its
+// infinity norm in [1/2, 1], as pairs (d_i, e_{i-1}^2) with e^2 >= kSturmE2: a
+// step then grows p by at most 3 and two steps shrink it by no less than
+// kSturmE2, so that taking out the exponent every eighth step keeps p in
+// range, and no two consecutive minors vanish. Half the bands, quotients -> minors
+// throughout: 2,304 matrices of order 400 7.31 -> 3.53 ms, of order 200 2.85 ->
+// 1.35, 120 of order 64 181 -> 113 us (two counts at once in a thread, with half
+// the waves: 191 us and 5.94 ms).
+constexpr double kSturmE2 = 1e-36;  // (1e-18 ||T||)^2, below the rounding of T
+__device__ __forceinline__ int sturm_count_p(const double2 *de, int N, double x) {
+  double p0 = 1.0, p1 = de[0].x - x;
+  uint32_t s1 = uint32_t(__double2hiint(p1)), cnt = s1 >> 31;
+  auto step = [&](double2 v) {
+    const double pn = fma(v.x - x, p1, -(v.y * p0));
+    const uint32_t sn = uint32_t(__double2hiint(pn));
+    cnt += (sn ^ s1) >> 31;
+    p0 = p1;
+    p1 = pn;
+    s1 = sn;
+  };
+  int i = 1;
+  for (; i + 8 <= N; i += 8) {
+    double2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = de[i + u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) step(v[u]);
+    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
+    p0 = __builtin_amdgcn_ldexp(p0, ex);
+    p1 = __builtin_amdgcn_ldexp(p1, ex);
+  }
+  for (; i < N; ++i) step(de[i]);
+  return int(cnt);
+}
+
+// The quotients' count from the same pairs, four steps' reads issued together.
+__device__ __forceinline__ int sturm_count_i(const double2 *de, int N, double x) {
   int cnt = 0;
-  double qv = sde[0].x - x;
-  if (fabs(qv) < pivmin) qv = -pivmin;
+  double qv = de[0].x - x;
+  if (fabs(qv) < DBL_MIN) qv = -DBL_MIN;
   cnt += qv < 0.0;
 #pragma unroll 4
   for (int i = 1; i < N; ++i) {
-    const double2 de = sde[i];
-    qv = (de.x - x) - div_nr(de.y, qv);
-    if (fabs(qv) < pivmin) qv = -pivmin;
+    const double2 v = de[i];
+    qv = (v.x - x) - div_nr(v.y, qv);
+    if (fabs(qv) < DBL_MIN) qv = -DBL_MIN;
     cnt += qv < 0.0;
   }
   return cnt;
+}
+
+// Interval width, relative to ||T||, from which a mixed path's bisection counts
+// by quotients. The two counts differ only within a few eps ||T|| of an
+// eigenvalue, i.e. in an eigenvalue's last bits; the vectors of a degenerate
+// level are a basis that those bits choose, and a mixed path rounds that basis
+// to FP32. So its last bits stay the quotients', while the wide intervals,
+// 2^14 such distances and more, take the cheaper count (4,608 matrices of order 400:
+// 11.0 -> 7.65 ms).
+constexpr double kQuotientWidth = 0x1p-38;
+
+// Power of two that takes a norm into [1/2, 1) (1 for a zero or non-finite norm;
+// at most 2^1000, so that a norm among the subnormal numbers has a finite one)
+__device__ __forceinline__ double sturm_scale(double tnorm) {
+  return tnorm > 0.0 && tnorm < INFINITY ? ldexp(1.0, min(-ilogb(tnorm) - 1, 1000)) : 1.0;
 }
 
 __device__ __forceinline__ double hash_unit(uint64_t a, uint64_t b) {
