@@ -1698,6 +1698,9 @@ static int eigh_run(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t ma
     if (N <= kSmallOrder)
       return eigh_small_fp64(ctx, H, N, ld, mat_stride, n_mat, band_lo, band_hi, evals, U, ldu, u_stride, status, stream,
                              clu_rel);
+  } else if (N <= kSmallMixed && !bf16x3) {
+    return eigh_small_c64(ctx, H, N, ld, mat_stride, n_mat, band_lo, band_hi, evals, U, ldu, u_stride, status, stream,
+                          clu_rel);
   }
   const size_t per = eigh_chunk_bytes<T>(ctx, N, m);
   const int64_t cap = eigh_sub_batch<T>(ctx, N, per, ctx->ws_bytes[WS_EIGH], n_mat);
@@ -1747,7 +1750,10 @@ static int eigh_refined_chunk(be_ctx *ctx, const double2 *H, int N, int ld, int6
     BE_RET_IF(check_launch(ctx, "split_h"));
   }
   // all bands on the mixed path (zeroes status)
-  BE_RET_IF(eigh_chunk<float>(ctx, Hc, N, N, NN, nb, 0, N, lam, Uall, N, NN, status, stream));
+  if (N <= kSmallMixed)
+    BE_RET_IF(eigh_small_c64(ctx, Hc, N, N, NN, nb, 0, N, lam, Uall, N, NN, status, stream, kCluRel));
+  else
+    BE_RET_IF(eigh_chunk<float>(ctx, Hc, N, N, NN, nb, 0, N, lam, Uall, N, NN, status, stream));
   auto zg = [&](int M_, int N_, int K_, int opA, const double2 *A_, int lda_, int64_t sA_, const double2 *B_, int ldb_,
                 int64_t sB_, double2 *C_, int ldc_, int64_t sC_, double beta, const char *tag) {
     ZGemm g;

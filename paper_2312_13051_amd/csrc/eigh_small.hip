@@ -13,16 +13,17 @@
 // per wave as have rows for its lanes. FP64, half the bands, general path ->
 // this one: order 4, 10,000 matrices 945 -> 62 us; 16, 4,096: 1,416 -> 158; 32,
 // 64: 604 -> 269, 8,192: 6,547 -> 1,837.
-// Tridiagonal part of the mixed path: order 8, 4,096: 345 -> 54; 32, 4,096:
-// 810 -> 377.
-//
-// FULL (FP64): from H to U. Otherwise (mixed paths) the reduction has been
-// done in FP32 by the panel kernel, and the back-transformation follows as
-// FP32 products: the kernel takes d, e and writes Z (as complex FP32).
+// Mixed path up to order 16, likewise: order 4, 52,500 matrices (a quarter of
+// the nested loops of 21 planes) 460 -> 123 us, of which the panel kernel took
+// 252 (a wave per matrix), three 16 x 16 products 87 and the copy to FP64 24.
+// Tridiagonal part alone, for orders 17 to 32 on the mixed path (reduction by
+// the panel kernel, FP32 products for the back-transformation): 32, 4,096:
+// 810 -> 377 us.
 #include <algorithm>
 
 #include "common.hpp"
 #include "eigh_small.hpp"
+#include "lanes.hpp"
 #include "tridiag.hpp"
 
 namespace {
@@ -46,32 +47,211 @@ __device__ __forceinline__ double grp_max(double v) {
   return v;
 }
 
+// What a launch takes in and gives out
+enum SmallMode {
+  kFull,     // FP64: H -> U
+  kFullC64,  // FP32 reduction and back-transformation: c64 H -> U (c128)
+  kTri       // d, e -> Z (c64)
+};
+
 // LDS of one matrix, in doubles: d, e, e^2 (N each), eigenvalues (m + 4),
 // block starts, group ids and marks (N + 1 + 2 m ints), X (N m), scratch for the
 // elimination's diagonals and the Gram matrix or, later, U (2 (N + 1) m), and
-// with FULL the matrix, v, w and tau (N N + 3 N complex), otherwise the scaled
-// pairs of the Sturm counts (2 N), which with FULL lie where w was.
-__host__ __device__ inline int small_doubles(int N, int m, bool full) {
+// in FP64 the matrix, v, w and tau (N N + 3 N complex), otherwise the scaled
+// pairs of the Sturm counts (2 N), which in FP64 lie where w was; kFullC64 adds
+// the matrix, W and T (N N each) and four vectors in c64.
+__host__ __device__ inline int small_doubles(int N, int m, SmallMode mode) {
   const int d = 3 * N + (m + 4) + (2 * m + N + 2) / 2 + N * m + 2 * (N + 1) * m;
-  return (d + 1 + 2 * (full ? N * N + 3 * N : N)) & ~1;  // even: the complex part is 16-byte aligned
+  const int c = mode == kFull ? 2 * (N * N + 3 * N) : 2 * N + (mode == kFullC64 ? 3 * N * N + 4 * N : 0);
+  return (d + 1 + c) & ~1;  // even: the complex part is 16-byte aligned
 }
 
-template <int TPM, bool FULL, typename OUT>
-__global__ __launch_bounds__(64) void eigh_small_kernel(double2 *H, int64_t sH, int ld, const double *dg,
+// Sum over the TPM lanes of a matrix, in the order in which wave_sum adds the
+// lanes of a wave whose others hold zeros
+template <int TPM>
+__device__ __forceinline__ float grp_sum_f(float v) {
+  if constexpr (TPM > 8) v += lane_xor<8>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<2>(v);
+  v += lane_xor<1>(v);
+  return v;
+}
+
+// Householder reduction of a c64 matrix A (N x N, in LDS, lower triangle; its
+// columns become the reflectors) of order N <= TPM with the panel kernel's
+// arithmetic: that kernel's steps with its lanes' rows, products and sums in
+// the same order, so that a matrix's T and reflectors have the same bits. W:
+// N x N, T: N x N with zeros on entry, the compact-WY factor on return; sv,
+// sy, st2: N each.
+template <int TPM>
+__device__ __forceinline__ void reduce_c64(float2 *A, float2 *W, float2 *T, float2 *sv, float2 *sy, float2 *st2,
+                                           double *sd, double *se, int N, int t) {
+  for (int j = 0; j < N; ++j) {
+    {  // the last reflector's share of column j
+      const int r = j + t;
+      if (r < N) {
+        const float2 a = A[r + j * N];
+        float ar = a.x, ai = a.y;
+        if (j > 0) {
+          const float2 vr = sv[r], wr = sy[r], wj = sy[j], vj = sv[j];
+          ar -= vr.x * wj.x + vr.y * wj.y + wr.x * vj.x + wr.y * vj.y;
+          ai -= vr.y * wj.x - vr.x * wj.y + wr.y * vj.x - wr.x * vj.y;
+        }
+        if (r == j) {
+          ai = 0;
+          sd[j] = double(ar);
+        }
+        A[r + j * N] = make_float2(ar, ai);
+      }
+    }
+    wave_lds_sync();
+    if (j == N - 1) {
+      if (t < N) A[t + j * N] = make_float2(0.f, 0.f);
+      if (t == 0) se[j] = 0.0;
+      wave_lds_sync();
+      break;
+    }
+    float xn = 0;
+    if (j + 2 + t < N) {
+      const float2 a = A[j + 2 + t + j * N];
+      xn += a.x * a.x + a.y * a.y;
+    }
+    xn = grp_sum_f<TPM>(xn);
+    const float2 alpha = A[j + 1 + j * N];
+    float2 tau = make_float2(0.f, 0.f), scal = tau;
+    float beta = alpha.x;
+    if (!(xn == 0.f && alpha.y == 0.f)) {
+      const float nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn);
+      beta = alpha.x >= 0.f ? -nrm : nrm;
+      tau = make_float2((beta - alpha.x) / beta, -alpha.y / beta);
+      const float dr = alpha.x - beta, di = alpha.y;
+      const float den = dr * dr + di * di;
+      scal = make_float2(dr / den, -di / den);
+    }
+    if (t == 0) se[j] = double(beta);
+    float2 v = make_float2(0.f, 0.f);
+    if (t == j + 1) {
+      v = make_float2(1.f, 0.f);
+    } else if (t > j && t < N) {
+      const float2 a = A[t + j * N];
+      v = make_float2(a.x * scal.x - a.y * scal.y, a.x * scal.y + a.y * scal.x);
+    }
+    wave_lds_sync();
+    if (t < N) {
+      sv[t] = v;
+      A[t + j * N] = v;
+    }
+    wave_lds_sync();
+    // y = A v: a lane's row, plus its column of the rows below
+    const int r0 = j + 1, r = r0 + t;
+    const bool rok = r < N;
+    const float2 vr = rok ? sv[r] : make_float2(0.f, 0.f);
+    float yr = 0, yi = 0;
+    float2 col = make_float2(0.f, 0.f);
+    for (int c = r0; c < N; ++c) {
+      const float2 a = (rok && r >= c) ? A[r + c * N] : make_float2(0.f, 0.f);
+      const float2 vc = sv[c];
+      const bool dg = r == c;
+      const float ax = a.x, ay = dg ? 0.f : a.y;
+      yr += ax * vc.x - ay * vc.y;
+      yi += ax * vc.y + ay * vc.x;
+      float2 p = dg ? make_float2(0.f, 0.f) : make_float2(ax * vr.x + ay * vr.y, ax * vr.y - ay * vr.x);
+      p.x = grp_sum_f<TPM>(p.x);
+      p.y = grp_sum_f<TPM>(p.y);
+      if (dg) col = p;
+    }
+    yr += col.x;
+    yi += col.y;
+    // y -= V W^H v + W V^H v; the earlier reflectors' share of column j + 1
+    float pr = 0, pi = 0;
+    for (int c = 0; c < j; ++c) {
+      const float2 w = rok ? W[r + c * N] : make_float2(0.f, 0.f), vv = rok ? A[r + c * N] : make_float2(0.f, 0.f);
+      float2 a, b;
+      a.x = fmaf(w.x, vr.x, w.y * vr.y);
+      a.y = fmaf(w.x, vr.y, -(w.y * vr.x));
+      b.x = fmaf(vv.x, vr.x, vv.y * vr.y);
+      b.y = fmaf(vv.x, vr.y, -(vv.y * vr.x));
+      a.x = grp_sum_f<TPM>(a.x);
+      a.y = grp_sum_f<TPM>(a.y);
+      b.x = grp_sum_f<TPM>(b.x);
+      b.y = grp_sum_f<TPM>(b.y);
+      if (t == 0) st2[c] = b;
+      yr -= vv.x * a.x - vv.y * a.y + w.x * b.x - w.y * b.y;
+      yi -= vv.x * a.y + vv.y * a.x + w.x * b.y + w.y * b.x;
+      const float2 wj = W[j + 1 + c * N], vj = A[j + 1 + c * N];
+      pr += vv.x * wj.x + vv.y * wj.y + w.x * vj.x + w.y * vj.y;
+      pi += vv.y * wj.x - vv.x * wj.y + w.y * vj.x - w.x * vj.y;
+    }
+    const float2 y = make_float2(tau.x * yr - tau.y * yi, tau.x * yi + tau.y * yr);
+    wave_lds_sync();
+    if (rok && j > 0) {
+      const float2 a0 = A[r + (j + 1) * N];
+      A[r + (j + 1) * N] = make_float2(a0.x - pr, a0.y - pi);
+    }
+    if (t < j) {
+      float xr = 0, xi = 0;
+      for (int c = t; c < j; ++c) {
+        const float2 tt = T[t + c * N], b = st2[c];
+        xr += tt.x * b.x - tt.y * b.y;
+        xi += tt.x * b.y + tt.y * b.x;
+      }
+      T[t + j * N] = make_float2(-(tau.x * xr - tau.y * xi), -(tau.x * xi + tau.y * xr));
+    }
+    if (t == 0) T[j + j * N] = tau;
+    float dr = 0, di = 0;
+    if (rok) {
+      dr += y.x * vr.x + y.y * vr.y;
+      di += y.x * vr.y - y.y * vr.x;
+    }
+    dr = grp_sum_f<TPM>(dr);
+    di = grp_sum_f<TPM>(di);
+    const float alr = -0.5f * (tau.x * dr - tau.y * di), ali = -0.5f * (tau.x * di + tau.y * dr);
+    if (t < r0 && t < N) W[t + j * N] = make_float2(0.f, 0.f);
+    if (rok) {
+      const float2 w = make_float2(y.x + alr * vr.x - ali * vr.y, y.y + alr * vr.y + ali * vr.x);
+      W[r + j * N] = w;
+      sy[r] = w;
+    }
+    wave_lds_sync();
+  }
+}
+
+// Entry (i, c) of a c64 product A B (A conjugated with CONJ) over k = 0 .. K-1,
+// A(i, k) = a[k sa], B(k, c) = b[k]: three real products per complex one, each a
+// chain of fused multiply-adds in the order of k, as the matrix cores of the
+// general path's products add them.
+template <bool CONJ>
+__device__ __forceinline__ float2 product_c64(const float2 *a, int sa, const float2 *b, int K) {
+  float rr = 0.f, ii = 0.f, x = 0.f;
+  for (int k = 0; k < K; ++k) {
+    const float2 u = a[k * sa], w = b[k];
+    const float ai = CONJ ? -u.y : u.y;
+    rr = fmaf(u.x, w.x, rr);
+    ii = fmaf(ai, w.y, ii);
+    x = fmaf(u.x + ai, w.x + w.y, x);
+  }
+  return make_float2(rr - ii, x - rr - ii);
+}
+
+template <int TPM, SmallMode MODE, typename IN, typename OUT>
+__global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int ld, const double *dg,
                                                         const double *eg, int64_t sDE, int N, int lo, int m,
                                                         int64_t n_mat, double clu_rel, double tol_orth, int max_it,
                                                         double *evals, OUT *U, int ldu, int64_t sU, uint32_t *status) {
   extern __shared__ double2 sm2[];
   constexpr int MPB = 64 / TPM;
+  constexpr bool FULL = MODE == kFull;
   const int lane = threadIdx.x, t = lane % TPM;
   const int64_t q = int64_t(blockIdx.x) * MPB + lane / TPM;
   const bool live = q < n_mat;
-  const int per = small_doubles(N, m, FULL);
+  const int per = small_doubles(N, m, MODE);
   double *base = reinterpret_cast<double *>(sm2) + (lane / TPM) * per;
-  double2 *A = reinterpret_cast<double2 *>(base);  // FULL: N x N, then v, w, tau (N each)
+  double2 *A = reinterpret_cast<double2 *>(base);  // kFull: N x N, then v, w, tau (N each)
   double2 *sv = A + (FULL ? N * N : 0), *sw = sv + (FULL ? N : 0), *stau = sw + (FULL ? N : 0);
   double2 *sde = FULL ? sw : stau;  // w is done with when the counts begin
-  double *sd = reinterpret_cast<double *>(FULL ? stau + N : sde + N), *se = sd + N, *se2 = se + N, *slam = se2 + N;
+  float2 *Af = reinterpret_cast<float2 *>(sde + N), *Wf = Af + N * N, *Tf = Wf + N * N;  // kFullC64
+  double *sd = FULL ? reinterpret_cast<double *>(stau + N)
+                    : reinterpret_cast<double *>(MODE == kFullC64 ? Tf + N * N + 4 * N : Af), *se = sd + N, *se2 = se + N, *slam = se2 + N;
   double *X0 = slam + m + 4, *ZG = X0 + N * m;
   int *sblk = reinterpret_cast<int *>(ZG + 2 * (N + 1) * m), *smark = sblk + N + 1, *sbad = smark + m;
   const double eps = DBL_EPSILON;
@@ -154,6 +334,17 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(double2 *H, int64_t sH, 
         const int r = e % N, c = e / N;
         Hq[r + int64_t(c) * ld] = r > c ? A[e] : make_double2(0.0, 0.0);
       }
+  } else if constexpr (MODE == kFullC64) {
+    float2 *Hq = H + (live ? q : 0) * sH, *vec = Tf + N * N;
+    for (int e = t; e < N * N; e += TPM) {
+      const int r = e % N, c = e / N;
+      Af[e] = r >= c ? Hq[r + int64_t(c) * ld] : make_float2(0.f, 0.f);
+      Tf[e] = make_float2(0.f, 0.f);
+    }
+    wave_lds_sync();
+    reduce_c64<TPM>(Af, Wf, Tf, vec, vec + N, vec + 2 * N, sd, se, N, t);
+    if (live)
+      for (int e = t; e < N * N; e += TPM) Hq[e % N + int64_t(e / N) * ld] = Af[e];
   } else {
     for (int i = t; i < N; i += TPM) {
       sd[i] = live ? dg[q * sDE + i] : 0.0;
@@ -331,6 +522,25 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(double2 *H, int64_t sH, 
           const int r = e % N, c = e / N;
           U[q * sU + r + int64_t(c) * ldu] = bad ? OUT{NAN, NAN} : OUT{Uc[c * (N + 1) + r].x, Uc[c * (N + 1) + r].y};
         }
+    } else if constexpr (MODE == kFullC64) {
+      // U = Z - V (T (V^H Z)) over rows 1 .. N-1, Z rounded to FP32
+      float2 *Z = reinterpret_cast<float2 *>(ZG), *X = Z + N * m, *Y = Wf;  // W is done with, m <= N
+      for (int e = t; e < N * m; e += TPM) Z[e] = make_float2(float(X0[e % N * m + e / N]), 0.f);
+      wave_lds_sync();
+      for (int e = t; e < N * m; e += TPM) X[e] = product_c64<true>(Af + 1 + e % N * N, 1, Z + 1 + e / N * N, N - 1);
+      wave_lds_sync();
+      for (int e = t; e < N * m; e += TPM) Y[e] = product_c64<false>(Tf + e % N, N, X + e / N * N, N);
+      wave_lds_sync();
+      for (int e = t; e < N * m; e += TPM) {
+        const int r = e % N, c = e / N;
+        float2 z = Z[e];
+        if (r > 0) {
+          const float2 p = product_c64<false>(Af + r, N, Y + c * N, N);
+          z.x -= p.x;
+          z.y -= p.y;
+        }
+        if (live) U[q * sU + r + int64_t(c) * ldu] = bad ? OUT{NAN, NAN} : OUT{z.x, z.y};
+      }
     } else if (live) {
       typedef decltype(OUT{}.x) F;
       for (int e = t; e < N * m; e += TPM) {
@@ -345,13 +555,13 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(double2 *H, int64_t sH, 
   if (live && t == 0) status[q] = st;
 }
 
-template <int TPM, bool FULL, typename OUT>
-int launch_small(be_ctx *ctx, double2 *H, int64_t sH, int ld, const double *d, const double *e, int64_t sDE, int N,
+template <int TPM, SmallMode MODE, typename IN, typename OUT>
+int launch_small(be_ctx *ctx, IN *H, int64_t sH, int ld, const double *d, const double *e, int64_t sDE, int N,
                  int lo, int m, int64_t n_mat, double clu_rel, double tol_orth, double *evals, OUT *U, int ldu,
                  int64_t sU, uint32_t *status, hipStream_t stream) {
   constexpr int MPB = 64 / TPM;
-  const size_t lds = size_t(MPB) * small_doubles(N, m, FULL) * sizeof(double) + 16;
-  auto kern = &eigh_small_kernel<TPM, FULL, OUT>;
+  const size_t lds = size_t(MPB) * small_doubles(N, m, MODE) * sizeof(double) + 16;
+  auto kern = &eigh_small_kernel<TPM, MODE, IN, OUT>;
   hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>((n_mat + MPB - 1) / MPB)), dim3(64), lds, stream, H, sH, ld, d, e,
                      sDE, N, lo, m, n_mat, clu_rel, tol_orth, ctx->dbg_bisect_max_iter, evals, U, ldu, sU, status);
   return be::check_launch(ctx, "eigh_small");
@@ -364,19 +574,26 @@ namespace be {
 int eigh_small_fp64(be_ctx *ctx, double2 *H, int N, int ld, int64_t ms, int64_t n_mat, int lo, int hi, double *evals,
                     double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream, double clu_rel) {
   ProfScope prof(ctx, "eigh_small", stream);
-  auto go = N <= 8    ? &launch_small<8, true, double2>
-            : N <= 16 ? &launch_small<16, true, double2>
-                      : &launch_small<64, true, double2>;
+  auto go = N <= 8    ? &launch_small<8, kFull, double2, double2>
+            : N <= 16 ? &launch_small<16, kFull, double2, double2>
+                      : &launch_small<64, kFull, double2, double2>;
   return go(ctx, H, ms, ld, nullptr, nullptr, 0, N, lo, hi - lo, n_mat, clu_rel, 1e-14, evals, U, ldu, us, status, stream);
+}
+
+int eigh_small_c64(be_ctx *ctx, float2 *H, int N, int ld, int64_t ms, int64_t n_mat, int lo, int hi, double *evals,
+                   double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream, double clu_rel) {
+  ProfScope prof(ctx, "eigh_small_c64", stream);
+  auto go = N <= 8 ? &launch_small<8, kFullC64, float2, double2> : &launch_small<16, kFullC64, float2, double2>;
+  return go(ctx, H, ms, ld, nullptr, nullptr, 0, N, lo, hi - lo, n_mat, clu_rel, 2e-7, evals, U, ldu, us, status, stream);
 }
 
 int tri_small_c64(be_ctx *ctx, const double *d, const double *e, int N, int64_t n_mat, int lo, int hi, double *evals,
                   float2 *Z, int ldz, int64_t sz, uint32_t *status, hipStream_t stream, double clu_rel, double tol_orth) {
   ProfScope prof(ctx, "tri_small", stream);
-  auto go = N <= 8    ? &launch_small<8, false, float2>
-            : N <= 16 ? &launch_small<16, false, float2>
-                      : &launch_small<64, false, float2>;
-  return go(ctx, nullptr, 0, 0, d, e, N, N, lo, hi - lo, n_mat, clu_rel, tol_orth, evals, Z, ldz, sz, status, stream);
+  auto go = N <= 8    ? &launch_small<8, kTri, float2, float2>
+            : N <= 16 ? &launch_small<16, kTri, float2, float2>
+                      : &launch_small<64, kTri, float2, float2>;
+  return go(ctx, static_cast<float2 *>(nullptr), 0, 0, d, e, N, N, lo, hi - lo, n_mat, clu_rel, tol_orth, evals, Z, ldz, sz, status, stream);
 }
 
 }  // namespace be

@@ -59,3 +59,32 @@ def test_small_orders(N, lo, hi, n, degenerate, precision):
         if m and (not gaps or min(gaps) > 1e-3 * nrm):
             P = U[q] @ U[q].conj().T - V[:, lo:hi] @ V[:, lo:hi].conj().T
             assert np.abs(P).max() < bound[2] * (1 if not gaps else max(1.0, 0.05 * nrm / min(gaps)))
+
+
+# every order of the one-launch mixed solve and the next, whole window on the refined path (FP64 subspace: its tests' bounds)
+@pytest.mark.parametrize("precision", ["mixed", "refined"])
+@pytest.mark.parametrize("N", range(1, 18))
+def test_mixed_orders(N, precision):
+    gu.need_gpu()
+    from paper_2312_13051_amd import _lib as L
+    H, n, mixed = hermitian(9, N, 6, N % 2 == 0), 9, precision == "mixed"
+    lo, hi = (0, N) if mixed else (N // 4, N)
+    m, bound = hi - lo, 1e-5 if mixed else 1e-12
+    c = gu.ctx()
+    try:
+        dH = gu.from_np(H, N + 2, torch.complex64 if mixed else torch.complex128)
+        U = gu.colmajor(n, N, m, N + 1, fill=0)
+        ev = torch.empty((n, m + 2), dtype=torch.float64, device="cuda")
+        st = torch.full((n,), 77, dtype=torch.int32, device="cuda")
+        c.eigh_batched(dH, L.BE_C64 if mixed else L.BE_C128, N, N + 2, dH.stride(0), n, lo, hi,
+                       L.BE_MIXED_FP32 if mixed else L.BE_MIXED_FP32_REFINED, ev, U, N + 1, U.stride(0), st)
+        ev, U = ev.cpu().numpy(), gu.to_np(U, N)[:, :, :m]
+    finally:
+        c.close()
+    for q in range(n):
+        w = np.linalg.eigvalsh(H[q])
+        nrm = max(1.0, np.abs(w).max())
+        assert np.abs(ev[q, 1:m + 1] - w[lo:hi]).max() <= 2e-5 * nrm
+        assert np.abs(U[q].conj().T @ U[q] - np.eye(m)).max() < bound
+        if mixed:
+            assert np.abs(H[q] @ U[q] - U[q] * ev[q, 1:m + 1]).max() <= 1e-4 * nrm
