@@ -11,14 +11,16 @@
 // read-back. Bound by the latency of the serial recurrences (Sturm counts, one
 // lane per eigenvalue, and the columns of the reduction), hence as many matrices
 // per wave as have rows for its lanes. FP64, half the bands, general path ->
-// this one: order 4, 10,000 matrices 945 -> 62 us; 16, 4,096: 1,416 -> 158; 32,
-// 64: 604 -> 269, 8,192: 6,547 -> 1,837.
+// this one: order 4, 10,000 matrices 945 -> 50 us; 16, 4,096: 1,416 -> 126; 32,
+// 12, all bands: 247; 8,192: 6,547 -> 1,566. The Sturm counts read T from
+// registers (from LDS: 62, 158, 287 and 1,833 us).
 // Mixed path up to order 16, likewise: order 4, 52,500 matrices (a quarter of
 // the nested loops of 21 planes) 460 -> 123 us, of which the panel kernel took
-// 252 (a wave per matrix), three 16 x 16 products 87 and the copy to FP64 24.
+// 252 (a wave per matrix), three 16 x 16 products 87 and the copy to FP64 24;
+// 210,000: 360 -> 298 with the counts from registers.
 // Tridiagonal part alone, for orders 17 to 32 on the mixed path (reduction by
 // the panel kernel, FP32 products for the back-transformation): 32, 4,096:
-// 810 -> 377 us.
+// 810 -> 260 us.
 #include <algorithm>
 
 #include "common.hpp"
@@ -34,16 +36,26 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Sum and maximum over the TPM lanes of a matrix
 template <int TPM>
 __device__ __forceinline__ double grp_sum(double v) {
-#pragma unroll
-  for (int o = TPM / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  if constexpr (TPM > 16) {
+    v = fold<32>(v, v);
+    v = fold<16>(v, v);
+  }
+  if constexpr (TPM > 8) v += lane_xor<8>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<2>(v);
+  v += lane_xor<1>(v);
   return v;
 }
 template <int TPM>
 __device__ __forceinline__ double grp_max(double v) {
-#pragma unroll
-  for (int o = TPM / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  if constexpr (TPM > 16) v = fold_max<16>(fold_max<32>(v));
+  if constexpr (TPM > 8) v = fmax(v, lane_xor<8>(v));
+  v = fmax(v, lane_xor<4>(v));
+  v = fmax(v, lane_xor<2>(v));
+  v = fmax(v, lane_xor<1>(v));
   return v;
 }
 
@@ -57,12 +69,11 @@ enum SmallMode {
 // LDS of one matrix, in doubles: d, e, e^2 (N each), eigenvalues (m + 4),
 // block starts, group ids and marks (N + 1 + 2 m ints), X (N m), scratch for the
 // elimination's diagonals and the Gram matrix or, later, U (2 (N + 1) m), and
-// in FP64 the matrix, v, w and tau (N N + 3 N complex), otherwise the scaled
-// pairs of the Sturm counts (2 N), which in FP64 lie where w was; kFullC64 adds
-// the matrix, W and T (N N each) and four vectors in c64.
+// with kFull the matrix, v, w and tau (N N + 3 N complex), with kFullC64 the
+// matrix, W and T (N N each) and four vectors in c64.
 __host__ __device__ inline int small_doubles(int N, int m, SmallMode mode) {
   const int d = 3 * N + (m + 4) + (2 * m + N + 2) / 2 + N * m + 2 * (N + 1) * m;
-  const int c = mode == kFull ? 2 * (N * N + 3 * N) : 2 * N + (mode == kFullC64 ? 3 * N * N + 4 * N : 0);
+  const int c = mode == kFull ? 2 * (N * N + 3 * N) : mode == kFullC64 ? 3 * N * N + 4 * N : 0;
   return (d + 1 + c) & ~1;  // even: the complex part is 16-byte aligned
 }
 
@@ -233,7 +244,8 @@ __device__ __forceinline__ float2 product_c64(const float2 *a, int sa, const flo
   return make_float2(rr - ii, x - rr - ii);
 }
 
-template <int TPM, SmallMode MODE, typename IN, typename OUT>
+// TPM lanes per matrix of order N <= NM
+template <int TPM, int NM, SmallMode MODE, typename IN, typename OUT>
 __global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int ld, const double *dg,
                                                         const double *eg, int64_t sDE, int N, int lo, int m,
                                                         int64_t n_mat, double clu_rel, double tol_orth, int max_it,
@@ -248,8 +260,7 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int l
   double *base = reinterpret_cast<double *>(sm2) + (lane / TPM) * per;
   double2 *A = reinterpret_cast<double2 *>(base);  // kFull: N x N, then v, w, tau (N each)
   double2 *sv = A + (FULL ? N * N : 0), *sw = sv + (FULL ? N : 0), *stau = sw + (FULL ? N : 0);
-  double2 *sde = FULL ? sw : stau;  // w is done with when the counts begin
-  float2 *Af = reinterpret_cast<float2 *>(sde + N), *Wf = Af + N * N, *Tf = Wf + N * N;  // kFullC64
+  float2 *Af = reinterpret_cast<float2 *>(base), *Wf = Af + N * N, *Tf = Wf + N * N;  // kFullC64
   double *sd = FULL ? reinterpret_cast<double *>(stau + N)
                     : reinterpret_cast<double *>(MODE == kFullC64 ? Tf + N * N + 4 * N : Af), *se = sd + N, *se2 = se + N, *slam = se2 + N;
   double *X0 = slam + m + 4, *ZG = X0 + N * m;
@@ -375,10 +386,10 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int l
   emax2 = grp_max<TPM>(emax2);
   const double tnorm = fmax(fabs(gl), fabs(gu)), pivmin = DBL_MIN * fmax(1.0, emax2);
   const double sc = sturm_scale(tnorm), isc = 1.0 / sc, tn = tnorm * sc;
-  for (int i = t; i < N; i += TPM) {
-    sde[i] = make_double2(sd[i] * sc, fmax(i > 0 ? se2[i - 1] * sc * sc : 0.0, kSturmE2));
-  }
-  wave_lds_sync();
+  double2 de[NM];  // the scaled pairs, every lane of the matrix all of them
+#pragma unroll
+  for (int i = 0; i < NM; ++i)
+    de[i] = i < N ? make_double2(sd[i] * sc, fmax(i > 0 ? se2[i - 1] * sc * sc : 0.0, kSturmE2)) : sturm_pad();
   gl = gl * sc - 2.0 * eps * tn - DBL_MIN;
   gu = gu * sc + 2.0 * eps * tn + DBL_MIN;
   const double tol_abs = eps * eps * tn;
@@ -393,7 +404,7 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int l
         const double mid = 0.5 * (a + b);
         conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + DBL_MIN, tol_abs) || mid <= a || mid >= b;
         if (conv || it == max_it) break;
-        if ((FULL || b - a > kQuotientWidth ? sturm_count_p(sde, N, mid) : sturm_count_i(sde, N, mid)) > k) b = mid;
+        if ((FULL || b - a > kQuotientWidth ? sturm_count_p(de, mid) : sturm_count_i(de, mid)) > k) b = mid;
         else a = mid;
       }
       if (!conv) st |= BE_ST_NONCONVERGED;
@@ -555,13 +566,13 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int l
   if (live && t == 0) status[q] = st;
 }
 
-template <int TPM, SmallMode MODE, typename IN, typename OUT>
+template <int TPM, int NM, SmallMode MODE, typename IN, typename OUT>
 int launch_small(be_ctx *ctx, IN *H, int64_t sH, int ld, const double *d, const double *e, int64_t sDE, int N,
                  int lo, int m, int64_t n_mat, double clu_rel, double tol_orth, double *evals, OUT *U, int ldu,
                  int64_t sU, uint32_t *status, hipStream_t stream) {
   constexpr int MPB = 64 / TPM;
   const size_t lds = size_t(MPB) * small_doubles(N, m, MODE) * sizeof(double) + 16;
-  auto kern = &eigh_small_kernel<TPM, MODE, IN, OUT>;
+  auto kern = &eigh_small_kernel<TPM, NM, MODE, IN, OUT>;
   hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>((n_mat + MPB - 1) / MPB)), dim3(64), lds, stream, H, sH, ld, d, e,
                      sDE, N, lo, m, n_mat, clu_rel, tol_orth, ctx->dbg_bisect_max_iter, evals, U, ldu, sU, status);
   return be::check_launch(ctx, "eigh_small");
@@ -574,25 +585,29 @@ namespace be {
 int eigh_small_fp64(be_ctx *ctx, double2 *H, int N, int ld, int64_t ms, int64_t n_mat, int lo, int hi, double *evals,
                     double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream, double clu_rel) {
   ProfScope prof(ctx, "eigh_small", stream);
-  auto go = N <= 8    ? &launch_small<8, kFull, double2, double2>
-            : N <= 16 ? &launch_small<16, kFull, double2, double2>
-                      : &launch_small<64, kFull, double2, double2>;
+  auto go = N <= 4    ? &launch_small<8, 4, kFull, double2, double2>
+            : N <= 8  ? &launch_small<8, 8, kFull, double2, double2>
+            : N <= 16 ? &launch_small<16, 16, kFull, double2, double2>
+                      : &launch_small<64, 32, kFull, double2, double2>;
   return go(ctx, H, ms, ld, nullptr, nullptr, 0, N, lo, hi - lo, n_mat, clu_rel, 1e-14, evals, U, ldu, us, status, stream);
 }
 
 int eigh_small_c64(be_ctx *ctx, float2 *H, int N, int ld, int64_t ms, int64_t n_mat, int lo, int hi, double *evals,
                    double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream, double clu_rel) {
   ProfScope prof(ctx, "eigh_small_c64", stream);
-  auto go = N <= 8 ? &launch_small<8, kFullC64, float2, double2> : &launch_small<16, kFullC64, float2, double2>;
+  auto go = N <= 4   ? &launch_small<8, 4, kFullC64, float2, double2>
+            : N <= 8 ? &launch_small<8, 8, kFullC64, float2, double2>
+                     : &launch_small<16, 16, kFullC64, float2, double2>;
   return go(ctx, H, ms, ld, nullptr, nullptr, 0, N, lo, hi - lo, n_mat, clu_rel, 2e-7, evals, U, ldu, us, status, stream);
 }
 
 int tri_small_c64(be_ctx *ctx, const double *d, const double *e, int N, int64_t n_mat, int lo, int hi, double *evals,
                   float2 *Z, int ldz, int64_t sz, uint32_t *status, hipStream_t stream, double clu_rel, double tol_orth) {
   ProfScope prof(ctx, "tri_small", stream);
-  auto go = N <= 8    ? &launch_small<8, kTri, float2, float2>
-            : N <= 16 ? &launch_small<16, kTri, float2, float2>
-                      : &launch_small<64, kTri, float2, float2>;
+  auto go = N <= 4    ? &launch_small<8, 4, kTri, float2, float2>
+            : N <= 8  ? &launch_small<8, 8, kTri, float2, float2>
+            : N <= 16 ? &launch_small<16, 16, kTri, float2, float2>
+                      : &launch_small<64, 32, kTri, float2, float2>;
   return go(ctx, static_cast<float2 *>(nullptr), 0, 0, d, e, N, N, lo, hi - lo, n_mat, clu_rel, tol_orth, evals, Z, ldz, sz, status, stream);
 }
 

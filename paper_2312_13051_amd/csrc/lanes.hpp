@@ -51,6 +51,14 @@ __device__ __forceinline__ double fold(double a, double b) {
   return __hiloint2double(int(h.x), int(l.x)) + __hiloint2double(int(h.y), int(l.y));
 }
 
+// max(v of L, v of L ^ O), O = 32 or 16
+template <int O>
+__device__ __forceinline__ double fold_max(double v) {
+  const uint2 l = lane_swap<O>(uint32_t(__double2loint(v)), uint32_t(__double2loint(v)));
+  const uint2 h = lane_swap<O>(uint32_t(__double2hiint(v)), uint32_t(__double2hiint(v)));
+  return fmax(__hiloint2double(int(h.x), int(l.x)), __hiloint2double(int(h.y), int(l.y)));
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
   v = fold<32>(v, v);

@@ -50,31 +50,54 @@ __device__ __forceinline__ int sturm_count(const double *sd, const double *se2, 
 // 1.35, 120 of order 64 181 -> 113 us (two counts at once in a thread, with half
 // the waves: 191 us and 5.94 ms).
 constexpr double kSturmE2 = 1e-36;  // (1e-18 ||T||)^2, below the rounding of T
-__device__ __forceinline__ int sturm_count_p(const double2 *de, int N, double x) {
-  double p0 = 1.0, p1 = de[0].x - x;
-  uint32_t s1 = uint32_t(__double2hiint(p1)), cnt = s1 >> 31;
-  auto step = [&](double2 v) {
+struct SturmMinors {
+  double x, p0, p1;
+  uint32_t s1, cnt;
+  __device__ __forceinline__ SturmMinors(double d0, double xx) : x(xx), p0(1.0), p1(d0 - xx) {
+    s1 = uint32_t(__double2hiint(p1));
+    cnt = s1 >> 31;
+  }
+  __device__ __forceinline__ void step(double2 v) {
     const double pn = fma(v.x - x, p1, -(v.y * p0));
     const uint32_t sn = uint32_t(__double2hiint(pn));
     cnt += (sn ^ s1) >> 31;
     p0 = p1;
     p1 = pn;
     s1 = sn;
-  };
+  }
+  __device__ __forceinline__ void rescale() {
+    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
+    p0 = __builtin_amdgcn_ldexp(p0, ex);
+    p1 = __builtin_amdgcn_ldexp(p1, ex);
+  }
+};
+__device__ __forceinline__ int sturm_count_p(const double2 *de, int N, double x) {
+  SturmMinors s(de[0].x, x);
   int i = 1;
   for (; i + 8 <= N; i += 8) {
     double2 v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) v[u] = de[i + u];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) step(v[u]);
-    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
-    p0 = __builtin_amdgcn_ldexp(p0, ex);
-    p1 = __builtin_amdgcn_ldexp(p1, ex);
+    for (int u = 0; u < 8; ++u) s.step(v[u]);
+    s.rescale();
   }
-  for (; i < N; ++i) step(de[i]);
-  return int(cnt);
+  for (; i < N; ++i) s.step(de[i]);
+  return int(s.cnt);
 }
+// with the pairs in registers (rows past N as sturm_pad)
+template <int NM>
+__device__ __forceinline__ int sturm_count_p(const double2 (&de)[NM], double x) {
+  SturmMinors s(de[0].x, x);
+#pragma unroll
+  for (int i = 1; i < NM; ++i) {
+    s.step(de[i]);
+    if (i % 8 == 0) s.rescale();
+  }
+  return int(s.cnt);
+}
+// A row with an eigenvalue past every x that is counted at (|x| <= 1 + rounding)
+__device__ __forceinline__ double2 sturm_pad() { return make_double2(2.0, kSturmE2); }
 
 // The quotients' count from the same pairs, four steps' reads issued together.
 __device__ __forceinline__ int sturm_count_i(const double2 *de, int N, double x) {
@@ -86,6 +109,20 @@ __device__ __forceinline__ int sturm_count_i(const double2 *de, int N, double x)
   for (int i = 1; i < N; ++i) {
     const double2 v = de[i];
     qv = (v.x - x) - div_nr(v.y, qv);
+    if (fabs(qv) < DBL_MIN) qv = -DBL_MIN;
+    cnt += qv < 0.0;
+  }
+  return cnt;
+}
+
+template <int NM>
+__device__ __forceinline__ int sturm_count_i(const double2 (&de)[NM], double x) {
+  double qv = de[0].x - x;
+  if (fabs(qv) < DBL_MIN) qv = -DBL_MIN;
+  int cnt = qv < 0.0;
+#pragma unroll
+  for (int i = 1; i < NM; ++i) {
+    qv = (de[i].x - x) - div_nr(de[i].y, qv);
     if (fabs(qv) < DBL_MIN) qv = -DBL_MIN;
     cnt += qv < 0.0;
   }
@@ -151,6 +188,8 @@ __device__ __forceinline__ InvitBlock invit_block(const double *sd, const double
   while (c0 > 0 && lam[c0] - lam[c0 - 1] <= dclu) --c0;
   while (c1 < m && lam[c1] - lam[c1 - 1] <= dclu) ++c1;
   const double wlo = lam[c0] - dblk, whi = lam[c1 - 1] + dblk;
+  if (nblk == 1 && c1 - c0 == 1)  // the window holds this eigenvalue and no other
+    return InvitBlock{c0, 0, N, true, false, lam[c]};
   const int jr = c - c0;
   int bs = 0, bt = N, cnt = 0;
   bool found = false, shared = false;
