@@ -72,9 +72,38 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // ---------------------------------------------------------------- small kernels
-__global__ void k_zero_u32(uint32_t *p, int64_t n) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+// A call's flags and outputs before its first step, in one launch (4 to 5 us
+// each on the host, as much as most steps of a small call): zeros, NaN, zeros.
+// With the flags OR-ed by the kernels that end a call and phases and sectors
+// taken where they are first needed: Wilson loop of 1 band on 64 x 64 points
+// 181 -> 162 us, nested loop on 100 x 100 points 225 -> 203.
+struct ClearList {
+  uint32_t *u[3];
+  int64_t nu[3];
+  double *nan[2];
+  int64_t nnan[2];
+  int32_t *z[2];
+  int64_t nz[2];
+};
+__global__ void k_clear(ClearList l) {
+  const int64_t t0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x, nt = int64_t(gridDim.x) * blockDim.x;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    for (int64_t i = t0; i < l.nu[a]; i += nt) l.u[a][i] = 0;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+    for (int64_t i = t0; i < l.nnan[a]; i += nt) l.nan[a][i] = NAN;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+    for (int64_t i = t0; i < l.nz[a]; i += nt) l.z[a][i] = 0;
+}
+int clear(be_ctx *ctx, const ClearList &l, hipStream_t stream) {
+  int64_t n = 1;
+  for (int a = 0; a < 3; ++a) n = std::max(n, l.nu[a]);
+  for (int a = 0; a < 2; ++a) n = std::max({n, l.nnan[a], l.nz[a]});
+  hipLaunchKernelGGL(k_clear, dim3(static_cast<uint32_t>(std::min<int64_t>((n + 255) / 256, 4096))), dim3(256), 0, stream,
+                     l);
+  return be::check_launch(ctx, "clear");
 }
 
 // Newton-Schulz polar iteration with a state per matrix (act): 1 iterating,
@@ -205,7 +234,8 @@ __host__ __device__ inline bool small_loop_fits(int N, int m, int n_loop) {
 
 template <int P>
 __global__ __launch_bounds__(kSmallThreads) void k_small_loop(Grid U, int N, int m, int n_loop, int polar,
-                                                              double2 *Fout, double2 *W, uint32_t *line_st) {
+                                                              double2 *Fout, double2 *W, double *theta, int ldt,
+                                                              double *theta_raw, double2 *Z, uint32_t *line_st) {
   extern __shared__ double2 sL[];  // the line's factors (n_loop x m*m), then 2 m*m entries per group
   constexpr int NG = kSmallThreads / P;
   const int64_t line = blockIdx.x;
@@ -269,26 +299,27 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_loop(Grid U, int N, int
     }
     __syncthreads();
   }
-  if (tid < mm) W[line * mm + tid] = sL[tid];
-}
-
-// Phases of 1 x 1 Wilson matrices (and their trivial eigenvectors).
-__global__ void k_phase_1(const double2 *W, int64_t n_lines, double *theta, int ldt, double *theta_raw, double2 *Z) {
-  const int64_t l = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (l >= n_lines) return;
-  const double th = arg_pi(W[l]);
-  theta[l * ldt] = th;
-  if (theta_raw) theta_raw[l] = th;
-  if (Z) Z[l] = make_double2(1.0, 0.0);
+  if (P == 1 && theta) {  // one band: the phase and the trivial eigenvector
+    if (tid == 0) {
+      const double th = arg_pi(sL[0]);
+      theta[line * ldt] = th;
+      if (theta_raw) theta_raw[line] = th;
+      if (Z) Z[line] = make_double2(1.0, 0.0);
+    }
+  } else if (tid < mm) {
+    W[line * mm + tid] = sL[tid];
+  }
 }
 
 // Carries the Wannier sector of a line along its loop, nu_{j+1} = F_j nu_j,
 // for m <= 8: one wave per line, a lane per element of nu (m x sc), which
 // takes its row of F_j from memory PF links ahead and the other elements by
 // lane permutes. A batched product per link takes n_par - 1 launches of 6 us
-// each, 0.72 ms for 100 links whatever the number of lines.
+// each, 0.72 ms for 100 links whatever the number of lines. The sector at the
+// first point is columns of Z (as k_gather_sector takes them).
 template <int M>
-__global__ __launch_bounds__(64) void k_transport_small(const double2 *F, double2 *nu, int m, int sc, int n_par) {
+__global__ __launch_bounds__(64) void k_transport_small(const double2 *F, const double2 *Z, const double *theta_raw,
+                                                        double lo, double hi, double2 *nu, int m, int sc, int n_par) {
   constexpr int PF = 4;
   const int64_t line = blockIdx.x;
   const int lane = threadIdx.x, r = lane % m, c = lane / m;
@@ -296,7 +327,12 @@ __global__ __launch_bounds__(64) void k_transport_small(const double2 *F, double
   const int64_t mm = int64_t(m) * m, nus = int64_t(m) * sc;
   const double2 *Fl = F + line * n_par * mm;
   double2 *nl = nu + line * n_par * nus;
-  double2 x = own ? nl[r + int64_t(c) * m] : make_double2(0.0, 0.0);
+  double2 x = make_double2(0.0, 0.0);
+  for (int n = 0, col = 0; n < m; ++n) {
+    const double y = theta_raw[line * m + n] / TWO_PI;
+    if (y > lo && y < hi && col++ == c && own) x = Z[line * mm + r + int64_t(n) * m];
+  }
+  if (own) nl[r + int64_t(c) * m] = x;
   for (int j0 = 0; j0 + 1 < n_par; j0 += PF) {
     double2 f[PF][M];
 #pragma unroll
@@ -1004,13 +1040,24 @@ __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uin
   if (tid == 0) fb[q] = s_bad;
 }
 
+// OR of a system's line flags, in every lane of its wave
+__device__ __forceinline__ uint32_t or_lines(const uint32_t *line_st, int n) {
+  uint32_t v = 0;
+  for (int i = threadIdx.x & 63; i < n; i += 64) v |= line_st[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v |= uint32_t(__shfl_xor(int(v), o, 64));
+  return v;
+}
+
 // Chern winding of each system from theta [line][ldt] (first m valid): one
 // wave per system, a lane per transverse line (one thread per system waited
-// out a memory access per phase: 118 us for 32 lines of 48 phases).
+// out a memory access per phase: 118 us for 32 lines of 48 phases). The
+// lines' flags are OR-ed into the system's.
 __global__ __launch_bounds__(64) void k_winding(const double *theta, int ldt, int m, int n_sys, int n_perp, double *phi,
-                                                int32_t *winding, uint32_t *status) {
+                                                int32_t *winding, const uint32_t *line_st, uint32_t *status) {
   const int s = blockIdx.x, lane = threadIdx.x;
   if (s >= n_sys) return;
+  const uint32_t flags = or_lines(line_st + int64_t(s) * n_perp, n_perp);
   auto phase_sum = [&](int i) {
     double acc = 0.0;
     const double *th = theta + (int64_t(s) * n_perp + i) * ldt;
@@ -1052,15 +1099,7 @@ __global__ __launch_bounds__(64) void k_winding(const double *theta, int ldt, in
   const double c = total / TWO_PI;
   const int ci = int(rint(c));
   winding[s] = ci;
-  if (dmax > 0.8 * M_PI || fabs(c - ci) > 1e-6) atomicOr(&status[s], BE_ST_WINDING_UNRESOLVED);
-}
-
-// OR line flags into system flags
-__global__ void k_or_lines(const uint32_t *line_st, int64_t n_lines, int per_sys, uint32_t *sys_st) {
-  int64_t line = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (line >= n_lines) return;
-  uint32_t v = line_st[line];
-  if (v) atomicOr(&sys_st[line / per_sys], v);
+  status[s] |= flags | (dmax > 0.8 * M_PI || fabs(c - ci) > 1e-6 ? uint32_t(BE_ST_WINDING_UNRESOLVED) : 0u);
 }
 
 }  // namespace
@@ -1087,21 +1126,13 @@ static int small_loop(be_ctx *ctx, Grid U, int N, int m, int64_t n_lines, int n_
     const int P = m == 1 ? 1 : m == 2 ? 4 : m <= 4 ? 16 : 64;
     const size_t sm = size_t(n_loop * mm + 2 * (kSmallThreads / P) * mm) * sizeof(double2);
     const int polar = mode == BE_OVL_POLAR;
-    if (P == 1) hipLaunchKernelGGL(k_small_loop<1>, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, line_status);
-    if (P == 4) hipLaunchKernelGGL(k_small_loop<4>, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, line_status);
-    if (P == 16)
-      hipLaunchKernelGGL(k_small_loop<16>, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, line_status);
-    if (P == 64)
-      hipLaunchKernelGGL(k_small_loop<64>, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, line_status);
+    auto kern = P == 1 ? &k_small_loop<1> : P == 4 ? &k_small_loop<4> : P == 16 ? &k_small_loop<16> : &k_small_loop<64>;
+    hipLaunchKernelGGL(kern, grid, block, sm, stream, U, N, m, n_loop, polar, F, W, Wout ? nullptr : theta_sorted, ldt,
+                       theta_raw, Zout, line_status);
     BE_RET_IF(check_launch(ctx, "small_loop"));
   }
   if (Fkeep) *Fkeep = F;
-  if (Wout) return BE_OK;
-  if (m == 1) {
-    hipLaunchKernelGGL(k_phase_1, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, W, n_lines,
-                       theta_sorted, ldt, theta_raw, Zout);
-    return check_launch(ctx, "phase_1");
-  }
+  if (Wout || m == 1) return BE_OK;
   return unitary_phases(ctx, W, m, n_lines, Hs, Zout, theta_sorted, ldt, theta_raw, line_status, stream,
                         mode == BE_OVL_POLAR);
 }
@@ -1428,10 +1459,10 @@ extern "C" int be_wilson_loop(be_ctx *ctx, const void *U, int32_t N, int32_t m, 
   Carve cv;
   cv.add(&line_st, size_t(n_lines));
   BE_RET_IF(cv.commit(ctx, stream, WS_OUTER));
-  hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, line_st, n_lines);
-  hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<uint32_t>((n_sys + 255) / 256)), dim3(256), 0, stream, status,
-                     int64_t(n_sys));
-  BE_RET_IF(check_launch(ctx, "zero"));
+  ClearList cl{};
+  cl.u[0] = line_st, cl.nu[0] = n_lines;
+  cl.u[1] = status, cl.nu[1] = n_sys;
+  BE_RET_IF(clear(ctx, cl, stream));
   // lines in passes whose overlaps, polar and product buffers (three m x m
   // matrices per link) stay within about 4 GiB of workspace; with more than
   // one pass, each pass leaves its Wilson matrices and the eigenphases of all
@@ -1458,9 +1489,7 @@ extern "C" int be_wilson_loop(be_ctx *ctx, const void *U, int32_t N, int32_t m, 
     BE_RET_IF(unitary_phases(ctx, Wall, m, n_lines, Hs, nullptr, theta, m, nullptr, line_st, stream,
                              mode == BE_OVL_POLAR));
   }
-  hipLaunchKernelGGL(k_or_lines, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, line_st,
-                     n_lines, n_perp, status);
-  hipLaunchKernelGGL(k_winding, dim3(n_sys), dim3(64), 0, stream, theta, m, m, n_sys, n_perp, phi, winding,
+  hipLaunchKernelGGL(k_winding, dim3(n_sys), dim3(64), 0, stream, theta, m, m, n_sys, n_perp, phi, winding, line_st,
                      status);
   return check_launch(ctx, "winding");
 }
@@ -1468,33 +1497,33 @@ extern "C" int be_wilson_loop(be_ctx *ctx, const void *U, int32_t N, int32_t m, 
 // ---------------------------------------------------------------- nested Wilson loop
 namespace {
 
-// Per line: sector = columns n of Z with x = theta_raw/2pi in (lo, hi).
-// Writes s_line[line]; flags WANNIER_GAP if a phase is within 1e-6 of a window edge.
-__global__ void k_sector_count(const double *theta_raw, int m, int64_t n_lines, double lo, double hi, int32_t *s_line,
-                               uint32_t *line_st) {
-  int64_t line = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (line >= n_lines) return;
-  int s = 0;
-  bool edge = false;
-  for (int n = 0; n < m; ++n) {
-    double x = theta_raw[line * m + n] / TWO_PI;
-    if (x > lo && x < hi) ++s;
-    if (fabs(x - lo) < 1e-6 || fabs(x - hi) < 1e-6) edge = true;
-  }
-  s_line[line] = s;
-  if (edge) line_st[line] |= BE_ST_WANNIER_GAP;
-}
-
-// Per system (one wave): sector size of line 0; WANNIER_GAP if any line differs.
-__global__ __launch_bounds__(64) void k_sector_sys(const int32_t *s_line, int n_sys, int n_perp, int32_t *s_sys,
-                                                   uint32_t *status) {
+// Per system (one wave, a lane per line): sector = columns n of Z with x =
+// theta_raw / 2 pi in (lo, hi); its size on line 0. WANNIER_GAP if the size of
+// any line differs or a phase is within 1e-6 of a window edge; the lines' own
+// flags are OR-ed in.
+__global__ __launch_bounds__(64) void k_sector(const double *theta_raw, int m, int n_sys, int n_perp, double lo, double hi,
+                                               const uint32_t *line_st, int32_t *s_sys, uint32_t *status) {
   const int s = blockIdx.x;
   if (s >= n_sys) return;
-  const int s0 = s_line[int64_t(s) * n_perp];
-  bool differ = false;
-  for (int i = threadIdx.x; i < n_perp; i += 64) differ = differ || s_line[int64_t(s) * n_perp + i] != s0;
-  if (__any(differ) && threadIdx.x == 0) atomicOr(&status[s], BE_ST_WANNIER_GAP);
-  if (threadIdx.x == 0) s_sys[s] = s0;
+  int s0 = 0;
+  bool gap = false;
+  for (int i0 = 0; i0 < n_perp; i0 += 64) {
+    const int i = i0 + threadIdx.x;
+    const double *th = theta_raw + (int64_t(s) * n_perp + min(i, n_perp - 1)) * m;
+    int cnt = 0;
+#pragma unroll 8
+    for (int n = 0; n < m; ++n) {
+      const double x = th[n] / TWO_PI;
+      cnt += x > lo && x < hi;
+      gap = gap || fabs(x - lo) < 1e-6 || fabs(x - hi) < 1e-6;
+    }
+    if (i0 == 0) s0 = __shfl(cnt, 0, 64);
+    gap = gap || cnt != s0;
+  }
+  const uint32_t flags = or_lines(line_st + int64_t(s) * n_perp, n_perp) | (__any(gap) ? uint32_t(BE_ST_WANNIER_GAP) : 0u);
+  if (threadIdx.x != 0) return;
+  status[s] |= flags;
+  s_sys[s] = s0;
 }
 
 // nu[line][0] = Z_line[:, sector] (m x sc, ld m), in the order of the columns.
@@ -1516,11 +1545,13 @@ __global__ void k_gather_sector(const double2 *Z, const double *theta_raw, int m
 
 // p[s][j] and p_mean[s] from nested theta [s][j][ldt] (first sc valid): one
 // wave per system. With the wrapped steps d_j between neighbouring base
-// points, the mean of the unwrapped p is p_0 + sum_j d_j (n - j) / n.
+// points, the mean of the unwrapped p is p_0 + sum_j d_j (n - j) / n. The flags
+// of the nested loops are OR-ed into the system's.
 __global__ __launch_bounds__(64) void k_nested_p(const double *th, int ldt, int sc, int n_sys, int n_par, double *p,
-                                                 double *p_mean) {
+                                                 double *p_mean, const uint32_t *line_st, uint32_t *status) {
   const int s = blockIdx.x, lane = threadIdx.x;
   if (s >= n_sys) return;
+  const uint32_t flags = or_lines(line_st + int64_t(s) * n_par, n_par);
   double carry = 0.0, p0 = 0.0, sum = 0.0;
   for (int j0 = 0; j0 < n_par; j0 += 64) {
     const int j = j0 + lane;
@@ -1552,11 +1583,7 @@ __global__ __launch_bounds__(64) void k_nested_p(const double *th, int ldt, int 
   mean -= floor(mean);
   if (mean >= 1.0) mean -= 1.0;
   p_mean[s] = mean;
-}
-
-__global__ void k_fill_nan(double *p, int64_t n) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = NAN;
+  status[s] |= flags;
 }
 
 }  // namespace
@@ -1575,7 +1602,7 @@ extern "C" int be_nested_wilson(be_ctx *ctx, const void *U, int32_t N, int32_t m
   uint32_t *line_st = nullptr, *line_st2 = nullptr;
   double *th0 = nullptr, *thraw = nullptr;
   double2 *Z = nullptr, *nu = nullptr, *w = nullptr;
-  int32_t *s_line = nullptr, *s_sys = nullptr;
+  int32_t *s_sys = nullptr;
   Carve cv;
   cv.add(&line_st, size_t(n_lines));
   cv.add(&line_st2, size_t(int64_t(n_sys) * n_par));
@@ -1584,17 +1611,14 @@ extern "C" int be_nested_wilson(be_ctx *ctx, const void *U, int32_t N, int32_t m
   cv.add(&Z, size_t(n_lines * std::max<int64_t>(mm, 1)));
   cv.add(&nu, size_t(n_lines * n_par * std::max<int64_t>(mm, 1)));
   cv.add(&w, size_t(n_lines * n_par * int64_t(N) * std::max(m, 1)));
-  cv.add(&s_line, size_t(n_lines));
   cv.add(&s_sys, size_t(n_sys));
   BE_RET_IF(cv.commit(ctx, stream, WS_OUTER));
-  hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, line_st, n_lines);
-  hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<uint32_t>((n_sys * int64_t(n_par) + 255) / 256)), dim3(256), 0, stream,
-                     line_st2, int64_t(n_sys) * n_par);
-  hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<uint32_t>((n_sys + 255) / 256)), dim3(256), 0, stream, status,
-                     int64_t(n_sys));
-  hipLaunchKernelGGL(k_fill_nan, dim3(static_cast<uint32_t>((int64_t(n_sys) * n_par * std::max(m, 1) + 255) / 256)), dim3(256),
-                     0, stream, nested_theta, int64_t(n_sys) * n_par * std::max(m, 1));
-  BE_RET_IF(check_launch(ctx, "zero"));
+  ClearList cl{};
+  cl.u[0] = line_st, cl.nu[0] = n_lines;
+  cl.u[1] = line_st2, cl.nu[1] = int64_t(n_sys) * n_par;
+  cl.u[2] = status, cl.nu[2] = n_sys;
+  cl.nan[0] = nested_theta, cl.nnan[0] = int64_t(n_sys) * n_par * std::max(m, 1);
+  BE_RET_IF(clear(ctx, cl, stream));
   for (int s = 0; s < n_sys; ++s) s_out_h[s] = 0;
   if (m == 0) return BE_OK;
   // ---- first Wilson loop at base point 0 with eigenvectors; keep the overlaps
@@ -1602,11 +1626,8 @@ extern "C" int be_nested_wilson(be_ctx *ctx, const void *U, int32_t N, int32_t m
   const double2 *F = nullptr;
   BE_RET_IF(wilson_core(ctx, g, N, m, n_lines, n_par, mode, th0, m, Z, thraw, line_st, &F, stream));
   // ---- sector sizes
-  hipLaunchKernelGGL(k_sector_count, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, thraw, m,
-                     n_lines, win_lo, win_hi, s_line, line_st);
-  hipLaunchKernelGGL(k_or_lines, dim3(static_cast<uint32_t>((n_lines + 255) / 256)), dim3(256), 0, stream, line_st,
-                     n_lines, n_perp, status);
-  hipLaunchKernelGGL(k_sector_sys, dim3(n_sys), dim3(64), 0, stream, s_line, n_sys, n_perp, s_sys, status);
+  hipLaunchKernelGGL(k_sector, dim3(n_sys), dim3(64), 0, stream, thraw, m, n_sys, n_perp, win_lo, win_hi, line_st, s_sys,
+                     status);
   BE_RET_IF(check_launch(ctx, "sector"));
   int32_t *hs = static_cast<int32_t *>(ctx->pinned);
   BE_CHECK_ARG(ctx, n_sys <= 1024, "be_nested_wilson: at most 1024 systems per call");
@@ -1627,17 +1648,18 @@ extern "C" int be_nested_wilson(be_ctx *ctx, const void *U, int32_t N, int32_t m
     }
     const int64_t l0 = int64_t(s0) * n_perp, nl = int64_t(s1 - s0) * n_perp;
     const int64_t nus = int64_t(m) * sc;  // one nu block
-    hipLaunchKernelGGL(k_gather_sector, dim3(static_cast<uint32_t>(nl)), dim3(64), 0, stream, Z + l0 * mm, thraw + l0 * m, m,
-                       nl, win_lo, win_hi, sc, n_par, nu);
-    BE_RET_IF(check_launch(ctx, "gather_sector"));
+    if (m > kSmallM) {
+      hipLaunchKernelGGL(k_gather_sector, dim3(static_cast<uint32_t>(nl)), dim3(64), 0, stream, Z + l0 * mm, thraw + l0 * m,
+                         m, nl, win_lo, win_hi, sc, n_par, nu);
+      BE_RET_IF(check_launch(ctx, "gather_sector"));
+    }
     // transport nu[line][j+1] = F[line][j] nu[line][j]
     if (m <= kSmallM) {
       ProfScope prof(ctx, "transport", stream);
       const dim3 grid(static_cast<uint32_t>(nl)), block(64);
       const double2 *Fl = F + l0 * n_par * mm;
-      if (m <= 2) hipLaunchKernelGGL(k_transport_small<2>, grid, block, 0, stream, Fl, nu, m, sc, n_par);
-      else if (m <= 4) hipLaunchKernelGGL(k_transport_small<4>, grid, block, 0, stream, Fl, nu, m, sc, n_par);
-      else hipLaunchKernelGGL(k_transport_small<8>, grid, block, 0, stream, Fl, nu, m, sc, n_par);
+      auto kern = m <= 2 ? &k_transport_small<2> : m <= 4 ? &k_transport_small<4> : &k_transport_small<8>;
+      hipLaunchKernelGGL(kern, grid, block, 0, stream, Fl, Z + l0 * mm, thraw + l0 * m, win_lo, win_hi, nu, m, sc, n_par);
       BE_RET_IF(check_launch(ctx, "transport"));
     }
     for (int j = 0; m > kSmallM && j + 1 < n_par; ++j) {
@@ -1708,10 +1730,9 @@ extern "C" int be_nested_wilson(be_ctx *ctx, const void *U, int32_t N, int32_t m
     const int64_t nl2 = int64_t(s1 - s0) * n_par;
     BE_RET_IF(wilson_core(ctx, gw, N, sc, nl2, n_perp, mode, nested_theta + int64_t(s0) * n_par * m, m, nullptr, nullptr,
                           line_st2 + int64_t(s0) * n_par, nullptr, stream));
-    hipLaunchKernelGGL(k_or_lines, dim3(static_cast<uint32_t>((nl2 + 255) / 256)), dim3(256), 0, stream,
-                       line_st2 + int64_t(s0) * n_par, nl2, n_par, status + s0);
     hipLaunchKernelGGL(k_nested_p, dim3(s1 - s0), dim3(64), 0, stream, nested_theta + int64_t(s0) * n_par * m, m,
-                       sc, s1 - s0, n_par, p + int64_t(s0) * n_par, p_mean + s0);
+                       sc, s1 - s0, n_par, p + int64_t(s0) * n_par, p_mean + s0, line_st2 + int64_t(s0) * n_par,
+                       status + s0);
     BE_RET_IF(check_launch(ctx, "nested_p"));
     s0 = s1;
   }
@@ -1775,11 +1796,6 @@ __global__ void k_pso_expect(const int32_t *mdn, int n_sys, SectorSizes want, ui
 __global__ void k_spin_chern(const int32_t *cd, const int32_t *cu, int n, double *cs) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s < n) cs[s] = 0.5 * double(cu[s] - cd[s]);
-}
-
-__global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
 }
 
 }  // namespace
@@ -1899,23 +1915,21 @@ extern "C" int be_spin_resolved_wilson(be_ctx *ctx, const void *U, int32_t N, in
   cv.add(&cnt, size_t(n_k));
   cv.add(&mdn, size_t(n_sys));
   BE_RET_IF(cv.commit(ctx, stream, WS_OUTER));
-  hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<uint32_t>((n_sys + 255) / 256)), dim3(256), 0, stream, status,
-                     int64_t(n_sys));
-  hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<uint32_t>((2 * n_lines + 255) / 256)), dim3(256), 0, stream, lst,
-                     2 * n_lines);
-  BE_RET_IF(check_launch(ctx, "zero"));
+  ClearList cl{};
+  cl.u[0] = status, cl.nu[0] = n_sys;
+  cl.u[1] = lst, cl.nu[1] = 2 * n_lines;
+  BE_RET_IF(clear(ctx, cl, stream));
   if (!stream_capturing(stream))  // under capture m_dn_h holds the caller's sector sizes
     for (int s = 0; s < n_sys; ++s) m_dn_h[s] = 0;
   if (m == 0) return BE_OK;
   BE_RET_IF(spin_operator_eig(ctx, U, N, m, ldu, u_stride, n_sys, kps, precision, spin_diag, pso_evals, A32buf, A, Q, ev,
                               kst, cnt, mdn, m_dn_h, status, stream));
-  hipLaunchKernelGGL(k_fill_nan, dim3(static_cast<uint32_t>((n_lines * m + 255) / 256)), dim3(256), 0, stream, theta_dn,
-                     n_lines * m);
-  hipLaunchKernelGGL(k_fill_nan, dim3(static_cast<uint32_t>((n_lines * m + 255) / 256)), dim3(256), 0, stream, theta_up,
-                     n_lines * m);
-  hipLaunchKernelGGL(k_fill_i32, dim3((n_sys + 255) / 256), dim3(256), 0, stream, C_dn, int64_t(n_sys), 0);
-  hipLaunchKernelGGL(k_fill_i32, dim3((n_sys + 255) / 256), dim3(256), 0, stream, C_up, int64_t(n_sys), 0);
-  BE_RET_IF(check_launch(ctx, "fill"));
+  ClearList out{};
+  out.nan[0] = theta_dn, out.nnan[0] = n_lines * m;
+  out.nan[1] = theta_up, out.nnan[1] = n_lines * m;
+  out.z[0] = C_dn, out.nz[0] = n_sys;
+  out.z[1] = C_up, out.nz[1] = n_sys;
+  BE_RET_IF(clear(ctx, out, stream));
   // ---- V = U Q for all systems at once (columns in ascending mu: the first
   // m_dn_h[s] span the spin-down sector), then per run of systems with equal
   // sector sizes, the Wilson loop of each sector on its column slice of V
@@ -1951,10 +1965,8 @@ extern "C" int be_spin_resolved_wilson(be_ctx *ctx, const void *U, int32_t N, in
       double *th = (sector == 0 ? theta_dn : theta_up) + l0 * m;
       uint32_t *ls = lst + sector * n_lines + l0;
       BE_RET_IF(wilson_core(ctx, gv, N, ms, nl, n_par, mode, th, m, nullptr, nullptr, ls, nullptr, stream));
-      hipLaunchKernelGGL(k_or_lines, dim3(static_cast<uint32_t>((nl + 255) / 256)), dim3(256), 0, stream, ls, nl, n_perp,
-                         status + s0);
       hipLaunchKernelGGL(k_winding, dim3(s1 - s0), dim3(64), 0, stream, th, m, ms, s1 - s0, n_perp, nullptr,
-                         (sector == 0 ? C_dn : C_up) + s0, status + s0);
+                         (sector == 0 ? C_dn : C_up) + s0, ls, status + s0);
       BE_RET_IF(check_launch(ctx, "spin winding"));
     }
     s0 = s1;
@@ -1993,9 +2005,9 @@ extern "C" int be_spin_sectors(be_ctx *ctx, const void *U, int32_t N, int32_t m,
   cv.add(&cnt, size_t(n_k));
   cv.add(&mdn, size_t(n_sys));
   BE_RET_IF(cv.commit(ctx, stream, WS_OUTER));
-  hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<uint32_t>((n_sys + 255) / 256)), dim3(256), 0, stream, status,
-                     int64_t(n_sys));
-  BE_RET_IF(check_launch(ctx, "zero"));
+  ClearList cl{};
+  cl.u[0] = status, cl.nu[0] = n_sys;
+  BE_RET_IF(clear(ctx, cl, stream));
   if (!stream_capturing(stream))  // under capture m_dn_h holds the caller's sector sizes
     for (int s = 0; s < n_sys; ++s) m_dn_h[s] = 0;
   if (m == 0) return BE_OK;
