@@ -663,8 +663,7 @@ __global__ __launch_bounds__(PT) void tri_invit(const double *d, const double *e
 
 // Groups of vectors that share a block of T (inside a cluster of equal
 // eigenvalues; vectors in different blocks have disjoint supports and are
-// orthogonal already) are orthonormalized by Cholesky QR (two passes; one
-// for groups larger than GK)
+// orthogonal already) are orthonormalized by Cholesky QR, two passes
 // (G = V^T V = R^T R, V <- V R^-1), done in lanes: the groups are packed into
 // 64-lane bins (no group straddles a bin), a bin is one wave, vector c sits
 // on one lane, and the rows of X are swept with coalesced loads (the
@@ -672,15 +671,20 @@ __global__ __launch_bounds__(PT) void tri_invit(const double *d, const double *e
 // other members of a lane's group by cross-lane permutes; the first member of
 // each group factors G in LDS; an apply sweep solves y R = x row by row, the
 // members finalizing y in order and passing it on by permutes. Groups larger
-// than GK run one such pass with the whole workgroup; a breakdown of the
-// Cholesky factorization falls back to modified Gram-Schmidt with one wave
-// per group.
-constexpr int GK = 32;
+// than GK take the whole workgroup and the matrix cores, panel by panel; a
+// breakdown of the Cholesky factorization falls back to modified Gram-Schmidt
+// with one wave per group. Bound by the latency of a workgroup's dependent
+// steps, so loads are issued RA rows ahead; the line between the two lies where
+// a lane's share of its group stops fitting few registers (groups of up to 32
+// in lanes, larger ones by dot products from packed LDS: 2,304 projected spin
+// operators of order 200, clusters of 100, 15.5 ms; so 3.5).
+constexpr int GK = 8;         // largest group taken in lanes
+constexpr int GS_LDS = 8192;  // doubles: the lanes' Gram rows, or a panel's Gram parts, factor and S
 
-__host__ __device__ inline int gs_bins_max(int m) { return m / (64 - GK + 1) + 2; }
+__host__ __device__ inline int gs_bins_max(int m) { return m / 33 + 2; }
 
 size_t gs_smem(int m) {
-  return size_t(PT) * GK * sizeof(double) + size_t(std::max(m, 1)) * sizeof(double) +
+  return GS_LDS * sizeof(double) + size_t(std::max(m, 1)) * sizeof(double) +
          (3 * size_t(gs_bins_max(m)) * 64 + 2 * size_t(std::max(m, 1))) * sizeof(int);
 }
 
@@ -688,30 +692,33 @@ __global__ __launch_bounds__(PT) void tri_gs(int N, int m, const double *lamg, d
                                              const int *marks, double *Gm, double clu_rel, const uint32_t *status) {
   extern __shared__ double gsm[];
   const int nbmax = gs_bins_max(m);
-  int *sv = reinterpret_cast<int *>(gsm + PT * GK + m);  // bin lane -> vector (-1: idle)
+  int *sv = reinterpret_cast<int *>(gsm + GS_LDS + m);  // bin lane -> vector (-1: idle)
   int *sb = sv + nbmax * 64;                         // bin lane -> lane of its group's first member
   int *sk = sb + nbmax * 64;                         // bin lane -> group size
   int *sfl = sk + nbmax * 64;                        // group start -> Cholesky breakdown
-  int *mk_q = sfl + m;                               // group id per vector
-  double *lam = gsm + PT * GK;                       // selected eigenvalues (m)
-  __shared__ int s_nbins;
+  int *mk_q = sfl + m;                               // group id per vector, then the groups: start | size << 16
+  double *lam = gsm + GS_LDS;                        // selected eigenvalues (m)
+  __shared__ int s_nbins, s_ngrp;
   const int64_t q = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = PT / 64;
   if (status[q] & BE_ST_NAN_INF) return;
   const double dclu = tol_cluster(lamg[q * (m + 1)], clu_rel);
   double *X = Zs + q * sZ + int64_t(3) * N * mp;
+  int marked = 0;
   for (int c = tid; c < m; c += PT) {
     sfl[c] = 0;
     mk_q[c] = marks[q * m + c];
+    marked |= mk_q[c];
     lam[c] = lamg[q * (m + 1) + 1 + c];
   }
-  __syncthreads();
+  if (!__syncthreads_or(marked)) return;  // no two vectors share a block
   if (tid == 0) {
-    int nb = 0, fill = 0;
+    int nb = 0, fill = 0, ng = 0;
     for (int c0 = 0; c0 < m;) {
       const int c1 = group_end(lam, mk_q, m, c0, dclu);
       const int k = c1 - c0;
-      if (mk_q[c0] && k > 1 && k <= GK) {
+      if (k > 1) mk_q[ng++] = c0 | k << 16;  // ng <= c0: behind the marks still to be read
+      if (k > 1 && k <= GK) {
         if (fill + k > 64) {
           for (int l = fill; l < 64; ++l) sv[nb * 64 + l] = -1;
           ++nb;
@@ -731,10 +738,12 @@ __global__ __launch_bounds__(PT) void tri_gs(int N, int m, const double *lamg, d
       ++nb;
     }
     s_nbins = nb;
+    s_ngrp = ng;
   }
   __syncthreads();
   const int nbins = s_nbins;
   double *G = gsm + wave * 64 * GK;  // this wave's Gram rows, G[lane][t]
+  constexpr int RA = 8;              // rows loaded ahead
   for (int j0 = 0; j0 < nbins; j0 += nw) {
     const int j = j0 + wave;
     const int c = j < nbins ? sv[j * 64 + lane] : -1;
@@ -749,11 +758,17 @@ __global__ __launch_bounds__(PT) void tri_gs(int N, int m, const double *lamg, d
       double g[GK];
 #pragma unroll
       for (int t = 0; t < GK; ++t) g[t] = 0.0;
-      for (int i = 0; i < N; ++i) {
-        const double x = act ? X[int64_t(i) * mp + c] : 0.0;
+      for (int i0 = 0; i0 < N; i0 += RA) {
+        double xv[RA];
 #pragma unroll
-        for (int t = 0; t < GK; ++t)
-          if (t < kmax) g[t] = fma(x, __shfl(x, min(63, b + t), 64), g[t]);
+        for (int u = 0; u < RA; ++u) xv[u] = X[int64_t(min(i0 + u, N - 1)) * mp + max(c, 0)];
+#pragma unroll
+        for (int u = 0; u < RA; ++u) {
+          const double x = act && i0 + u < N ? xv[u] : 0.0;
+#pragma unroll
+          for (int t = 0; t < GK; ++t)
+            if (t < kmax) g[t] = fma(x, __shfl(x, min(63, b + t), 64), g[t]);
+        }
       }
 #pragma unroll
       for (int t = 0; t < GK; ++t) G[lane * GK + t] = g[t];
@@ -785,123 +800,147 @@ __global__ __launch_bounds__(PT) void tri_gs(int N, int m, const double *lamg, d
       for (int t = 0; t < GK; ++t) rcol[t] = (ok && t < rel) ? G[(b + t) * GK + rel] : 0.0;
       const double rinv = ok ? 1.0 / G[lane * GK + rel] : 0.0;
       // apply sweep: y R = x, row by row
-      for (int i = 0; i < N; ++i) {
-        const int64_t o = int64_t(i) * mp + (act ? c : 0);
-        const double x = act ? X[o] : 0.0;
-        double y = 0.0, acc = 0.0;
+      for (int i0 = 0; i0 < N; i0 += RA) {
+        double xv[RA];
 #pragma unroll
-        for (int t = 0; t < GK; ++t) {
-          if (t < kmax) {
-            if (rel == t) y = (x - acc) * rinv;
-            const double yt = __shfl(y, min(63, b + t), 64);
-            if (rel > t) acc = fma(yt, rcol[t], acc);
+        for (int u = 0; u < RA; ++u) xv[u] = X[int64_t(min(i0 + u, N - 1)) * mp + max(c, 0)];
+#pragma unroll
+        for (int u = 0; u < RA; ++u) {
+          const double x = act ? xv[u] : 0.0;
+          double y = 0.0, acc = 0.0;
+#pragma unroll
+          for (int t = 0; t < GK; ++t) {
+            if (t < kmax) {
+              if (rel == t) y = (x - acc) * rinv;
+              const double yt = __shfl(y, min(63, b + t), 64);
+              if (rel > t) acc = fma(yt, rcol[t], acc);
+            }
           }
+          if (ok && i0 + u < N) X[int64_t(i0 + u) * mp + c] = y;
         }
-        if (ok) X[o] = y;
       }
       __syncthreads();
     }
   }
-  // groups larger than GK: one Cholesky-QR pass by the whole workgroup (its
-  // O(cond^2 eps) loss of orthogonality is removed by the symmetric
-  // Newton-Schulz orthonormalization of all vectors that follows). The Gram
-  // matrix and its factor are kept packed (upper
-  // triangle, row by row) in LDS next to a tile of the cluster's rows when
-  // they fit (k(k+1)/2 + k <= PT*GK), else in the matrix's m x m scratch Gq.
-  // The Gram matrix is accumulated tile by tile, the factorization runs one
-  // column per step, R is inverted in place, and X_c R^-1 is formed from
-  // rows staged in the LDS tile, one (row, column) dot product per thread.
-  double *Gq = Gm + q * int64_t(m) * m;
-  for (int c0 = 0; c0 < m;) {
-    const int c1 = group_end(lam, mk_q, m, c0, dclu);
-    const int k = c1 - c0;
-    if (mk_q[c0] && k > GK) {
-      const int npk = k * (k + 1) / 2;
-      const bool in_lds = npk + k <= PT * GK;
-      double *Rp = in_lds ? gsm : Gq;              // packed upper triangle
-      double *tile = in_lds ? gsm + npk : gsm;     // rows of the group
-      const int RB = in_lds ? (PT * GK - npk) / k : (PT * GK) / k;
-      // packed index of (s, t), s <= t
-      auto pk = [k](int s2, int t) { return s2 * k - (s2 * (s2 - 1)) / 2 + (t - s2); };
-      for (int pass = 0; pass < 1 && !sfl[c0]; ++pass) {
-        __syncthreads();
-        for (int e = tid; e < npk; e += PT) Rp[e] = 0.0;
-        // Gram matrix, upper triangle, tile by tile (16 threads per row s2)
-        for (int i0 = 0; i0 < N; i0 += RB) {
-          const int nr = min(RB, N - i0);
-          __syncthreads();
-          for (int e = tid; e < nr * k; e += PT) {
-            const int r = e / k, col = e - r * k;
-            tile[e] = X[int64_t(i0 + r) * mp + c0 + col];
-          }
-          __syncthreads();
-          for (int s2 = tid >> 4; s2 < k; s2 += PT >> 4)
-            for (int t = s2 + (tid & 15); t < k; t += 16) {
-              double acc = 0.0;
-              for (int r = 0; r < nr; ++r) acc = fma(tile[r * k + s2], tile[r * k + t], acc);
-              Rp[pk(s2, t)] += acc;
+  // larger groups, by the whole workgroup in panels of 16 vectors on the matrix
+  // cores: P -= Q (Q^T P) with the group's finished vectors Q, then Cholesky QR
+  // of the panel (G = P^T P = R^T R, P <- P R^-1). One pass: its loss of
+  // orthogonality (condition number times eps, squared inside a panel) is
+  // removed by the symmetric Newton-Schulz orthonormalization of all vectors
+  // that follows. S = Q^T P is in LDS while it fits, else in the matrix's m x m
+  // scratch.
+  double *const Gw = gsm, *const R = gsm + nw * 256, *const rinv = R + 256, *const Sl = rinv + 16;
+  const int li = lane & 15, lk = lane >> 4, wv = __builtin_amdgcn_readfirstlane(wave);
+  const int nrt = (N + 15) / 16;  // row tiles
+  for (int gi = 0; gi < s_ngrp; ++gi) {
+    const int c0 = mk_q[gi] & 0xffff, k = mk_q[gi] >> 16, c1 = c0 + k;
+    if (k > GK) {
+      double *const S = k * 16 + nw * 256 + 272 <= GS_LDS ? Sl : Gm + q * int64_t(m) * m;
+      for (int b = 0; 16 * b < k && !sfl[c0]; ++b) {
+        const int cb = c0 + 16 * b, w = min(16, c1 - cb);
+        const double *const Q = X + c0;
+        double *const P = X + cb;
+        for (int t = wv; t < b; t += nw) {  // S tile t = Q_t^T P
+          v4d acc = {0, 0, 0, 0};
+          for (int i0 = 0; i0 < N; i0 += 4 * RA) {  // loads of RA steps in flight (clamped, masked after)
+            double qa[RA], pb[RA];
+#pragma unroll
+            for (int u = 0; u < RA; ++u) {
+              const int64_t o = int64_t(min(i0 + 4 * u + lk, N - 1)) * mp;
+              qa[u] = Q[o + 16 * t + li];
+              pb[u] = P[o + min(li, w - 1)];
             }
+#pragma unroll
+            for (int u = 0; u < RA; ++u)
+              acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[u], i0 + 4 * u + lk < N && li < w ? pb[u] : 0.0, acc, 0, 0, 0);
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) S[(16 * t + lk + 4 * r) * 16 + li] = acc[r];
         }
         __syncthreads();
-        // right-looking Cholesky, one column per step
-        for (int j = 0; j < k; ++j) {
-          if (tid == 0) {
-            const double dg = Rp[pk(j, j)];
-            if (!(dg > 1e-12) || !isfinite(dg)) sfl[c0] = 1;  // columns enter with unit norm
-            Rp[pk(j, j)] = sqrt(fmax(dg, DBL_MIN));
+        v4d g = {0, 0, 0, 0};  // this wave's part of P^T P
+        for (int rt = wv; rt < nrt; rt += nw) {
+          const double *const Qi = Q + int64_t(min(16 * rt + li, N - 1)) * mp + lk;
+          double x[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[r] = P[int64_t(min(16 * rt + lk + 4 * r, N - 1)) * mp + min(li, w - 1)];
+          v4d acc = {0, 0, 0, 0};
+          for (int s0 = 0; s0 < 16 * b; s0 += 16) {
+            double qa[4], sb2[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              qa[u] = Qi[s0 + 4 * u];
+              sb2[u] = S[(s0 + 4 * u + lk) * 16 + li];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[u], sb2[u], acc, 0, 0, 0);
           }
-          __syncthreads();
-          if (sfl[c0]) break;
-          const double rjj = Rp[pk(j, j)];
-          for (int t = j + 1 + tid; t < k; t += PT) Rp[pk(j, t)] /= rjj;
-          __syncthreads();
-          for (int s2 = j + 1 + (tid >> 4); s2 < k; s2 += PT >> 4) {
-            const double rs = Rp[pk(j, s2)];
-            for (int t = s2 + (tid & 15); t < k; t += 16) Rp[pk(s2, t)] -= rs * Rp[pk(j, t)];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {  // accumulator register r: row lk + 4 r, column li
+            const int i = 16 * rt + lk + 4 * r;
+            const bool ok = i < N && li < w;
+            x[r] = ok ? x[r] - acc[r] : 0.0;
+            if (ok && b > 0) P[int64_t(i) * mp + li] = x[r];
           }
-          __syncthreads();
+#pragma unroll
+          for (int r = 0; r < 4; ++r) g = __builtin_amdgcn_mfma_f64_16x16x4f64(x[r], x[r], g, 0, 0, 0);
         }
-        if (sfl[c0]) break;
-        // R^-1 in place, rows from the bottom: row i needs rows > i of R^-1
-        for (int i = k - 1; i >= 0; --i) {
-          const double rii = Rp[pk(i, i)];
-          for (int j = i + tid; j < k; j += PT) {
-            double v = j == i ? 1.0 : 0.0;
-            for (int p = i + 1; p <= j; ++p) v -= Rp[pk(i, p)] * Rp[pk(p, j)];
-            tile[j] = v / rii;
-          }
-          __syncthreads();
-          for (int j = i + tid; j < k; j += PT) Rp[pk(i, j)] = tile[j];
-          __syncthreads();
-        }
-        // X_c <- X_c R^-1: rows staged in LDS, independent (row, column) dot products
-        for (int i0 = 0; i0 < N; i0 += RB) {
-          const int nr = min(RB, N - i0);
-          __syncthreads();
-          for (int e = tid; e < nr * k; e += PT) {
-            const int r = e / k, col = e - r * k;
-            tile[e] = X[int64_t(i0 + r) * mp + c0 + col];
-          }
-          __syncthreads();
-          for (int e = tid; e < nr * k; e += PT) {
-            const int r = e / k, j = e - r * k;
-            const double *xr = tile + r * k;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Gw[wave * 256 + (lk + 4 * r) * 16 + li] = g[r];
+        __syncthreads();
+        if (wave == 0) {  // R (16 x 16, row by row) = Cholesky factor of the summed Gram matrix
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int e = (lk + 4 * r) * 16 + li;
             double v = 0.0;
-            for (int p = 0, ix = j; p <= j; ix += k - p - 1, ++p) v = fma(xr[p], Rp[ix], v);
-            X[int64_t(i0 + r) * mp + c0 + j] = v;
+            for (int u = 0; u < nw; ++u) v += Gw[u * 256 + e];
+            g[r] = v;
+          }
+          for (int j = 0; j < w; ++j) {
+            // row j of the Schur complement: register j / 4 of the lanes 16 (j % 4) + li
+            double row = 0.0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) row = r == j / 4 ? g[r] : row;
+            row = __shfl(row, 16 * (j & 3) + li, 64);
+            const double dg = __shfl(row, j, 64);
+            if (!(dg > 1e-12) || !isfinite(dg)) {  // columns enter with unit norm
+              if (lane == 0) sfl[c0] = 1;
+              break;
+            }
+            const double rjj = sqrt(dg), ri = 1.0 / rjj, rt = row * ri;
+            if (lane < 16) R[j * 16 + li] = li == j ? rjj : rt;
+            if (lane == 0) rinv[j] = ri;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) g[r] = fma(-__shfl(rt, lk + 4 * r, 64), rt, g[r]);
+          }
+        }
+        __syncthreads();
+        if (sfl[c0]) break;
+        for (int i = tid; i < N; i += PT) {  // y R = x, a row per thread
+          double x[16];
+          double *const Pi = P + int64_t(i) * mp;
+#pragma unroll
+          for (int t = 0; t < 16; ++t) x[t] = t < w ? Pi[t] : 0.0;
+#pragma unroll
+          for (int t = 0; t < 16; ++t) {
+            if (t < w) {
+              x[t] *= rinv[t];
+#pragma unroll
+              for (int u = t + 1; u < 16; ++u)
+                if (u < w) x[u] = fma(-x[t], R[t * 16 + u], x[u]);
+              Pi[t] = x[t];
+            }
           }
         }
         __syncthreads();
       }
     }
-    c0 = c1;
   }
   __syncthreads();
   // clusters left to the fallback: a Cholesky breakdown
-  for (int c0 = 0, w = 0; c0 < m;) {
-    const int c1 = group_end(lam, mk_q, m, c0, dclu);
-    const int k = c1 - c0;
-    if (mk_q[c0] && k > 1 && sfl[c0]) {
+  for (int gi = 0, w = 0; gi < s_ngrp; ++gi) {
+    const int c0 = mk_q[gi] & 0xffff, c1 = c0 + (mk_q[gi] >> 16);
+    if (sfl[c0]) {
       if (w++ % nw == wave) {
         for (int pass = 0; pass < 2; ++pass) {
           for (int t = c0; t < c1; ++t) {
@@ -926,7 +965,6 @@ __global__ __launch_bounds__(PT) void tri_gs(int N, int m, const double *lamg, d
         }
       }
     }
-    c0 = c1;
   }
 }
 
