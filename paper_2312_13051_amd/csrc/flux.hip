@@ -7,7 +7,7 @@
 // and across it (both periodic), det(U(k')^H U(k)):
 //   links    batched MFMA GEMMs U(k')^H U(k) (the across-direction batch runs
 //            with the transverse index innermost and cyclic),
-//   phases   k_det_phase: blocked LU with partial pivoting, one workgroup per link,
+//   phases   k_det_phase_r, k_det_phase: blocked LU with partial pivoting, one workgroup per link,
 //            arg det = sum of the pivots' arguments (+ pi per row swap),
 //            log |det| = sum of log |pivot|. A link is singular, its
 //            variable det/|det| undetermined, when its smallest singular
@@ -28,8 +28,10 @@
 #include <cmath>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "common.hpp"
+#include "lanes.hpp"
 
 namespace {
 
@@ -60,8 +62,7 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
 
 // Smallest singular value of an m x m matrix from its LU factors P M = L U,
 // stored in place (row-major rows of length m; unit lower L strictly below
-// the diagonal, U on and above it): logical row i of the factors is row
-// rowmap[i] of A, or row i when rowmap is null. Row interchanges do not
+// the diagonal, U on and above it). Row interchanges do not
 // change singular values, so sigma_min(M) = sigma_min(L U). Two steps of
 // inverse iteration on (LU)^{-1} (LU)^{-H} from a fixed start vector whose
 // entries have modulus one, then the Rayleigh quotient rq = |(LU)^{-H} x|^2
@@ -76,9 +77,9 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
 // the factors (coalesced); solves with L and U read columns.
 // x: m double2 of LDS, slot: 2 double2 of LDS, red: as for block_sum.
 template <int NT>
-__device__ double lu_smin(const double2 *A, int m, const int *rowmap, double2 *x, double2 *slot, double *red) {
+__device__ double lu_smin(const double2 *A, int m, double2 *x, double2 *slot, double *red) {
   const int tid = threadIdx.x;
-  auto rowp = [&](int i) { return A + int64_t(rowmap ? rowmap[i] : i) * m; };
+  auto rowp = [&](int i) { return A + int64_t(i) * m; };
   auto first_above = [&](int c) {  // smallest r > c owned by this thread
     int r = tid;
     if (r <= c) r += ((c - r) / NT + 1) * NT;
@@ -163,6 +164,36 @@ __device__ double lu_smin(const double2 *A, int m, const int *rowmap, double2 *x
     }
     __syncthreads();
   }
+}
+
+// Largest value of the lanes of a wave and its index (the smallest of equals)
+template <int O>
+__device__ __forceinline__ void best_step(double &best, int &bi) {
+  double ov = best;
+  int oi = bi;
+  if constexpr (O >= 16) {  // both halves' values in every lane
+    const uint2 l = lane_swap<O>(uint32_t(__double2loint(best)), uint32_t(__double2loint(best)));
+    const uint2 h = lane_swap<O>(uint32_t(__double2hiint(best)), uint32_t(__double2hiint(best)));
+    const uint2 i = lane_swap<O>(uint32_t(bi), uint32_t(bi));
+    best = __hiloint2double(int(h.x), int(l.x));
+    ov = __hiloint2double(int(h.y), int(l.y));
+    bi = int(i.x);
+    oi = int(i.y);
+  } else {
+    ov = lane_xor<O>(best);
+    oi = __float_as_int(lane_xor<O>(__int_as_float(bi)));
+  }
+  const bool take = ov > best || (ov == best && oi < bi);
+  best = take ? ov : best;
+  bi = take ? oi : bi;
+}
+__device__ __forceinline__ void lane_best(double &best, int &bi) {
+  best_step<32>(best, bi);
+  best_step<16>(best, bi);
+  best_step<8>(best, bi);
+  best_step<4>(best, bi);
+  best_step<2>(best, bi);
+  best_step<1>(best, bi);
 }
 
 // Singular-value certificate of a link from its LU: log |det| when that is at
@@ -366,163 +397,215 @@ __global__ __launch_bounds__(DT) void k_det_phase(double2 *A, int m, int64_t sA,
   __syncthreads();
   la = s_la;
   if (la < kLogSingular && la > -INFINITY) {
-    const double sg = lu_smin<DT>(M, m, nullptr, sP, sP + m, s_v);
+    const double sg = lu_smin<DT>(M, m, sP, sP + m, s_v);
     la = sg > 0.0 ? log(sg) : -INFINITY;
   }
   if (tid == 0) lsig[blockIdx.x] = la;
 }
 
-// The same factorization by one wave per link (orders up to 128), with the
-// row interchanges kept as a permutation in LDS instead of moving rows in
-// memory: the panel's rows are read through the permutation, the block row
-// of U is solved in registers by the lane that owns its column and applied
-// to the trailing rows at once, and no barrier waits for another wave. The
-// pivots, their arguments and moduli are those of the workgroup kernel.
-template <int NB>
-__global__ __launch_bounds__(64) void k_det_phase_w(double2 *A, int m, int64_t sA, double *phase, double *lsig) {
-  extern __shared__ double2 sP[];            // panel, column-major: sP[c * rows + r]
-  int *perm = reinterpret_cast<int *>(sP + int64_t(m) * NB);  // logical row -> physical row
+// The same factorization for orders up to NT: a thread per row of the panel,
+// which it holds in registers, so that a column costs two barriers, a search
+// over lanes by moves between them and one LDS read of the pivot row. The
+// panel's interchanges reach the other columns as one gather (all rows of a
+// column loaded before any is stored), and the trailing update runs on the
+// matrix cores: k_det_phase waited out a memory access per interchange and per
+// row, a single wave per link below order 128 besides. Bound by the latency of
+// the columns' steps. 400 links, a wave or a workgroup per link before -> now:
+// order 16 39 -> 25 us, 48 154 -> 91, 79 382 -> 188, 128 1,198 -> 376; 500 of
+// order 166 996 -> 637; 300 of order 256 2.42 -> 1.32 ms. lsig and phase as there (the sums over the
+// pivots in another order).
+template <int NT>
+__global__ __launch_bounds__(NT, 2) void k_det_phase_r(double2 *A, int m, int64_t sA, double *phase, double *lsig) {
+  constexpr int NB = 16, NW = NT / 64;
+  constexpr int LP = NB + 1;       // pitch: lanes that read a column of 16 rows meet different banks
+  extern __shared__ double2 sL[];  // factored panel, row by row: sL[r * LP + c]
+  __shared__ double2 s_row[2][NB];  // the pivot's row, the row it takes the place of
+  __shared__ double2 s_piv[NB];
+  __shared__ double s_v[NW];
+  __shared__ int s_i[NW], s_p[NB], s_src[NT];
   double2 *M = A + int64_t(blockIdx.x) * sA;  // M[r][c] = M[r * m + c]
-  const int lane = threadIdx.x;
-  double ph = 0.0, la = 0.0;
-  for (int r = lane; r < m; r += 64) perm[r] = r;
-  __syncthreads();
-  auto wave_best = [&](double best, int bi, double &ob, int &oi) {
-    for (int o = 32; o > 0; o >>= 1) {
-      const double v = __shfl_xor(best, o, 64);
-      const int i = __shfl_xor(bi, o, 64);
-      if (v > best || (v == best && i < bi)) {
-        best = v;
-        bi = i;
-      }
-    }
-    ob = best;
-    oi = bi;
-  };
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4, wv = __builtin_amdgcn_readfirstlane(wave);
+  double ph = 0.0, la = 0.0;  // lane c < NB: of the pivots of columns c, NB + c, ...
   for (int k0 = 0; k0 < m; k0 += NB) {
     const int nbp = min(NB, m - k0), rows = m - k0;
-    double best = -1.0;
-    int bi = 0;
-    // panel load through the permutation, pivot search of its first column
-    for (int e = lane; e < rows * nbp; e += 64) {
-      const int r = e / nbp, c = e - r * nbp;
-      const double2 v = M[int64_t(perm[k0 + r]) * m + k0 + c];
-      sP[c * rows + r] = v;
-      if (c == 0) {
-        const double a2 = v.x * v.x + v.y * v.y;
-        if (a2 > best || (a2 == best && r < bi)) {
-          best = a2;
-          bi = r;
-        }
-      }
-    }
-    double bv;
-    int p;
-    wave_best(best, bi, bv, p);
-    __syncthreads();
-    for (int c = 0; c < nbp; ++c) {
-      if (bv < 0.0) p = c;
-      if (p != c) {
-        for (int cc = lane; cc < nbp; cc += 64) {
-          const double2 t = sP[cc * rows + c];
-          sP[cc * rows + c] = sP[cc * rows + p];
-          sP[cc * rows + p] = t;
-        }
+    double2 x[NB];
+    unrolled<NB>([&](auto CC) {
+      constexpr int c = CC;
+      const double2 v = M[int64_t(k0 + min(tid, rows - 1)) * m + k0 + min(c, nbp - 1)];
+      x[c] = make_double2(c < nbp ? v.x : 0.0, c < nbp ? v.y : 0.0);
+    });
+    s_src[tid] = tid;
+    unrolled<NB>([&](auto CC) {
+      constexpr int c = CC;
+      if (c < nbp) {
+        // pivot: the largest |x_c| of rows c .., the first of equal ones (none: row c)
+        const double a2 = x[c].x * x[c].x + x[c].y * x[c].y;
+        double best = tid >= c && tid < rows && a2 > -1.0 ? a2 : -1.0;
+        int bi = tid;
+        lane_best(best, bi);
         if (lane == 0) {
-          const int t = perm[k0 + c];
-          perm[k0 + c] = perm[k0 + p];
-          perm[k0 + p] = t;
+          s_v[wave] = best;
+          s_i[wave] = bi;
         }
-      }
-      __syncthreads();
-      const double2 piv = sP[c * rows + c];
-      const double den = piv.x * piv.x + piv.y * piv.y;
-      ph += atan2(piv.y, piv.x) + (p != c ? kPi : 0.0);
-      la += 0.5 * log(den);
-      const double2 ipv = den > 0.0 ? make_double2(piv.x / den, -piv.y / den) : make_double2(0.0, 0.0);
-      best = -1.0;
-      bi = c + 1;
-      for (int r = c + 1 + lane; r < rows; r += 64) {
-        const double2 a = sP[c * rows + r];
-        const double2 l = make_double2(a.x * ipv.x - a.y * ipv.y, a.x * ipv.y + a.y * ipv.x);
-        sP[c * rows + r] = l;
-        for (int cc = c + 1; cc < nbp; ++cc) {
-          const double2 u = sP[cc * rows + c];
-          double2 x = sP[cc * rows + r];
-          x.x -= l.x * u.x - l.y * u.y;
-          x.y -= l.x * u.y + l.y * u.x;
-          sP[cc * rows + r] = x;
-          if (cc == c + 1) {
-            const double a2 = x.x * x.x + x.y * x.y;
-            if (a2 > best) {
-              best = a2;
-              bi = r;
-            }
+        __syncthreads();
+        best = s_v[0];
+        int p = s_i[0];
+        for (int w = 1; w < NW; ++w)
+          if (s_v[w] > best || (s_v[w] == best && s_i[w] < p)) {
+            best = s_v[w];
+            p = s_i[w];
           }
+        if (best < 0.0) p = c;
+        if (tid == p || tid == c) {  // (row c is the pivot's own where p = c)
+          double2 *const to = s_row[tid != p];
+          unrolled<NB>([&](auto D) { to[D] = x[D]; });
         }
+        if (tid == 0) {
+          s_p[c] = p;
+          const int t = s_src[c];
+          s_src[c] = s_src[p];
+          s_src[p] = t;
+        }
+        __syncthreads();
+        const bool swap = p != c && (tid == c || tid == p);
+        if (__any(swap)) {
+          const double2 *const from = s_row[tid == p];
+          unrolled<NB>([&](auto D) {
+            const double2 o = from[D];
+            x[D] = make_double2(swap ? o.x : x[D].x, swap ? o.y : x[D].y);
+          });
+        }
+        const double2 pv = s_row[0][c];
+        const double den = pv.x * pv.x + pv.y * pv.y;
+        if (tid == 0) s_piv[c] = pv;
+        const double2 ipv = den > 0.0 ? make_double2(pv.x / den, -pv.y / den) : make_double2(0.0, 0.0);
+        const double2 l0 = be::cmul(x[c], ipv);
+        const bool below = tid > c;  // rows up to c stay: their multiplier is zero
+        const double2 l = make_double2(below ? l0.x : 0.0, below ? l0.y : 0.0);
+        x[c] = make_double2(below ? l.x : x[c].x, below ? l.y : x[c].y);
+        unrolled<NB - 1 - c>([&](auto D) {
+          constexpr int cc = c + 1 + D;
+          x[cc] = be::csub(x[cc], be::cmul(l, s_row[0][cc]));
+        });
       }
-      wave_best(best, bi, bv, p);
-      __syncthreads();
+    });
+    // the factored panel to LDS (L11 and L21 of the steps below) and back to M
+    if (tid < rows)
+      unrolled<NB>([&](auto D) {
+        sL[tid * LP + D] = x[D];
+        if (D < nbp) M[int64_t(k0 + tid) * m + k0 + D] = x[D];
+      });
+    __syncthreads();
+    if (tid < nbp) {
+      const double2 pv = s_piv[tid];
+      ph += atan2(pv.y, pv.x) + (s_p[tid] != tid ? kPi : 0.0);
+      la += 0.5 * log(pv.x * pv.x + pv.y * pv.y);
     }
-    // the factored panel back to M (rows through the permutation), for sigma_min
-    for (int e = lane; e < rows * nbp; e += 64) {
-      const int r = e / nbp, c = e - r * nbp;
-      M[int64_t(perm[k0 + r]) * m + k0 + c] = sP[c * rows + r];
-    }
-    if (k0 + nbp >= m) break;
-    // block row of U (in registers, and stored) and trailing update, one lane per column
+    // interchanges of the other columns, a thread per column: the first nbp rows
+    // and the pivots' old rows change (a pivot from the first rows, or a column
+    // past the last panel's, stores what the rows' own stores then replace);
+    // right of the panel also U12 = L11^{-1} (P A12)
     const int j0 = k0 + nbp, C = m - j0;
-    for (int jb = 0; jb < C; jb += 64) {
-      const int j = j0 + jb + lane;
-      if (jb + lane < C) {
-        double2 u[NB];
+    auto interchange = [&](int j, auto solve) {
+      double2 u[NB];
+      double vx[NB], vy[NB];
+      unrolled<NB>([&](auto D) {  // the rows are the same in every thread: scalar addresses
+        const int cc = min(int(D), nbp - 1);
+        const int ru = __builtin_amdgcn_readfirstlane(s_src[cc]), rv = __builtin_amdgcn_readfirstlane(s_src[s_p[cc]]);
+        u[D] = (M + int64_t(k0 + ru) * m)[j];
+        const double2 v = (M + int64_t(k0 + rv) * m)[j];
+        vx[D] = v.x;
+        vy[D] = v.y;
+      });
+      unrolled<NB>([&](auto D) {
+        const int r = __builtin_amdgcn_readfirstlane(s_p[min(int(D), nbp - 1)]);
+        (M + int64_t(k0 + r) * m)[j] = make_double2(vx[D], vy[D]);
+      });
+      // L11 is read when the rows' registers are free again (read ahead of the
+      // stores it made registers spill)
+      __builtin_amdgcn_sched_barrier(0);
+      unrolled<NB>([&](auto D) {
+        constexpr int c = D;
+        if constexpr (c % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        double2 y = u[c];
+        if constexpr (decltype(solve)::value)
+          unrolled<c>([&](auto E) { y = be::csub(y, be::cmul(sL[c * LP + E], u[E])); });
+        u[c] = y;
+        (M + int64_t(k0 + min(c, nbp - 1)) * m)[j] = y;
+      });
+    };
+    for (int j = tid; j < k0; j += NT) interchange(j, std::false_type{});
+    for (int j = j0 + tid; j < m; j += NT) interchange(j, std::true_type{});
+    __syncthreads();
+    // trailing update M22 -= L21 U12 on the matrix cores (broadcasts of L21 to a
+    // lane per column kept the LDS busier than the FP64 units): a wave per
+    // 16 columns, whose U12 it holds
+    const int nct = (C + 15) / 16, nrt = (rows - nbp + 15) / 16;
+    for (int ct = wv; ct < nct; ct += NW) {
+      const int jc = 16 * ct + li, j = j0 + min(jc, C - 1);
+      double2 u[4];
 #pragma unroll
-        for (int c = 0; c < NB; ++c) {
-          if (c < nbp) {
-            double2 x = M[int64_t(perm[k0 + c]) * m + j];
+      for (int t = 0; t < 4; ++t) u[t] = M[int64_t(k0 + 4 * t + lk) * m + j];  // C > 0: nbp = NB
+      double2 *Mj = M + int64_t(j0) * m + j;
+      const int rmax = rows - nbp - 1;
+      double2 y[4];
 #pragma unroll
-            for (int cc = 0; cc < c; ++cc) {
-              const double2 l = sP[cc * rows + c];
-              x.x -= l.x * u[cc].x - l.y * u[cc].y;
-              x.y -= l.x * u[cc].y + l.y * u[cc].x;
-            }
-            u[c] = x;
-            M[int64_t(perm[k0 + c]) * m + j] = x;
-          } else {
-            u[c] = make_double2(0.0, 0.0);
-          }
+      for (int r = 0; r < 4; ++r) y[r] = Mj[int64_t(min(lk + 4 * r, rmax)) * m];
+      for (int rt = 0; rt < nrt; ++rt) {
+        v4d re, im;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          re[r] = y[r].x;
+          im[r] = y[r].y;
         }
-#pragma unroll 1
-        for (int r = nbp; r < rows; ++r) {
-          double2 *pr = M + int64_t(perm[k0 + r]) * m + j;
-          double2 x = *pr;
 #pragma unroll
-          for (int c = 0; c < NB; ++c) {
-            const double2 l = sP[c * rows + r];
-            x.x -= l.x * u[c].x - l.y * u[c].y;
-            x.y -= l.x * u[c].y + l.y * u[c].x;
-          }
-          *pr = x;
+        for (int r = 0; r < 4; ++r) y[r] = Mj[int64_t(min(16 * (rt + 1) + lk + 4 * r, rmax)) * m];  // the next tile
+        const double2 *Lr = sL + (nbp + min(16 * rt + li, rmax)) * LP + lk;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const double2 l = Lr[4 * t];
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(-l.x, u[t].x, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(-l.x, u[t].y, im, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f64_16x16x4f64(l.y, u[t].y, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f64_16x16x4f64(-l.y, u[t].x, im, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = 16 * rt + lk + 4 * r;
+          if (i <= rmax && jc < C) Mj[int64_t(i) * m] = make_double2(re[r], im[r]);
         }
       }
     }
     __syncthreads();
+  }
+  if (wave == 0) {  // sums over the NB lanes that hold pivots
+    ph = lane < NB ? ph : 0.0;
+    la = lane < NB ? la : 0.0;
+#pragma unroll
+    for (int o = NB / 2; o > 0; o >>= 1) {
+      ph += __shfl_xor(ph, o, 64);
+      la += __shfl_xor(la, o, 64);
+    }
+    if (lane == 0) {
+      phase[blockIdx.x] = m > 0 ? wrap_pi(ph) : 0.0;
+      s_v[0] = la;
+    }
   }
   __syncthreads();
+  la = s_v[0];
+  __syncthreads();
   if (la < kLogSingular && la > -INFINITY) {
-    const double sg = lu_smin<64>(M, m, perm, sP, sP + m, nullptr);
+    const double sg = lu_smin<NT>(M, m, sL, sL + m, s_v);
     la = sg > 0.0 ? log(sg) : -INFINITY;
   }
-  if (lane == 0) {
-    phase[blockIdx.x] = m > 0 ? wrap_pi(ph) : 0.0;
-    lsig[blockIdx.x] = la;
-  }
+  if (tid == 0) lsig[blockIdx.x] = la;
 }
 
-// Panel width for order m: the widest whose panel (m x NB c128) fits in
-// 160 KiB of LDS, preferring at most 64 KiB (several workgroups per CU).
+// Largest order of the kernel with a row per thread, and the panel width of the
+// other for order m (a panel of at most 160 KiB of LDS; 64 where that fits).
+constexpr int kDetRows = 256;
 int det_panel_width(int m) {
-  if (m <= 256) return 16;
   if (m <= 512) return 8;
   if (m <= 2544) return 4;
   return 0;
@@ -656,12 +739,9 @@ int flux_run(be_ctx *ctx, const void *U, int32_t N, int32_t m, int32_t ldu, int6
   if (nbw == 4)
     BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_det_phase<4>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, 2544 * 4 * 16));
-  else if (nbw == 8)
+  else if (m > kDetRows)
     BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_det_phase<8>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, 512 * 8 * 16));
-  else
-    BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_det_phase<16>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 256 * 16 * 16));
   const int64_t kps = int64_t(n_par) * n_perp;
   const int64_t mm = int64_t(std::max(m, 1)) * std::max(m, 1);
   hipLaunchKernelGGL(k_zero_st, dim3((n_sys + 255) / 256), dim3(256), 0, stream, status, int64_t(n_sys));
@@ -707,11 +787,15 @@ int flux_run(be_ctx *ctx, const void *U, int32_t N, int32_t m, int32_t ldu, int6
         const size_t lds = size_t(std::max(m, 1)) * nbw * sizeof(double2);
         double *ph = dir == 0 ? fs.ph_par : fs.ph_perp, *ls = dir == 0 ? fs.ls_par : fs.ls_perp;
         const dim3 grid(static_cast<uint32_t>(nk));
-        if (m <= 128)
-          hipLaunchKernelGGL(k_det_phase_w<8>, grid, dim3(64), size_t(m) * 8 * sizeof(double2) + size_t(m) * 4,
-                             stream, L, m, mm, ph, ls);
-        else if (nbw == 16)
-          hipLaunchKernelGGL(k_det_phase<16>, grid, dim3(DT), lds, stream, L, m, mm, ph, ls);
+        if (m <= kDetRows) {
+          const size_t sm = size_t(std::max(m, 1)) * 17 * sizeof(double2);
+          const int nt = m <= 64 ? 64 : m <= 128 ? 128 : 256;
+          auto kern = nt == 64 ? &k_det_phase_r<64> : nt == 128 ? &k_det_phase_r<128> : &k_det_phase_r<256>;
+          if (sm > 65536)
+            BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, int(sm)));
+          hipLaunchKernelGGL(kern, grid, dim3(nt), sm, stream, L, m, mm, ph, ls);
+        }
         else if (nbw == 8)
           hipLaunchKernelGGL(k_det_phase<8>, grid, dim3(DT), lds, stream, L, m, mm, ph, ls);
         else

@@ -38,16 +38,6 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// f(integral_constant<0>) ... f(integral_constant<N - 1>): loops over registers
-// whose index has to be a constant from the start
-template <int... I, typename F>
-__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F &&f) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void unrolled(F &&f) {
-  unrolled(std::make_integer_sequence<int, N>{}, f);
-}
 // Index of block (a, b), b <= 2 a + 1, among a thread's elements: by columns b
 __host__ __device__ constexpr int blk(int NA, int a, int b) {
   int k = 0;

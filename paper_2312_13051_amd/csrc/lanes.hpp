@@ -1,9 +1,10 @@
-// Sums across the lanes of a wave without LDS permutes.
+// Sums across the lanes of a wave without LDS permutes, loops over registers.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <utility>
 
 namespace {
 
@@ -68,6 +69,17 @@ __device__ __forceinline__ T wave_sum(T v) {
   v += lane_xor<2>(v);
   v += lane_xor<1>(v);
   return v;
+}
+
+// f(integral_constant<0>) ... f(integral_constant<N - 1>): loops over registers
+// whose index has to be a constant from the start
+template <int... I, typename F>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F &&f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F &&f) {
+  unrolled(std::make_integer_sequence<int, N>{}, f);
 }
 
 }  // namespace
