@@ -70,3 +70,31 @@ def test_phase_table(N, n_R, n_k, dtype):
     eps = 2.3e-16 if dtype == 0 else 6e-8
     assert np.abs(H - ref).max() < 20 * (2 * n_R + 1) * eps * scale
     assert np.array_equal(H, np.conj(H.swapaxes(1, 2)))
+
+
+# lists around the share of pairs from which the others are filled in (half, and eight more), alone and beside a sparse one:
+# every element of H is written
+@pytest.mark.parametrize("N, share", [(1, 0.0), (2, 0.3), (4, 0.2), (4, 0.6), (9, 0.3), (9, 0.45), (9, 0.9), (40, 0.4), (40, 0.6)])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_every_element_written(N, share, dtype):
+    gu.need_gpu()
+    rng = np.random.default_rng([N, int(100 * share)])
+    hops = []
+    for sh in (share, 0.1):
+        a, b = np.nonzero(np.triu(rng.random((N, N)) < sh))
+        t = rng.standard_normal(a.size) + 1j * np.where(a == b, 0.0, rng.standard_normal(a.size))
+        off = a != b
+        i, j = np.concatenate([a, b[off]]), np.concatenate([b, a[off]])
+        hops.append(syn.HopList(N, 2, i.astype(np.int32), j.astype(np.int32), np.zeros((i.size, 2), np.int32),
+                                np.concatenate([t, t[off].conj()])))
+    kappa = rng.uniform(-1, 1, (5, 3))
+    c = gu.ctx()
+    try:
+        for hs in (hops[:1], hops):
+            H = build(c, hs, kappa, dtype, 2)
+            ref = np.zeros((len(hs), N, N), complex)
+            for s, h in enumerate(hs):
+                ref[s, h.i, h.j] = h.t
+            assert np.abs(H - np.repeat(ref, 5, axis=0)).max(initial=0.0) <= (0.0 if dtype == 0 else 1e-6)
+    finally:
+        c.close()
