@@ -1127,6 +1127,195 @@ size_t panel_lds(int N, size_t csize, int nt) {
   return panel_smem(N, csize, nt) + (panel_part_lds(N, csize, nt) ? panel_part_bytes(N - 1, csize) : 0);
 }
 
+// ---------------------------------------------------------------- panels of few large matrices
+// The panel kernel gives a matrix one workgroup, which reads its trailing
+// matrix at the rate of one compute unit. Where there are few (the Hermitian
+// problems of a dozen lines' Wilson matrices), each column's matrix-vector product is
+// spread over the device instead (few_matvec: the panel kernel's tiles and
+// slots, a wave per tile) and the rest of the column follows in one workgroup
+// per matrix (few_column: the panel kernel's steps 4, 5 and, for the next
+// column, 1 and 2), two launches per column. Bound by the launches and by the
+// passes over V and W in one workgroup. Panels before -> so: 12 matrices of
+// order 1152 163 -> 34 ms, 4 of 2304 857 -> 96, 16 of 512 20.9 -> 9.0.
+__global__ __launch_bounds__(256) void few_matvec(const double2 *A, int64_t sA, int lda, int N, int j, const double2 *Vj,
+                                                  int64_t sVW, double2 *part, int64_t sP) {
+  constexpr int CW = 8, CSH = 3;  // columns in flight; lane -> column shift of xpose_colsum
+  const int64_t q = blockIdx.y;
+  const double2 *Aq = A + q * sA, *v = Vj + q * sVW;
+  double2 *pq = part + q * sP;
+  const int lane = threadIdx.x & 63;
+  const int r0 = j + 1, nrb = (N - r0 + 63) >> 6, nslot = nrb + 1, ntile = nrb * (nrb + 1) / 2;
+  for (int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); t < ntile; t += gridDim.x * 4) {
+    int bi = 0, bj = t;
+    while (bj > bi) {
+      bj -= bi + 1;
+      ++bi;
+    }
+    const int r = r0 + 64 * bi + lane, rc = min(r, N - 1), cb = r0 + 64 * bj;
+    const double2 vr = r < N ? v[rc] : make_double2(0.0, 0.0);
+    const double2 vl = v[min(cb + lane, N - 1)];  // of column cb + lane
+    double2 *pcol = pq + (bj * nslot + (bj + 1) + (bi - bj)) * 64;
+    double yr = 0.0, yi = 0.0;
+    for (int k = 0; k < 64 && cb + k < N; k += CW) {
+      double2 a[CW];
+#pragma unroll
+      for (int u = 0; u < CW; ++u) {  // entries above the diagonal or past the matrix are masked below
+        const int c = min(cb + k + u, N - 1);
+        a[u] = Aq[max(rc, c) + int64_t(c) * lda];
+      }
+#pragma unroll
+      for (int u = 0; u < CW; ++u) {
+        const int c = cb + k + u;
+        const bool use = c < N && r < N && r >= c, dg = r == c;
+        const double vx = __shfl(vl.x, k + u, 64), vy = __shfl(vl.y, k + u, 64);
+        const double ax = use ? a[u].x : 0.0, ay = use && !dg ? a[u].y : 0.0;
+        yr += ax * vx - ay * vy;
+        yi += ax * vy + ay * vx;
+        a[u] = dg ? make_double2(0.0, 0.0) : make_double2(ax * vr.x + ay * vr.y, ax * vr.y - ay * vr.x);
+      }
+      const double2 sc = xpose_colsum<CW>(a, lane);
+      if ((lane & ((1 << CSH) - 1)) == 0) pcol[k + (lane >> CSH)] = sc;
+    }
+    pq[(bi * nslot + bj) * 64 + lane] = make_double2(yr, yi);
+  }
+}
+
+constexpr int FT = 1024;  // threads of few_column
+
+// Reflector of column j, whose updated entries r >= j are in sx: d, e, tau (T's
+// diagonal) and v (A's column, V, V2).
+__device__ void few_reflect(double2 *Aq, int lda, int N, int j, double2 *Vj, double2 *V2j, double2 *Tjj, double *dj,
+                            double *ej, const double2 *sx, double *red) {
+  const int tid = threadIdx.x;
+  double xn = 0.0, dummy = 0.0;
+  for (int r = j + 2 + tid; r < N; r += FT) xn += sx[r].x * sx[r].x + sx[r].y * sx[r].y;
+  block_sum2(xn, dummy, red);
+  const double2 alpha = sx[j + 1];
+  double2 tau = make_double2(0.0, 0.0), scal = tau;
+  double beta = alpha.x;
+  if (!(xn == 0.0 && alpha.y == 0.0)) {
+    const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn);
+    beta = alpha.x >= 0.0 ? -nrm : nrm;
+    tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
+    const double dr = alpha.x - beta, di = alpha.y, den = dr * dr + di * di;
+    scal = make_double2(dr / den, -di / den);
+  }
+  if (tid == 0) {
+    *dj = sx[j].x;
+    *ej = beta;
+    *Tjj = tau;
+  }
+  for (int r = tid; r < N; r += FT) {
+    const double2 v = r <= j       ? make_double2(0.0, 0.0)
+                      : r == j + 1 ? make_double2(1.0, 0.0)
+                                   : be::cmul(sx[r], scal);
+    Aq[r + int64_t(j) * lda] = v;
+    Vj[r] = v;
+    V2j[r] = v;
+  }
+}
+
+// Column jj of the panel that starts at column p0, after its matrix-vector
+// product (jj < 0: only the first column's reflector), then column jj + 1's
+// update and reflector.
+__global__ __launch_bounds__(FT) void few_column(double2 *A, int64_t sA, int lda, int N, int p0, int jj, double2 *VW,
+                                                 int64_t sVW, double2 *Tm, int64_t sTm, double *d, double *e, int64_t sDE,
+                                                 const double2 *part, int64_t sP) {
+  extern __shared__ double2 fsm[];
+  double2 *sv = fsm, *sy = sv + N, *st1 = sy + N, *st2 = st1 + NB, *sVr = st2 + NB, *sWr = sVr + NB;
+  double *red = reinterpret_cast<double *>(sWr + NB);
+  const int64_t q = blockIdx.x;
+  double2 *Aq = A + q * sA, *V = VW + q * sVW, *W = V + int64_t(NB) * N, *V2 = W + int64_t(NB) * N, *T = Tm + q * sTm;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double *dq = d + q * sDE, *eq = e + q * sDE;
+  if (jj < 0) {
+    for (int t = tid; t < NB * NB; t += FT) T[t] = make_double2(0.0, 0.0);
+    for (int r = p0 + tid; r < N; r += FT) {
+      double2 a = Aq[r + int64_t(p0) * lda];
+      if (r == p0) a.y = 0.0;
+      sv[r] = a;
+    }
+    __syncthreads();
+    few_reflect(Aq, lda, N, p0, V, V2, T, dq + p0, eq + p0, sv, red);
+    return;
+  }
+  const int j = p0 + jj, r0 = j + 1, nrb = (N - r0 + 63) >> 6, nslot = nrb + 1;
+  const double2 *pq = part + q * sP, tau = T[jj + jj * NB];
+  for (int c = tid; c < jj; c += FT) {
+    sVr[c] = V[r0 + int64_t(c) * N];
+    sWr[c] = W[r0 + int64_t(c) * N];
+  }
+  for (int r = r0 + tid; r < N; r += FT) {
+    sv[r] = V[r + int64_t(jj) * N];
+    const double2 *pb = pq + ((r - r0) >> 6) * nslot * 64 + ((r - r0) & 63);
+    double2 y = make_double2(0.0, 0.0);
+#pragma unroll 8
+    for (int t = 0; t < nslot; ++t) y = be::cadd(y, pb[t * 64]);
+    sy[r] = y;
+  }
+  __syncthreads();
+  for (int c = wave; c < jj; c += FT / 64) {  // t1 = W^H v, t2 = V^H v
+    double2 a = make_double2(0.0, 0.0), b = a;
+#pragma unroll 4
+    for (int r = r0 + lane; r < N; r += 64) {
+      const double2 v = sv[r];
+      a = be::cadd(a, be::cmulc(W[r + int64_t(c) * N], v));
+      b = be::cadd(b, be::cmulc(V[r + int64_t(c) * N], v));
+    }
+    a.x = wave_sum(a.x);
+    a.y = wave_sum(a.y);
+    b.x = wave_sum(b.x);
+    b.y = wave_sum(b.y);
+    if (lane == 0) {
+      st1[c] = a;
+      st2[c] = b;
+    }
+  }
+  __syncthreads();
+  const bool next = jj + 1 < NB;
+  double dr = 0.0, di = 0.0;
+  for (int r = r0 + tid; r < N; r += FT) {  // y -= V t1 + W t2, w = tau y; the earlier reflectors' share of column j + 1
+    double2 y = sy[r], p = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (int c = 0; c < jj; ++c) {
+      const double2 vv = V[r + int64_t(c) * N], w = W[r + int64_t(c) * N];
+      y = be::csub(y, be::cadd(be::cmul(vv, st1[c]), be::cmul(w, st2[c])));
+      p = be::cadd(p, be::cadd(be::cmulc(sWr[c], vv), be::cmulc(sVr[c], w)));
+    }
+    y = be::cmul(tau, y);
+    sy[r] = y;
+    const double2 v = sv[r];
+    dr += y.x * v.x + y.y * v.y;
+    di += y.x * v.y - y.y * v.x;
+    if (next) Aq[r + int64_t(r0) * lda] = be::csub(Aq[r + int64_t(r0) * lda], p);
+  }
+  if (tid < jj) {  // T(0:jj, jj) = -tau T(0:jj, 0:jj) t2
+    double2 x = make_double2(0.0, 0.0);
+    for (int c = tid; c < jj; ++c) x = be::cadd(x, be::cmul(T[tid + c * NB], st2[c]));
+    x = be::cmul(tau, x);
+    T[tid + jj * NB] = make_double2(-x.x, -x.y);
+  }
+  block_sum2(dr, di, red);
+  const double2 al = make_double2(-0.5 * (tau.x * dr - tau.y * di), -0.5 * (tau.x * di + tau.y * dr));
+  for (int r = r0 + tid; r < N; r += FT) {  // w += alpha v, alpha = -tau (w^H v) / 2
+    const double2 w = be::cadd(sy[r], be::cmul(al, sv[r]));
+    W[r + int64_t(jj) * N] = w;
+    sy[r] = w;
+  }
+  if (!next) return;
+  __syncthreads();
+  const double2 wj = sy[r0], vj = sv[r0];
+  __syncthreads();
+  for (int r = r0 + tid; r < N; r += FT) {
+    double2 a = be::csub(Aq[r + int64_t(r0) * lda], be::cadd(be::cmulc(wj, sv[r]), be::cmulc(vj, sy[r])));
+    if (r == r0) a.y = 0.0;
+    sv[r] = a;
+  }
+  __syncthreads();
+  few_reflect(Aq, lda, N, r0, V + int64_t(jj + 1) * N, V2 + int64_t(jj + 1) * N, T + (jj + 1) * (NB + 1), dq + r0, eq + r0,
+              sv, red);
+}
+
 template <typename T>
 using PanelFn = void (*)(typename CT<T>::c *, int64_t, int, int, int, int, typename CT<T>::c *, int64_t,
                          typename CT<T>::c *, int64_t, double *, double *, int64_t, typename CT<T>::c *, int64_t,
@@ -1341,16 +1530,44 @@ struct GemmOf<float> {
 // on-chip reduction (FP64).
 static int panels_before_resident(int N) { return N <= kResidentOrder ? 0 : (N - kResidentOrder + NB - 1) / NB; }
 
+// Few matrices: at most three panel workgroups for eight compute units (panels,
+// panel kernel -> column launches: 96 matrices of order 288 3.15 -> 3.16 ms, 400
+// 8.06 -> 6.96, 1024 122 -> 84; 128 of 288 3.24 -> 3.30, 256 of 400 10.8 -> 13.1).
+// The two round differently, and a caller's matrix keeps its bits in any batch:
+// only the eigenphases' problems, which no other batch holds, may take it.
+static bool few_matrices(be_ctx *ctx, int64_t nb_mat) { return 8 * nb_mat <= 3 * ctx->n_cu; }
+
+// Panel of NB columns from p0 by column launches (p0 + NB < N: the resident
+// kernel takes the last columns).
+static void few_panel(be_ctx *ctx, double2 *H, int64_t ms, int ld, int N, int p0, int64_t nb_mat, double2 *VW, int64_t sVW,
+                      double2 *Tm, int64_t sT, double *dd, double *ee, double2 *Pf, int64_t sPf, hipStream_t stream) {
+  const size_t sm = (2 * size_t(N) + 4 * NB) * sizeof(double2) + 2 * (FT / 64) * sizeof(double);
+  if (sm > 65536)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&few_column), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              int(sm));
+  for (int jj = -1; jj < NB; ++jj) {
+    if (jj >= 0) {
+      const int nrb = (N - p0 - jj - 1 + 63) / 64, tiles = nrb * (nrb + 1) / 2;
+      const int64_t g = std::min<int64_t>((tiles + 3) / 4, std::max<int64_t>(1, 4 * ctx->n_cu / nb_mat));
+      hipLaunchKernelGGL(few_matvec, dim3(static_cast<uint32_t>(g), static_cast<uint32_t>(nb_mat)), dim3(256), 0, stream,
+                         H, ms, ld, N, p0 + jj, VW + int64_t(jj) * N, sVW, Pf, sPf);
+    }
+    hipLaunchKernelGGL(few_column, dim3(static_cast<uint32_t>(nb_mat)), dim3(FT), sm, stream, H, ms, ld, N, p0, jj, VW,
+                       sVW, Tm, sT, dd, ee, int64_t(N), Pf, sPf);
+  }
+}
+
 // One sub-batch of nb_mat matrices. T is the working precision of the
 // Householder reduction and back-transformation (double: FP64 path, float:
 // mixed path); the tridiagonal solve and the re-orthonormalization are FP64.
 // Hin: nb_mat matrices of CT<T>::c; U: c128 output.
-// bf16x3 (T = float only): the trailing update and the back-transformation
+// columns (T = double only): a batch of few matrices may take its panels by
+// column launches. bf16x3 (T = float only): the trailing update and the back-transformation
 // take the split-bf16 products of the complex GEMM.
 template <typename T>
 static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t ms, int64_t nb_mat, int lo, int hi,
                       double *evals, double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream,
-                      double clu_rel = kCluRel, bool bf16x3 = false) {
+                      double clu_rel = kCluRel, bool bf16x3 = false, bool columns = false) {
   typedef typename CT<T>::c C;
   typedef typename GemmOf<T>::type G;
   const int m = hi - lo;
@@ -1398,6 +1615,10 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
   const int64_t sPg = pl ? 0 : int64_t(panel_part_bytes(N - 1, 1));
   C *Pg = nullptr;
   if (!pl && p_res > 0) cv.add(&Pg, size_t(nb_mat) * sPg);
+  const bool few = columns && !mixed && p_res > 0 && few_matrices(ctx, nb_mat);
+  const int64_t sPf = int64_t((N + 62) / 64) * ((N + 62) / 64 + 1) * 64;
+  double2 *Pf = nullptr;
+  if (few) cv.add(&Pf, size_t(nb_mat) * sPf);
   BE_RET_IF(cv.commit(ctx, stream, WS_EIGH));
   hipLaunchKernelGGL(zero_u32, dim3((nb_mat + 255) / 256), dim3(256), 0, stream, status, nb_mat);
   BE_RET_IF(check_launch(ctx, "zero_u32"));
@@ -1412,7 +1633,12 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
     const int p0 = p * NB, nbp = std::min(NB, N - p0);
     {
       ProfScope prof(ctx, "hetrd_panel", stream);
-      hipLaunchKernelGGL(panel, dim3(nb_mat), dim3(pnt), psm, stream, H, ms, ld, N, p0, nbp, VW, sVW,
+      if constexpr (sizeof(T) == sizeof(double)) {
+        if (few) {
+          few_panel(ctx, H, ms, ld, N, p0, nb_mat, VW, sVW, Tm + int64_t(p) * NB * NB, sT, dd, ee, Pf, sPf, stream);
+        }
+      }
+      if (!few) hipLaunchKernelGGL(panel, dim3(nb_mat), dim3(pnt), psm, stream, H, ms, ld, N, p0, nbp, VW, sVW,
                          Tm + int64_t(p) * NB * NB, sT, dd, ee, int64_t(N), Pg, sPg, status);
     }
     BE_RET_IF(check_launch(ctx, "hetrd_panel"));
@@ -1728,7 +1954,7 @@ static int64_t eigh_sub_batch(be_ctx *ctx, int N, size_t per, size_t reusable, i
 template <typename T>
 static int eigh_run(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t mat_stride, int64_t n_mat, int band_lo,
                     int band_hi, double *evals, double2 *U, int ldu, int64_t u_stride, uint32_t *status,
-                    hipStream_t stream, double clu_rel = kCluRel, bool bf16x3 = false) {
+                    hipStream_t stream, double clu_rel = kCluRel, bool bf16x3 = false, bool columns = false) {
   const int m = band_hi - band_lo;
   BE_RET_IF(check_eigh_lds(ctx, N, m, sizeof(typename CT<T>::c)));
   if (n_mat == 0) return BE_OK;
@@ -1745,7 +1971,7 @@ static int eigh_run(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t ma
   for (int64_t b0 = 0; b0 < n_mat; b0 += cap) {
     const int64_t nb_mat = std::min<int64_t>(cap, n_mat - b0);
     BE_RET_IF(eigh_chunk<T>(ctx, H + b0 * mat_stride, N, ld, mat_stride, nb_mat, band_lo, band_hi, evals + b0 * (m + 2),
-                            U + b0 * u_stride, ldu, u_stride, status + b0, stream, clu_rel, bf16x3));
+                            U + b0 * u_stride, ldu, u_stride, status + b0, stream, clu_rel, bf16x3, columns));
   }
   return BE_OK;
 }
@@ -1939,8 +2165,9 @@ static int eigh_refined(be_ctx *ctx, const double2 *H, int N, int ld, int64_t ms
 
 int eigh_fp64(be_ctx *ctx, double2 *H, int N, int ld, int64_t mat_stride, int64_t n_mat, int band_lo, int band_hi,
               double *evals, double2 *U, int ldu, int64_t u_stride, uint32_t *status, hipStream_t stream,
-              double clu_rel) {
-  return eigh_run<double>(ctx, H, N, ld, mat_stride, n_mat, band_lo, band_hi, evals, U, ldu, u_stride, status, stream, clu_rel);
+              double clu_rel, bool columns) {
+  return eigh_run<double>(ctx, H, N, ld, mat_stride, n_mat, band_lo, band_hi, evals, U, ldu, u_stride, status, stream, clu_rel,
+                          false, columns);
 }
 
 int eigh_mixed(be_ctx *ctx, float2 *H, int N, int ld, int64_t mat_stride, int64_t n_mat, int band_lo, int band_hi,

@@ -1390,7 +1390,7 @@ static int unitary_phases(be_ctx *ctx, const double2 *cur, int m, int64_t n_line
     ctx->prof_scope = scope + "unitary_";  // launch-timer names of the inner eigensolver
     // clusters only at 64 eps: W's nearly equal phases (often hundreds within
     // 1e-9 of each other) are then resolved one by one, each vector checked below
-    const int erc = eigh_fp64(ctx, A, m, m, mm, nl, 0, m, ev, V, m, mm, est, stream, 64.0 * DBL_EPSILON);
+    const int erc = eigh_fp64(ctx, A, m, m, mm, nl, 0, m, ev, V, m, mm, est, stream, 64.0 * DBL_EPSILON, true);
     ctx->prof_scope = scope;
     BE_RET_IF(erc);
     ZGemm g;  // W V

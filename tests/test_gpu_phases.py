@@ -55,3 +55,11 @@ def test_chosen_phases(m, kind):
     assert status & ~4 == 0
     assert phase_set_error(got, np.array(lines)) < 4e-12
     assert np.all(np.diff(got, axis=1) >= 0)
+
+
+# orders whose Hermitian problems, few of them, are reduced by column launches before the on-chip reduction takes the last
+# columns: one panel, a panel and one column more, blocks of 64 rows with remainders
+@pytest.mark.parametrize("m", [217, 248, 249, 300, 513])
+@pytest.mark.parametrize("kind", ["spread", "crowd"])
+def test_few_large_orders(m, kind):
+    test_chosen_phases(m, kind)
