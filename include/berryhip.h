@@ -206,7 +206,8 @@ int be_build_hk(be_ctx *ctx, const be_hk_plan *plan, int32_t sys_first, int32_t 
  * large N where 4 GiB holds fewer matrices than the device runs at once, of
  * up to that many within 48 GiB (at most half the free device memory).
  * Synchronizes the stream once per sub-batch and orthonormalization step
- * (the largest Gram error of Z is read back).
+ * (the largest Gram error of Z is read back). Small orders (up to 32 in FP64,
+ * 16 on the mixed path) are solved in one launch without either.
  * Size limit: the panel vectors (2N complex values) and the tridiagonal
  * solver's arrays ((4N + m + 4) doubles; (3N + m) doubles and N + 1 + 2m
  * ints) are held in LDS and must fit in 160 KiB, which allows N up to about
@@ -215,9 +216,10 @@ int be_eigh_batched(be_ctx *ctx, void *H, int32_t dtype, int32_t N, int32_t ld, 
                     int32_t n_mat, int32_t band_lo, int32_t band_hi, int32_t precision, double *evals,
                     void *U, int32_t ldu, int64_t u_stride, uint32_t *status, hipStream_t stream);
 
-/* Matrices of order N that the eigensolver's panel kernel keeps resident on
- * the device at once for `precision` (one workgroup per matrix; depends on
- * the panel thread count chosen for N). be_eigh_batched processes a batch in
+/* Matrices of order N that the eigensolver's reduction (the panel kernel, or
+ * the on-chip kernel for FP64 orders up to 216) keeps resident on the device at
+ * once for `precision` (one workgroup per matrix; depends on the panel thread
+ * count chosen for N). be_eigh_batched processes a batch in
  * equal sub-batches of whole such rounds where its workspace cap allows, so a
  * batch of a multiple of *round matrices fills every round. Host-only query
  * (an occupancy calculation), no device work. */
