@@ -52,6 +52,7 @@ FP64_PEAK_TFLOPS = 78.6
 BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA
 FP32_PEAK_TFLOPS = 157.3
 NB = 32  # panel width of the Householder reduction
+ON_CHIP = 216  # columns that the FP64 reduction takes on chip
 
 
 def systems():
@@ -131,19 +132,28 @@ def cpu_baseline(sample, workers, fn=_oracle_line, warm_with_sample=True):
 
 
 # ---------------------------------------------------------------- algorithmic work
-def hetrd_panel_bytes(N, n_mat, elem_bytes=16):
+def panels_off_chip(N):
+    """Panels of an FP64 reduction before its last columns are reduced on chip."""
+    return max(0, -(-(N - ON_CHIP) // NB))
+
+
+def hetrd_panel_bytes(N, n_mat, elem_bytes=16, panels=None):
     """Algorithmic HBM bytes of all panel launches of one eigensolver call: the
     Hermitian matrix-vector product of each reflector column reads one
     triangle (diagonal included) of the trailing matrix, 16 B per c128
-    element, 8 B per c64: sum_j e (N-j-1)(N-j)/2, about e N^3/6 per matrix."""
-    return n_mat * sum(elem_bytes * (N - j - 1) * (N - j) // 2 for j in range(N - 1))
+    element, 8 B per c64: sum_j e (N-j-1)(N-j)/2, about e N^3/6 per matrix.
+    panels: the first so many panels only."""
+    cols = N - 1 if panels is None else min(N - 1, panels * NB)
+    return n_mat * sum(elem_bytes * (N - j - 1) * (N - j) // 2 for j in range(cols))
 
 
-def eigh_gemm_flops(name, N, m, n_mat):
-    """Algorithmic flops (8 per complex multiply-add) of the eigensolver's GEMMs."""
+def eigh_gemm_flops(name, N, m, n_mat, panels=None):
+    """Algorithmic flops (8 per complex multiply-add) of the eigensolver's GEMMs
+    (panels: trailing updates of the first so many panels only)."""
     P = (N + NB - 1) // NB
     if name == "her2k":   # Hermitian rank-2nb update, one triangle
-        return n_mat * sum(8.0 * (N - p * NB - NB) ** 2 * NB for p in range(P) if N - p * NB - NB > 0)
+        return n_mat * sum(8.0 * (N - p * NB - NB) ** 2 * NB for p in range(P if panels is None else panels)
+                           if N - p * NB - NB > 0)
     if name == "unmtr":   # X = V^H U, Y = T X (T triangular), U -= V Y
         tot = 0.0
         for p in range(P):
@@ -191,17 +201,18 @@ def gemm_phase_summary(flops, prof_ms, fp32_tags, scale=1.0, bf16_tags=()):
                     "extras (polar, reorth) are timed but not counted"}
 
 
-def gemm_phase_flops(N, m, n_par, n_k_sys, m_dn):
+def gemm_phase_flops(N, m, n_par, n_k_sys, m_dn, fp64=False, pso_fp64=False):
     """Algorithmic GEMM flops per call-site tag for one pass over the systems
-    (spin-resolved loop). m_dn: spin-down sector size per system."""
+    (spin-resolved loop). m_dn: spin-down sector size per system; fp64,
+    pso_fp64: the eigensolver of H, of P S P, reduces in FP64."""
     nk = n_k_sys * len(m_dn)
     md = np.asarray(m_dn, dtype=np.float64)
     mu = m - md
     return {
-        "her2k": eigh_gemm_flops("her2k", N, m, nk),
+        "her2k": eigh_gemm_flops("her2k", N, m, nk, panels_off_chip(N) if fp64 else None),
         "unmtr": eigh_gemm_flops("unmtr", N, m, nk),
         "pso": 4.0 * m * (m + 1) * N * nk,                 # U^H (S U), one triangle (Hermitian)
-        "pso_her2k": eigh_gemm_flops("her2k", m, m, nk),   # eigensolver of P S P (order m, all bands)
+        "pso_her2k": eigh_gemm_flops("her2k", m, m, nk, panels_off_chip(m) if pso_fp64 else None),  # P S P, all bands
         "pso_unmtr": eigh_gemm_flops("unmtr", m, m, nk),
         "spin_sector": 8.0 * N * m * m * nk,               # U [Q- Q+]
         "overlap": float(np.sum(8.0 * N * (md ** 2 + mu ** 2))) * n_k_sys,
@@ -459,11 +470,11 @@ def main():
     name, (ms_tot, launches) = dom
     roof = {"kernel": name, "bound": "alu", "achieved": None, "peak": None, "unit": None, "frac": None,
             "traffic": None, "avg_launch_ms": round(ms_tot / launches, 4), "launches": launches}
-    flops = gemm_phase_flops(N, m, N_PAR, n_k, mdn_all)
+    flops = gemm_phase_flops(N, m, N_PAR, n_k, mdn_all, fp64=not mixed, pso_fp64=args.precision in ("fp64", "refined"))
     fp32_tags = ("her2k", "unmtr", "pso_her2k", "pso_unmtr") if mixed else ()
     if name == "hetrd_panel":
         elem = 8 if mixed else 16
-        byts = hetrd_panel_bytes(N, total_k, elem) * steps
+        byts = hetrd_panel_bytes(N, total_k, elem, None if mixed else panels_off_chip(N)) * steps
         ach = byts / (ms_tot * 1e-3) / 1e9
         pp = "mixed" if mixed else "fp64"  # the refined path runs the mixed path's panel kernel
         traffic = traffic_from_profile(os.path.join(ROOT, "profiles", f"hetrd_panel_bhz400_{pp}.md"),
@@ -677,12 +688,12 @@ def main_study(args):
             "traffic": None, "avg_launch_ms": round(ms_tot / launches, 4), "launches": launches}
     n_mat = total_k * steps
     if name == "hetrd_panel":
-        byts = hetrd_panel_bytes(N, n_mat, 8 if mixed else 16)
+        byts = hetrd_panel_bytes(N, n_mat, 8 if mixed else 16, None if mixed else panels_off_chip(N))
         ach = byts / (ms_tot * 1e-3) / 1e9
         roof.update({"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(ach / HBM_PEAK_GBS, 4), "algorithmic_bytes_per_launch": round(byts / launches, 1)})
     elif name in ("her2k", "unmtr"):
-        fl = eigh_gemm_flops(name, N, m, n_mat)
+        fl = eigh_gemm_flops(name, N, m, n_mat, None if mixed else panels_off_chip(N))
         pk = FP32_PEAK_TFLOPS if mixed else FP64_PEAK_TFLOPS
         ach = fl / (ms_tot * 1e-3) / 1e12
         roof.update({"bound": "mfma", "achieved": round(ach, 2), "peak": pk, "unit": "TFLOP/s",
@@ -929,7 +940,7 @@ def main_served(args):
     roof = {"kernel": name, "bound": "alu", "achieved": None, "peak": None, "unit": None, "frac": None,
             "traffic": None, "avg_launch_ms": round(ms_tot / launches, 4), "launches": launches}
     if name == "hetrd_panel":
-        byts = sum(hetrd_panel_bytes(r.N, r.n_k, 8 if mixed else 16) for r in reqs)
+        byts = sum(hetrd_panel_bytes(r.N, r.n_k, 8 if mixed else 16, None if mixed else panels_off_chip(r.N)) for r in reqs)
         ach = byts / (ms_tot * 1e-3) / 1e9
         roof.update({"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(ach / HBM_PEAK_GBS, 4), "algorithmic_bytes_per_launch": round(byts / launches, 1),
