@@ -11,14 +11,16 @@
 //    GEMM, C -= [V W] [W V]^H, on its lower tiles only (the upper triangle is
 //    never read again). The
 //    panel's compact-WY factor T (Q_panel = I - V T V^H) is accumulated on the
-//    fly from the same dot products.
+//    fly from the same dot products. In FP64 the last columns (216 at most, all
+//    of a smaller matrix) are reduced on chip (hetrd_resident.hip), and panels
+//    of few large matrices may run column by column over the whole device.
 // 2. FP64 tridiagonal eigensolver (tri_bisect, tri_invit, tri_gs): bisection with Sturm counts,
 //    one lane per eigenvalue, for the selected indices and their neighbours;
 //    T is split where an off-diagonal is negligible (an eigenvalue of
 //    multiplicity k forces k-1 such splits), and the k lanes of a k-fold
 //    eigenvalue run inverse iteration (partial pivoting, pseudo-random start)
 //    on k distinct blocks that hold it, so their vectors have disjoint
-//    supports; lanes that must share a block fall back to Gram-Schmidt. The
+//    supports; lanes that must share a block are orthonormalized by Cholesky QR. The
 //    vectors are then orthonormalized in FP64 by Newton-Schulz steps on the
 //    Gram matrix (symmetric orthonormalization, MFMA DGEMMs) until
 //    max |Z^T Z - I| < 1e-14 (5e-8 on the mixed path).
@@ -28,6 +30,7 @@
 //    X = V^H U, Y = T X, U -= V Y.
 // 4. Mixed precision: the reduction and back-transformation run in FP32 on
 //    FP32 MFMA; the tridiagonal solve and the orthonormalization stay FP64.
+// Small orders take eigh_small.hip instead (whole, or its tridiagonal part).
 #include <algorithm>
 #include <cfloat>
 #include <cmath>

@@ -11,7 +11,8 @@
 //                 singular values in (0, sqrt 3), which holds since ||F|| <= 1
 //   chain         W_line = F_{n-1} ... F_0 as a binary tree of batched GEMMs
 //                 that keeps the left-to-right order
-//   eigenphases   one wave per W: Householder reduction to Hessenberg form,
+//   eigenphases   from order 13 on through the Hermitian eigensolver; below, and
+//                 where that cannot resolve a matrix, one wave per W: Householder reduction to Hessenberg form,
 //                 then single-shift complex QR with Wilkinson shifts; a
 //                 subdiagonal entry is negligible below 32 eps times its two
 //                 diagonal neighbours (the level to which a product of polar
