@@ -101,27 +101,50 @@ __global__ __launch_bounds__(RT, NA <= 3 ? 4 : 2) void hetrd_resident_kernel(dou
   if (S > 0 && tid < n) sx[tid] = strip[tid];  // column 0 (else written with the loads)
   __syncthreads();
   for (int j = 0; j + 1 < n; ++j) {
-    // ---- reflector of column j (every wave by itself); u = x - beta e_{j+1}, v = scal u
+    // ---- reflector of column j (every wave by itself); u = 2^sh (x - beta e_{j+1}) of
+    // norm about one, v = scal u: products of three factors of u, A and u, and the
+    // square of scal, would leave the range of FP64 for matrices of norm 1e103 or
+    // 1e-105 already, and for columns of norm 1e-154
     double xn = 0.0;
     for (int i = j + 2 + lane; i < n; i += 64) {
       const double2 x = sx[i];
       xn = fma(x.x, x.x, fma(x.y, x.y, xn));
     }
     xn = wave_sum(xn);
-    const double2 alpha = sx[j + 1];
+    double2 alpha = sx[j + 1];
     double2 tau = make_double2(0.0, 0.0), scal = tau, ub = tau;
-    double beta = alpha.x;
+    double beta = alpha.x, nn = alpha.x * alpha.x + alpha.y * alpha.y + xn;
+    int sh = 0;
+    if (!(nn >= 0x1p-900 && nn <= 0x1p900)) {  // the squares may have left the range: again, scaled by the largest entry
+      double mx = 0.0;
+      for (int i = j + 1 + lane; i < n; i += 64) mx = fmax(mx, fmax(fabs(sx[i].x), fabs(sx[i].y)));
+      for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+      sh = -__builtin_amdgcn_frexp_exp(mx);
+      xn = 0.0;
+      for (int i = j + 2 + lane; i < n; i += 64) {
+        const double x = __builtin_amdgcn_ldexp(sx[i].x, sh), y = __builtin_amdgcn_ldexp(sx[i].y, sh);
+        xn = fma(x, x, fma(y, y, xn));
+      }
+      xn = wave_sum(xn);
+      alpha = make_double2(__builtin_amdgcn_ldexp(alpha.x, sh), __builtin_amdgcn_ldexp(alpha.y, sh));
+      nn = alpha.x * alpha.x + alpha.y * alpha.y + xn;
+    }
     if (xn != 0.0 || alpha.y != 0.0) {
-      const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn);
-      beta = alpha.x >= 0.0 ? -nrm : nrm;
-      tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
-      ub = make_double2(alpha.x - beta, alpha.y);
+      const double nrm = sqrt(nn), b = alpha.x >= 0.0 ? -nrm : nrm;
+      const int ex = -__builtin_amdgcn_frexp_exp(nrm);
+      beta = __builtin_amdgcn_ldexp(b, -sh);
+      tau = make_double2((b - alpha.x) / b, -alpha.y / b);
+      ub = make_double2(__builtin_amdgcn_ldexp(alpha.x - b, ex), __builtin_amdgcn_ldexp(alpha.y, ex));
       const double den = ub.x * ub.x + ub.y * ub.y;
       scal = make_double2(ub.x / den, -ub.y / den);
+      sh += ex;
     }
     if (tid < NX) {
       double2 u = make_double2(0.0, 0.0);
-      if (tid > j && tid < n) u = tid == j + 1 ? ub : sx[tid];
+      if (tid > j && tid < n) {
+        u = sx[tid];
+        u = tid == j + 1 ? ub : make_double2(__builtin_amdgcn_ldexp(u.x, sh), __builtin_amdgcn_ldexp(u.y, sh));
+      }
       su[tid] = u;
     }
     lds_barrier();
