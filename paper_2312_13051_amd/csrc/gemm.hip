@@ -362,12 +362,12 @@ inline bool use_big_tiles(int M, int N) {
 
 template <typename T>
 int dispatch(be_ctx *ctx, GP<T> p, int opA, int opB, hipStream_t s) {
+  if (p.M <= 0 || p.N <= 0 || p.batch <= 0) return BE_OK;  // nothing to launch
   // FP64 from order 128 on: 64 x 64 tiles, whose idle wave sub-tiles are skipped
   // (2,304 products 400 x 200 by K = 200: 5.93 ms before, 5.50 in 32 x 32 tiles,
   // 4.92 so; at 100 x 100 by 100 the small tiles stay even)
   if (sizeof(T) == 8 && std::min(p.M, p.N) >= 48 && std::max(p.M, p.N) > 128)
     return launch_cfg<T, 64, 64, 4, 2>(ctx, p, opA, opB, s);
-  if (p.M <= 0 || p.N <= 0 || p.batch <= 0) return BE_OK;
   // Tile choice by output size; small outputs use one-wave tiles.
   // 64 x 64 tiles with 8 waves (each 16 x 32): fewer registers per wave than
   // with 4 waves, twice the resident waves per SIMD (measured faster)

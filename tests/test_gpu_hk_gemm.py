@@ -122,3 +122,14 @@ def test_zgemm_matches_numpy(opA, opB, M, N, K, batch):
     got = gu.to_np(dC, M)
     scale = np.abs(opa(A)) @ np.abs(opb(B)) + np.abs(C0)
     assert np.all(np.abs(got - ref) <= 1e-14 * K * scale + 1e-300)
+
+
+# outputs on either side of each tile choice: an empty batch is accepted and does nothing
+@pytest.mark.parametrize("M,N", [(8, 8), (30, 30), (48, 129), (200, 200)])
+def test_zgemm_empty_batch(M, N):
+    gu.need_gpu()
+    A, B, C = (gu.colmajor(1, M, N, M, fill=1.0) for _ in range(3))
+    c = gu.ctx()
+    c.zgemm_strided("N", "N", M, N, 4, 1.0, A, M, A.stride(0), B, 4, B.stride(0), 0.0, C, M, C.stride(0), 0)
+    torch.cuda.synchronize()
+    assert torch.all(C == 1.0)
