@@ -538,8 +538,11 @@ __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *
   const double eps = DBL_EPSILON;
   // the scaled matrix (norm in [1/2, 1]) and its interval
   const double sc = sturm_scale(tnorm), isc = 1.0 / sc, tn = tnorm * sc;
+  int floored = 0;
   for (int i = tid; i < N; i += PT) {
-    sde[i] = make_double2(sd[i] * sc, fmax(i > 0 ? se2[i - 1] * sc * sc : 0.0, kSturmE2));
+    const double e2 = i > 0 ? se2[i - 1] * sc * sc : 1.0;
+    floored |= below_floor(e2);
+    sde[i] = make_double2(sd[i] * sc, fmax(e2, kSturmE2));
   }
   gl = gl * sc - 2.0 * eps * tn - DBL_MIN;
   gu = gu * sc + 2.0 * eps * tn + DBL_MIN;
@@ -553,7 +556,8 @@ __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *
   // subintervals, which replaces the first ~8 bisection steps of every lane
   __shared__ int s_cnt[PT];
   const double hstep = (gu - gl) / double(PT + 1);
-  __syncthreads();
+  const bool low = __syncthreads_or(floored);  // T splits
+  const double pivmin = DBL_MIN * fmax(1.0, tnorm * tnorm);
   s_cnt[tid] = sturm_count_p(sde, N, gl + double(tid + 1) * hstep);
   __syncthreads();
   const int nidx = m + 4;
@@ -570,12 +574,16 @@ __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *
       int u = 0;
       while (u < PT && s_cnt[u] <= k) ++u;
       double a = u == 0 ? gl : gl + double(u) * hstep, b = u == PT ? gu : gl + double(u + 1) * hstep;
-      bool conv = false;
+      bool conv = false, fine = false;
       for (int it = 0; it <= max_it; ++it) {
+        if (low && !fine) fine = widen_low(a, b, tn);
         const double mid = 0.5 * (a + b);
         conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + DBL_MIN, tol_abs) || mid <= a || mid >= b;
         if (conv || it == max_it) break;
-        if ((b - a > qwidth ? sturm_count_p(sde, N, mid) : sturm_count_i(sde, N, mid)) > k) b = mid;
+        const int cnt = fine             ? sturm_count(sd, se2, N, mid * isc, pivmin)
+                        : b - a > qwidth ? sturm_count_p(sde, N, mid)
+                                         : sturm_count_i(sde, N, mid);
+        if (cnt > k) b = mid;
         else a = mid;
       }
       if (!conv) atomicOr(&status[q], BE_ST_NONCONVERGED);

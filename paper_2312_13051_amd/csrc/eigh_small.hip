@@ -387,9 +387,13 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int l
   const double tnorm = fmax(fabs(gl), fabs(gu)), pivmin = DBL_MIN * fmax(1.0, emax2);
   const double sc = sturm_scale(tnorm), isc = 1.0 / sc, tn = tnorm * sc;
   double2 de[NM];  // the scaled pairs, every lane of the matrix all of them
+  bool low = false;  // T splits
 #pragma unroll
-  for (int i = 0; i < NM; ++i)
-    de[i] = i < N ? make_double2(sd[i] * sc, fmax(i > 0 ? se2[i - 1] * sc * sc : 0.0, kSturmE2)) : sturm_pad();
+  for (int i = 0; i < NM; ++i) {
+    const double e2 = i > 0 && i < N ? se2[i - 1] * sc * sc : 1.0;
+    low = low || below_floor(e2);
+    de[i] = i < N ? make_double2(sd[i] * sc, fmax(e2, kSturmE2)) : sturm_pad();
+  }
   gl = gl * sc - 2.0 * eps * tn - DBL_MIN;
   gu = gu * sc + 2.0 * eps * tn + DBL_MIN;
   const double tol_abs = eps * eps * tn;
@@ -399,12 +403,16 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int l
     double val = NAN;
     if (k >= 0) {
       double a = gl, b = gu;
-      bool conv = false;
+      bool conv = false, fine = false;
       for (int it = 0; it <= max_it; ++it) {
+        if (low && !fine) fine = widen_low(a, b, tn);
         const double mid = 0.5 * (a + b);
         conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + DBL_MIN, tol_abs) || mid <= a || mid >= b;
         if (conv || it == max_it) break;
-        if ((FULL || b - a > kQuotientWidth ? sturm_count_p(de, mid) : sturm_count_i(de, mid)) > k) b = mid;
+        const int cnt = fine                                ? sturm_count(sd, se2, N, mid * isc, pivmin)
+                        : FULL || b - a > kQuotientWidth ? sturm_count_p(de, mid)
+                                                         : sturm_count_i(de, mid);
+        if (cnt > k) b = mid;
         else a = mid;
       }
       if (!conv) st |= BE_ST_NONCONVERGED;

@@ -138,6 +138,19 @@ __device__ __forceinline__ int sturm_count_i(const double2 (&de)[NM], double x) 
 // 11.0 -> 7.65 ms).
 constexpr double kQuotientWidth = 0x1p-38;
 
+// Couplings below the minors' floor are raised to it there, which moves a level by
+// up to 2e-18 ||T||: below the rounding of the levels themselves down to 2^-6 ||T||,
+// but not of the levels near zero of a T that splits. From kQuotientWidth on those
+// are found by quotients on T as it is, in an interval wide enough for that move.
+constexpr double kLowLevel = 0x1p-6, kLowMove = 8e-18;  // relative to the norm tn of a T scaled as above
+__device__ __forceinline__ bool below_floor(double e2) { return e2 < kSturmE2; }
+__device__ __forceinline__ bool widen_low(double &a, double &b, double tn) {
+  if (b - a > kQuotientWidth || fmax(fabs(a), fabs(b)) > kLowLevel) return false;
+  a -= kLowMove * tn;
+  b += kLowMove * tn;
+  return true;
+}
+
 // Power of two that takes a norm into [1/2, 1) (1 for a zero or non-finite norm;
 // at most 2^1000, so that a norm among the subnormal numbers has a finite one)
 __device__ __forceinline__ double sturm_scale(double tnorm) {

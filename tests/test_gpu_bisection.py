@@ -35,3 +35,36 @@ def test_eigenvalues(N, kind, scale):
         c.close()
     w = np.linalg.eigvalsh(H[0])
     assert np.abs(ev[0, 1:-1] / scale - w).max() <= 3 * N * np.finfo(float).eps * np.abs(w).max()
+
+
+# levels far below the norm whose rows couple to the rest by nothing, and among themselves by less than the rounding of the
+# norm. The reduction passes these real tridiagonal matrices through, so each block's levels are found to the block's own
+# backward error or to the bisection's floor, eps^2 ||H||
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("N", [4, 8, 9, 16, 17, 32, 40, 300])
+def test_levels_of_decoupled_blocks(N, precision):
+    gu.need_gpu()
+    from paper_2312_13051_amd import _lib as L
+    mixed, n1 = precision == "mixed", N // 2
+    rng = np.random.default_rng([N, 8])
+    blocks = [tridiagonal(n, "random", rng).astype(np.float32).astype(float) for n in (n1, N - n1)]
+    small = 2.0 ** -66
+    H = np.zeros((N, N))
+    H[:n1, :n1], H[n1:, n1:] = blocks[0], blocks[1] * small
+    c = gu.ctx()
+    try:
+        dH = gu.from_np(H.astype(complex)[None], N, torch.complex64 if mixed else torch.complex128)
+        U = gu.colmajor(1, N, N, N, fill=0)
+        ev = torch.empty((1, N + 2), dtype=torch.float64, device="cuda")
+        st = torch.empty(1, dtype=torch.int32, device="cuda")
+        c.eigh_batched(dH, L.BE_C64 if mixed else L.BE_C128, N, N, dH.stride(0), 1, 0, N,
+                       L.BE_MIXED_FP32 if mixed else L.BE_FP64, ev, U, N, U.stride(0), st)
+        got = ev[0, 1:-1].cpu().numpy()
+    finally:
+        c.close()
+    eps = np.finfo(float).eps
+    w1, w2 = (np.linalg.eigvalsh(b) for b in blocks)
+    n0 = int((w1 < 0).sum())
+    near, far = got[n0:n0 + w2.size], np.concatenate([got[:n0], got[n0 + w2.size:]])
+    assert np.abs(far - w1).max() <= 3 * N * eps * np.abs(w1).max()
+    assert np.abs(near - w2 * small).max() <= 3 * N * eps * np.abs(w2).max() * small + 4 * eps ** 2 * np.abs(w1).max()
