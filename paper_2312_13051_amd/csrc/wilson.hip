@@ -946,19 +946,26 @@ __global__ __launch_bounds__(256) void k_herm_of_unitary(const double2 *W, int m
   }
 }
 
-// Phases from the eigenpairs of A. c_n (the eigenvalue, from bisection:
-// complete and accurate whatever the vectors) fixes |theta_n - phi| =
-// acos(c_n); s_n = Im(e^{-i phi} v_n^H (W v_n)) gives the sign. A vector
-// inside a cluster of nearly equal phases may be any mix of the cluster's
-// eigenvectors (W matrices of disordered supercells hold hundreds of phases
-// within 1e-9 of 0): its s_n keeps the common sign and |s_n| stays at
-// sqrt(1 - c_n^2), which is checked (a mix of a pair theta, 2 phi - theta
-// would break it). Within 0.05 of the branch points (sin ~ 0), and whenever
-// eigenvectors are returned, theta_n = phi + atan2(s_n, c_n) from a vector
-// whose residual |W v - e^{i theta} v| must be below 1e-10 (and the
-// eigensolver's status clear); above it the cosine serves down to |sin| = 0.005. Ascending sort; optional raw phases and
-// eigenvectors. One workgroup per matrix, a wave per column. fb[q] = 1 where
-// the QR kernel must take over.
+// Phases from the eigenpairs of A. W is a product of polar factors, unitary to
+// some 1e-14 per link: W = rho U with rho_n = |W v_n| / |v_n| to the second order
+// in that, whatever mix of eigenvectors v_n is. c_n (the eigenvalue, from
+// bisection: complete and accurate whatever the vectors) over rho_n fixes
+// |theta_n - phi| = acos(c_n / rho_n), which loses eps / |sin|; s_n =
+// Im(e^{-i phi} v_n^H (W v_n)) gives the sign, and atan2(s_n, c_n) the phase to
+// eps where v_n is an eigenvector. A vector inside a cluster of nearly equal
+// phases may be any mix of the cluster's eigenvectors (W matrices of disordered
+// supercells hold hundreds of phases within 1e-9 of 0): its s_n keeps the common
+// sign and |s_n| stays at rho sin, which is checked (a mix of a pair theta, 2 phi
+// - theta would break it), but its quotient is a mean of the cluster's phases.
+// Hence atan2 wherever it lies within the cosine's own uncertainty of acos (8 eps
+// / |sin|), else acos. On the CPU, orders 13 to 200, W unitary to 1e-13: without
+// rho, cosines alone, 4e-12 to 1e-11 off; so 4e-16 to 2e-14, and 1e-13 in crowds
+// of phases 3e-14 apart and in pairs. Within 0.005 of the branch points (sin ~ 0),
+// and whenever eigenvectors are returned, theta_n = phi + atan2(s_n, c_n) from a
+// vector whose residual |W v - e^{i theta} v| must be below 1e-10 (and the
+// eigensolver's status clear). Ascending sort; optional raw phases and
+// eigenvectors. One workgroup per matrix, a wave per column. fb[q] = 1 where the
+// QR kernel must take over.
 __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uint32_t *est, const double2 *V,
                                                      const double2 *WV, int m, int64_t n_mat, double *theta_sorted,
                                                      int ldt, double *theta_raw, double2 *Zout, int *fb) {
@@ -975,29 +982,36 @@ __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uin
   __syncthreads();
   for (int n = wave; n < m; n += 4) {
     const double2 *v = Vq + int64_t(n) * m, *g = Gq + int64_t(n) * m;
-    double pr = 0.0, pi = 0.0, vv = 0.0;
+    double pr = 0.0, pi = 0.0, vv = 0.0, ww = 0.0;
     for (int r = lane; r < m; r += 64) {
       const double2 a = v[r], b = g[r];
       pr += a.x * b.x + a.y * b.y;
       pi += a.x * b.y - a.y * b.x;
       vv += a.x * a.x + a.y * a.y;
+      ww += b.x * b.x + b.y * b.y;
     }
     for (int o = 32; o > 0; o >>= 1) {
       pr += __shfl_xor(pr, o, 64);
       pi += __shfl_xor(pi, o, 64);
       vv += __shfl_xor(vv, o, 64);
+      ww += __shfl_xor(ww, o, 64);
     }
     // Im(e^{-i phi} v^H W v) / v^H v (the vectors of a crowd of nearly equal
-    // phases need not come out normalized)
-    const double s = (cs * pi - sn * pr) / vv;
-    const double c = fmin(1.0, fmax(-1.0, ev[q * (m + 2) + 1 + n]));
+    // phases need not come out normalized), and both parts over rho
+    const double rho = sqrt(ww / vv), s = (cs * pi - sn * pr) / (vv * rho);
+    const double c = fmin(1.0, fmax(-1.0, ev[q * (m + 2) + 1 + n] / rho));
     const double sabs = sqrt(fmax(0.0, 1.0 - c * c));
-    const bool by_cos = !vectors && sabs >= 0.05;
-    double th = kHermShift + (by_cos ? copysign(acos(c), s) : atan2(s, c));
+    const bool by_cos = !vectors && sabs >= 0.005;
+    double x = atan2(s, c);
+    if (by_cos) {
+      const double ac = copysign(acos(c), s);
+      if (!(fabs(x - ac) <= 8.0 * DBL_EPSILON / sabs)) x = ac;
+    }
+    double th = kHermShift + x;
     if (th > M_PI) th -= 2.0 * M_PI;
     bool bad = !(th == th);
     if (by_cos) {
-      bad = bad || !(fabs(fabs(s) - sabs) <= 1e-3);
+      bad = bad || !(fabs(rho - 1.0) <= 1e-3) || !(fabs(fabs(s) - sabs) <= fmin(1e-3, 0.02 * sabs));
     } else {
       const double er = cos(th), ei = sin(th);
       double res = 0.0;
@@ -1007,18 +1021,7 @@ __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uin
         res += dx * dx + dy * dy;
       }
       for (int o = 32; o > 0; o >>= 1) res += __shfl_xor(res, o, 64);
-      if (!(res <= 1e-20)) {  // |W v - e^{i theta} v| > 1e-10, or NaN
-        // two phases on either side of the branch point whose cosines nearly
-        // agree (to ~1e-6) mix in the vectors at that level; the cosines are
-        // accurate whatever the vectors, so away from the point itself they give
-        // the phase (error ~eps / |sin|) and the vector its sign
-        if (!vectors && sabs >= 0.005 && fabs(fabs(s) - sabs) <= 0.1 * sabs) {
-          th = kHermShift + copysign(acos(c), s);
-          if (th > M_PI) th -= 2.0 * M_PI;
-        } else {
-          bad = true;
-        }
-      }
+      bad = bad || !(res <= 1e-20);  // |W v - e^{i theta} v| > 1e-10, or NaN
     }
     if (lane == 0) {
       sth[n] = th;

@@ -63,3 +63,52 @@ def test_chosen_phases(m, kind):
 @pytest.mark.parametrize("kind", ["spread", "crowd"])
 def test_few_large_orders(m, kind):
     test_chosen_phases(m, kind)
+
+
+def round_loop(theta, n_par, seed):
+    """A closed line of n_par points whose Wilson matrix has the given phases: in a common random basis, each band's two
+    components go round a circle, (sqrt(1 - p), sqrt(p) e^{i delta j}), delta = 2 pi / n_par, with the p whose links have the
+    phase theta / n_par. All links are well conditioned (singular values from cos(pi / n_par) up)."""
+    m = theta.size
+    rng = np.random.default_rng(seed)
+    V = np.linalg.qr(rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m)))[0]
+    delta = 2 * np.pi / n_par
+    t = np.tan(np.abs(theta) / n_par)
+    p = t / (np.sin(delta) + t * (1 - np.cos(delta)))
+    return np.stack([np.concatenate([(V * np.sqrt(1 - p)) @ V.conj().T,
+                                     (V * (np.sqrt(p) * np.exp(-1j * np.sign(theta) * delta * j))) @ V.conj().T])
+                     for j in range(n_par)])
+
+
+# phases 0.05 to 0.06 from the branch point of the Hermitian problem, on either side, where a phase from the cosine alone is off
+# by eps / |sin| and the cosine's own errors, and well-separated ones: as near as the matrices are unitary, to about 100 eps
+@pytest.mark.parametrize("m", [12, 13, 16, 33, 48, 64, 100])
+@pytest.mark.parametrize("kind", ["near", "spread"])
+def test_phases_to_rounding(m, kind):
+    gu.need_gpu()
+    rng = np.random.default_rng([m, len(kind), 5])
+    lines = []
+    for _ in range(8):
+        th = rng.uniform(-1.4, 1.4, m)
+        if kind == "near":
+            th[:m // 2] = PHI + rng.choice([-1.0, 1.0], m // 2) * rng.uniform(0.05, 0.06, m // 2)
+        lines.append(th)
+    got, status = loop_phases(np.stack([round_loop(th, 16, [m, q, 5]) for q, th in enumerate(lines)]))
+    assert status & ~4 == 0
+    assert phase_set_error(got, np.array(lines)) < 100 * np.finfo(float).eps
+
+
+def loop_phases(U):
+    """Phases and status of one system's Wilson loops over the lines of U (line, point, N, m)."""
+    n_perp, n_par, N, m = U.shape
+    f8 = dict(dtype=torch.float64, device="cuda")
+    i4 = dict(dtype=torch.int32, device="cuda")
+    c = gu.ctx()
+    try:
+        Ud = gu.from_np(U.reshape(-1, N, m), N)
+        out, phi = torch.empty((1, n_perp, m), **f8), torch.empty((1, n_perp), **f8)
+        wn, st = torch.empty(1, **i4), torch.empty(1, **i4)
+        c.wilson_loop(Ud, N, m, N, Ud.stride(0), 1, n_par, n_perp, 0, out, phi, wn, st)
+        return out[0].cpu().numpy(), int(st[0])
+    finally:
+        c.close()
