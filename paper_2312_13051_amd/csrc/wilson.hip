@@ -956,7 +956,9 @@ __global__ __launch_bounds__(256) void k_herm_of_unitary(const double2 *W, int m
 // phases may be any mix of the cluster's eigenvectors (W matrices of disordered
 // supercells hold hundreds of phases within 1e-9 of 0): its s_n keeps the common
 // sign and |s_n| stays at rho sin, which is checked (a mix of a pair theta, 2 phi
-// - theta would break it), but its quotient is a mean of the cluster's phases.
+// - theta would break it), but its quotient is a mean of the cluster's phases. A
+// rho more than 1e-9 from one is a line whose links did not converge: its W is
+// not normal, and A's eigenvectors are not W's.
 // Hence atan2 wherever it lies within the cosine's own uncertainty of acos (8 eps
 // / |sin|), else acos. On the CPU, orders 13 to 200, W unitary to 1e-13: without
 // rho, cosines alone, 4e-12 to 1e-11 off; so 4e-16 to 2e-14, and 1e-13 in crowds
@@ -1011,7 +1013,7 @@ __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uin
     if (th > M_PI) th -= 2.0 * M_PI;
     bool bad = !(th == th);
     if (by_cos) {
-      bad = bad || !(fabs(rho - 1.0) <= 1e-3) || !(fabs(fabs(s) - sabs) <= fmin(1e-3, 0.02 * sabs));
+      bad = bad || !(fabs(rho - 1.0) <= 1e-9) || !(fabs(fabs(s) - sabs) <= fmin(1e-3, 0.02 * sabs));
     } else {
       const double er = cos(th), ei = sin(th);
       double res = 0.0;

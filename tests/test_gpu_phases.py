@@ -112,3 +112,34 @@ def loop_phases(U):
         return out[0].cpu().numpy(), int(st[0])
     finally:
         c.close()
+
+
+def newton_schulz(F):
+    """The polar iteration of the loops' links: at most 51 steps of X (3 I - X^H X) / 2."""
+    eye = np.eye(F.shape[0])
+    for _ in range(51):
+        G = F.conj().T @ F
+        err = np.abs(G - eye).max()
+        F = F @ (1.5 * eye - 0.5 * G)
+        if err < 1e-7:
+            break
+    return F
+
+
+# a link with a singular value that 51 steps take to 0.45, 0.9995 or 0.99994: the line is flagged, its W is neither unitary
+# nor normal, and its phases are the arguments of W's eigenvalues. The value is uncertain by the rounding of the link's
+# entries, 2 m eps relative to the value at the start, and the phases with it
+@pytest.mark.parametrize("m", [12, 13, 48, 100, 101])
+@pytest.mark.parametrize("smin", [5e-10, 3e-9, 3.5e-9])
+def test_link_not_converged(m, smin):
+    gu.need_gpu()
+    rng = np.random.default_rng([m, 6])
+    P, Q, P2, Q2 = (np.linalg.qr(rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m)))[0] for _ in range(4))
+    s = np.r_[smin, np.ones(m - 1)]
+    U = np.stack([np.concatenate([np.eye(m), np.zeros((m, m))]),
+                  np.concatenate([(P * s) @ Q.conj().T, (Q * np.sqrt(1 - s * s)) @ Q.conj().T]),
+                  np.concatenate([0.8 * P2 @ Q2.conj().T, 0.6 * np.eye(m)])])[None]
+    F = [newton_schulz(U[0, (j + 1) % 3].conj().T @ U[0, j]) for j in range(3)]
+    got, status = loop_phases(U)
+    assert status & 2
+    assert phase_set_error(got, np.angle(np.linalg.eigvals(F[2] @ F[1] @ F[0]))[None]) < 2 * m * np.finfo(float).eps / smin
