@@ -323,8 +323,8 @@ int noalloc_scratch_init(be_ctx *ctx, int device);
 // Batched eigensolver for bands [band_lo, band_hi) (uses slot WS_EIGH): FP64,
 // or mixed (c64 input, FP32 reduction and back-transformation, FP64
 // tridiagonal solve and orthonormalization, c128 eigenvectors out). columns: few
-// large matrices may be reduced by column launches (other rounding than the
-// panel kernel, so a result then depends on the size of its batch).
+// large matrices are reduced by column launches (the panel kernel's results, bit
+// for bit).
 int eigh_fp64(be_ctx *ctx, double2 *H, int N, int ld, int64_t mat_stride, int64_t n_mat, int band_lo, int band_hi,
               double *evals, double2 *U, int ldu, int64_t u_stride, uint32_t *status, hipStream_t stream,
               double clu_rel = 1e-12, bool columns = false);

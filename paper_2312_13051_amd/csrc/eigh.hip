@@ -1142,11 +1142,15 @@ size_t panel_lds(int N, size_t csize, int nt) {
 // The panel kernel gives a matrix one workgroup, which reads its trailing
 // matrix at the rate of one compute unit. Where there are few (the Hermitian
 // problems of a dozen lines' Wilson matrices), each column's matrix-vector product is
-// spread over the device instead (few_matvec: the panel kernel's tiles and
-// slots, a wave per tile) and the rest of the column follows in one workgroup
+// spread over the device instead (few_matvec: the panel kernel's items and
+// slots, a wave per item) and the rest of the column follows in one workgroup
 // per matrix (few_column: the panel kernel's steps 4, 5 and, for the next
-// column, 1 and 2), two launches per column. Bound by the launches and by the
-// passes over V and W in one workgroup. Panels before -> so: 12 matrices of
+// column, 1 and 2), two launches per column. The sums run over the same terms in
+// the same order as the panel kernel's of nt threads, and the products that the
+// compiler fuses there are written as fma here: a matrix keeps its bits (the tests
+// compare them), so the choice may depend on what else a call holds.
+// Bound by the launches and by the passes over V and W in one workgroup. Panels
+// before -> so: 12 matrices of
 // order 1152 163 -> 34 ms, 4 of 2304 857 -> 96, 16 of 512 20.9 -> 9.0.
 __global__ __launch_bounds__(256) void few_matvec(const double2 *A, int64_t sA, int lda, int N, int j, const double2 *Vj,
                                                   int64_t sVW, double2 *part, int64_t sP) {
@@ -1155,19 +1159,21 @@ __global__ __launch_bounds__(256) void few_matvec(const double2 *A, int64_t sA, 
   const double2 *Aq = A + q * sA, *v = Vj + q * sVW;
   double2 *pq = part + q * sP;
   const int lane = threadIdx.x & 63;
-  const int r0 = j + 1, nrb = (N - r0 + 63) >> 6, nslot = nrb + 1, ntile = nrb * (nrb + 1) / 2;
-  for (int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); t < ntile; t += gridDim.x * 4) {
+  const int r0 = j + 1, nrb = (N - r0 + 63) >> 6, S = panel_split(nrb), gw = 64 / S, nslot = nrb * S + 1;
+  const int nitem = nrb * (nrb + 1) / 2 * S;
+  for (int it = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); it < nitem; it += gridDim.x * 4) {
+    const int t = it / S, g = it - t * S;
     int bi = 0, bj = t;
     while (bj > bi) {
       bj -= bi + 1;
       ++bi;
     }
-    const int r = r0 + 64 * bi + lane, rc = min(r, N - 1), cb = r0 + 64 * bj;
+    const int r = r0 + 64 * bi + lane, rc = min(r, N - 1), cb = r0 + 64 * bj + g * gw;
     const double2 vr = r < N ? v[rc] : make_double2(0.0, 0.0);
     const double2 vl = v[min(cb + lane, N - 1)];  // of column cb + lane
-    double2 *pcol = pq + (bj * nslot + (bj + 1) + (bi - bj)) * 64;
+    double2 *pcol = pq + (bj * nslot + (bj + 1) * S + (bi - bj)) * 64 + g * gw;
     double yr = 0.0, yi = 0.0;
-    for (int k = 0; k < 64 && cb + k < N; k += CW) {
+    for (int k = 0; k < gw && cb + k < N; k += CW) {
       double2 a[CW];
 #pragma unroll
       for (int u = 0; u < CW; ++u) {  // entries above the diagonal or past the matrix are masked below
@@ -1178,37 +1184,41 @@ __global__ __launch_bounds__(256) void few_matvec(const double2 *A, int64_t sA, 
       for (int u = 0; u < CW; ++u) {
         const int c = cb + k + u;
         const bool use = c < N && r < N && r >= c, dg = r == c;
-        const double vx = __shfl(vl.x, k + u, 64), vy = __shfl(vl.y, k + u, 64);
+        const double2 vc = make_double2(__shfl(vl.x, k + u, 64), __shfl(vl.y, k + u, 64));
         const double ax = use ? a[u].x : 0.0, ay = use && !dg ? a[u].y : 0.0;
-        yr += ax * vx - ay * vy;
-        yi += ax * vy + ay * vx;
-        a[u] = dg ? make_double2(0.0, 0.0) : make_double2(ax * vr.x + ay * vr.y, ax * vr.y - ay * vr.x);
+        yr += fma(ax, vc.x, -(ay * vc.y));
+        yi += fma(ay, vc.x, ax * vc.y);
+        a[u] = dg ? make_double2(0.0, 0.0) : make_double2(fma(ax, vr.x, ay * vr.y), fma(ax, vr.y, -(ay * vr.x)));
       }
       const double2 sc = xpose_colsum<CW>(a, lane);
       if ((lane & ((1 << CSH) - 1)) == 0) pcol[k + (lane >> CSH)] = sc;
     }
-    pq[(bi * nslot + bj) * 64 + lane] = make_double2(yr, yi);
+    pq[(bi * nslot + bj * S + g) * 64 + lane] = make_double2(yr, yi);
   }
 }
 
 constexpr int FT = 1024;  // threads of few_column
 
 // Reflector of column j, whose updated entries r >= j are in sx: d, e, tau (T's
-// diagonal) and v (A's column, V, V2).
+// diagonal) and v (A's column, V, V2). nt: threads whose sums the norm takes.
 __device__ void few_reflect(double2 *Aq, int lda, int N, int j, double2 *Vj, double2 *V2j, double2 *Tjj, double *dj,
-                            double *ej, const double2 *sx, double *red) {
+                            double *ej, const double2 *sx, double *red, int nt) {
   const int tid = threadIdx.x;
   double xn = 0.0, dummy = 0.0;
-  for (int r = j + 2 + tid; r < N; r += FT) xn += sx[r].x * sx[r].x + sx[r].y * sx[r].y;
+  for (int r = tid < nt ? j + 2 + tid : N; r < N; r += nt) {
+    const double2 a = sx[r];
+    xn += fma(a.x, a.x, a.y * a.y);
+  }
   block_sum2(xn, dummy, red);
   const double2 alpha = sx[j + 1];
   double2 tau = make_double2(0.0, 0.0), scal = tau;
   double beta = alpha.x;
   if (!(xn == 0.0 && alpha.y == 0.0)) {
-    const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn);
+    const double nrm = sqrt(fma(alpha.x, alpha.x, alpha.y * alpha.y) + xn);
     beta = alpha.x >= 0.0 ? -nrm : nrm;
     tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
-    const double dr = alpha.x - beta, di = alpha.y, den = dr * dr + di * di;
+    const double dr = alpha.x - beta, di = alpha.y;
+    const double den = fma(dr, dr, di * di);
     scal = make_double2(dr / den, -di / den);
   }
   if (tid == 0) {
@@ -1217,9 +1227,10 @@ __device__ void few_reflect(double2 *Aq, int lda, int N, int j, double2 *Vj, dou
     *Tjj = tau;
   }
   for (int r = tid; r < N; r += FT) {
+    const double2 a = r > j ? sx[r] : make_double2(0.0, 0.0);
     const double2 v = r <= j       ? make_double2(0.0, 0.0)
                       : r == j + 1 ? make_double2(1.0, 0.0)
-                                   : be::cmul(sx[r], scal);
+                                   : make_double2(fma(a.x, scal.x, -(a.y * scal.y)), fma(a.x, scal.y, a.y * scal.x));
     Aq[r + int64_t(j) * lda] = v;
     Vj[r] = v;
     V2j[r] = v;
@@ -1231,7 +1242,7 @@ __device__ void few_reflect(double2 *Aq, int lda, int N, int j, double2 *Vj, dou
 // update and reflector.
 __global__ __launch_bounds__(FT) void few_column(double2 *A, int64_t sA, int lda, int N, int p0, int jj, double2 *VW,
                                                  int64_t sVW, double2 *Tm, int64_t sTm, double *d, double *e, int64_t sDE,
-                                                 const double2 *part, int64_t sP) {
+                                                 const double2 *part, int64_t sP, int nt) {
   extern __shared__ double2 fsm[];
   double2 *sv = fsm, *sy = sv + N, *st1 = sy + N, *st2 = st1 + NB, *sVr = st2 + NB, *sWr = sVr + NB;
   double *red = reinterpret_cast<double *>(sWr + NB);
@@ -1247,10 +1258,10 @@ __global__ __launch_bounds__(FT) void few_column(double2 *A, int64_t sA, int lda
       sv[r] = a;
     }
     __syncthreads();
-    few_reflect(Aq, lda, N, p0, V, V2, T, dq + p0, eq + p0, sv, red);
+    few_reflect(Aq, lda, N, p0, V, V2, T, dq + p0, eq + p0, sv, red, nt);
     return;
   }
-  const int j = p0 + jj, r0 = j + 1, nrb = (N - r0 + 63) >> 6, nslot = nrb + 1;
+  const int j = p0 + jj, r0 = j + 1, nrb = (N - r0 + 63) >> 6, S = panel_split(nrb), nslot = nrb * S + 1;
   const double2 *pq = part + q * sP, tau = T[jj + jj * NB];
   for (int c = tid; c < jj; c += FT) {
     sVr[c] = V[r0 + int64_t(c) * N];
@@ -1258,58 +1269,78 @@ __global__ __launch_bounds__(FT) void few_column(double2 *A, int64_t sA, int lda
   }
   for (int r = r0 + tid; r < N; r += FT) {
     sv[r] = V[r + int64_t(jj) * N];
-    const double2 *pb = pq + ((r - r0) >> 6) * nslot * 64 + ((r - r0) & 63);
-    double2 y = make_double2(0.0, 0.0);
+    const int b = (r - r0) >> 6, ns = (b + 1) * S + nrb - b;
+    const double2 *pb = pq + int64_t(b) * nslot * 64 + ((r - r0) & 63);
+    double sr = 0.0, si = 0.0;
 #pragma unroll 8
-    for (int t = 0; t < nslot; ++t) y = be::cadd(y, pb[t * 64]);
-    sy[r] = y;
+    for (int t = 0; t < ns; ++t) {  // row slots, then column slots
+      const double2 x = pb[t * 64];
+      sr += x.x;
+      si += x.y;
+    }
+    sy[r] = make_double2(sr, si);
   }
   __syncthreads();
   for (int c = wave; c < jj; c += FT / 64) {  // t1 = W^H v, t2 = V^H v
-    double2 a = make_double2(0.0, 0.0), b = a;
+    double a_r = 0.0, a_i = 0.0, b_r = 0.0, b_i = 0.0;
 #pragma unroll 4
     for (int r = r0 + lane; r < N; r += 64) {
-      const double2 v = sv[r];
-      a = be::cadd(a, be::cmulc(W[r + int64_t(c) * N], v));
-      b = be::cadd(b, be::cmulc(V[r + int64_t(c) * N], v));
+      const double2 v = sv[r], w = W[r + int64_t(c) * N], vv = V[r + int64_t(c) * N];
+      a_r += fma(w.x, v.x, w.y * v.y);
+      a_i += fma(w.x, v.y, -(w.y * v.x));
+      b_r += fma(vv.x, v.x, vv.y * v.y);
+      b_i += fma(vv.x, v.y, -(vv.y * v.x));
     }
-    a.x = wave_sum(a.x);
-    a.y = wave_sum(a.y);
-    b.x = wave_sum(b.x);
-    b.y = wave_sum(b.y);
+    a_r = wave_sum(a_r);
+    a_i = wave_sum(a_i);
+    b_r = wave_sum(b_r);
+    b_i = wave_sum(b_i);
     if (lane == 0) {
-      st1[c] = a;
-      st2[c] = b;
+      st1[c] = make_double2(a_r, a_i);
+      st2[c] = make_double2(b_r, b_i);
     }
   }
   __syncthreads();
   const bool next = jj + 1 < NB;
-  double dr = 0.0, di = 0.0;
   for (int r = r0 + tid; r < N; r += FT) {  // y -= V t1 + W t2, w = tau y; the earlier reflectors' share of column j + 1
-    double2 y = sy[r], p = make_double2(0.0, 0.0);
+    const double2 y = sy[r];
+    double yr = y.x, yi = y.y, pr = 0.0, pi = 0.0;
 #pragma unroll 4
     for (int c = 0; c < jj; ++c) {
-      const double2 vv = V[r + int64_t(c) * N], w = W[r + int64_t(c) * N];
-      y = be::csub(y, be::cadd(be::cmul(vv, st1[c]), be::cmul(w, st2[c])));
-      p = be::cadd(p, be::cadd(be::cmulc(sWr[c], vv), be::cmulc(sVr[c], w)));
+      const double2 vv = V[r + int64_t(c) * N], w = W[r + int64_t(c) * N], a = st1[c], b = st2[c];
+      yr -= fma(-w.y, b.y, fma(w.x, b.x, fma(vv.x, a.x, -(vv.y * a.y))));
+      yi -= fma(w.y, b.x, fma(w.x, b.y, fma(vv.y, a.x, vv.x * a.y)));
+      const double2 wj = sWr[c], vj = sVr[c];
+      pr += fma(w.y, vj.y, fma(w.x, vj.x, fma(vv.x, wj.x, vv.y * wj.y)));
+      pi += fma(-w.x, vj.y, fma(w.y, vj.x, fma(vv.y, wj.x, -(vv.x * wj.y))));
     }
-    y = be::cmul(tau, y);
-    sy[r] = y;
-    const double2 v = sv[r];
-    dr += y.x * v.x + y.y * v.y;
-    di += y.x * v.y - y.y * v.x;
-    if (next) Aq[r + int64_t(r0) * lda] = be::csub(Aq[r + int64_t(r0) * lda], p);
+    sy[r] = make_double2(fma(tau.x, yr, -(tau.y * yi)), fma(tau.x, yi, tau.y * yr));
+    if (next) {
+      const double2 a0 = Aq[r + int64_t(r0) * lda];
+      Aq[r + int64_t(r0) * lda] = make_double2(a0.x - pr, a0.y - pi);
+    }
   }
   if (tid < jj) {  // T(0:jj, jj) = -tau T(0:jj, 0:jj) t2
-    double2 x = make_double2(0.0, 0.0);
-    for (int c = tid; c < jj; ++c) x = be::cadd(x, be::cmul(T[tid + c * NB], st2[c]));
-    x = be::cmul(tau, x);
-    T[tid + jj * NB] = make_double2(-x.x, -x.y);
+    double xr = 0.0, xi = 0.0;
+    for (int c = tid; c < jj; ++c) {
+      const double2 tt = T[tid + c * NB], b = st2[c];
+      xr += fma(tt.x, b.x, -(tt.y * b.y));
+      xi += fma(tt.y, b.x, tt.x * b.y);
+    }
+    T[tid + jj * NB] = make_double2(-fma(tau.x, xr, -(tau.y * xi)), -fma(tau.y, xr, tau.x * xi));
+  }
+  __syncthreads();
+  double dr = 0.0, di = 0.0;
+  for (int r = tid < nt ? r0 + tid : N; r < N; r += nt) {
+    const double2 w = sy[r], v = sv[r];
+    dr += fma(w.x, v.x, w.y * v.y);
+    di += fma(w.x, v.y, -(w.y * v.x));
   }
   block_sum2(dr, di, red);
-  const double2 al = make_double2(-0.5 * (tau.x * dr - tau.y * di), -0.5 * (tau.x * di + tau.y * dr));
+  const double alr = -0.5 * fma(tau.x, dr, -(tau.y * di)), ali = -0.5 * fma(tau.y, dr, tau.x * di);
   for (int r = r0 + tid; r < N; r += FT) {  // w += alpha v, alpha = -tau (w^H v) / 2
-    const double2 w = be::cadd(sy[r], be::cmul(al, sv[r]));
+    const double2 y = sy[r], v = sv[r];
+    const double2 w = make_double2(fma(-ali, v.y, fma(alr, v.x, y.x)), fma(ali, v.x, fma(alr, v.y, y.y)));
     W[r + int64_t(jj) * N] = w;
     sy[r] = w;
   }
@@ -1318,13 +1349,14 @@ __global__ __launch_bounds__(FT) void few_column(double2 *A, int64_t sA, int lda
   const double2 wj = sy[r0], vj = sv[r0];
   __syncthreads();
   for (int r = r0 + tid; r < N; r += FT) {
-    double2 a = be::csub(Aq[r + int64_t(r0) * lda], be::cadd(be::cmulc(wj, sv[r]), be::cmulc(vj, sy[r])));
-    if (r == r0) a.y = 0.0;
-    sv[r] = a;
+    const double2 a = Aq[r + int64_t(r0) * lda], vr = sv[r], wr = sy[r];
+    const double ar = a.x - fma(wr.y, vj.y, fma(wr.x, vj.x, fma(vr.x, wj.x, vr.y * wj.y)));
+    const double ai = a.y - fma(-wr.x, vj.y, fma(wr.y, vj.x, fma(vr.y, wj.x, -(vr.x * wj.y))));
+    sv[r] = make_double2(ar, r == r0 ? 0.0 : ai);
   }
   __syncthreads();
   few_reflect(Aq, lda, N, r0, V + int64_t(jj + 1) * N, V2 + int64_t(jj + 1) * N, T + (jj + 1) * (NB + 1), dq + r0, eq + r0,
-              sv, red);
+              sv, red, nt);
 }
 
 template <typename T>
@@ -1544,27 +1576,27 @@ static int panels_before_resident(int N) { return N <= kResidentOrder ? 0 : (N -
 // Few matrices: at most three panel workgroups for eight compute units (panels,
 // panel kernel -> column launches: 96 matrices of order 288 3.15 -> 3.16 ms, 400
 // 8.06 -> 6.96, 1024 122 -> 84; 128 of 288 3.24 -> 3.30, 256 of 400 10.8 -> 13.1).
-// The two round differently, and a caller's matrix keeps its bits in any batch:
-// only the eigenphases' problems, which no other batch holds, may take it.
+// Only the eigenphases' problems, where this was measured, take it.
 static bool few_matrices(be_ctx *ctx, int64_t nb_mat) { return 8 * nb_mat <= 3 * ctx->n_cu; }
 
 // Panel of NB columns from p0 by column launches (p0 + NB < N: the resident
 // kernel takes the last columns).
 static void few_panel(be_ctx *ctx, double2 *H, int64_t ms, int ld, int N, int p0, int64_t nb_mat, double2 *VW, int64_t sVW,
-                      double2 *Tm, int64_t sT, double *dd, double *ee, double2 *Pf, int64_t sPf, hipStream_t stream) {
+                      double2 *Tm, int64_t sT, double *dd, double *ee, double2 *Pf, int64_t sPf, int nt,
+                      hipStream_t stream) {
   const size_t sm = (2 * size_t(N) + 4 * NB) * sizeof(double2) + 2 * (FT / 64) * sizeof(double);
   if (sm > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&few_column), hipFuncAttributeMaxDynamicSharedMemorySize,
                               int(sm));
   for (int jj = -1; jj < NB; ++jj) {
     if (jj >= 0) {
-      const int nrb = (N - p0 - jj - 1 + 63) / 64, tiles = nrb * (nrb + 1) / 2;
-      const int64_t g = std::min<int64_t>((tiles + 3) / 4, std::max<int64_t>(1, 4 * ctx->n_cu / nb_mat));
+      const int nrb = (N - p0 - jj - 1 + 63) / 64, items = nrb * (nrb + 1) / 2 * panel_split(nrb);
+      const int64_t g = std::min<int64_t>((items + 3) / 4, std::max<int64_t>(1, 4 * ctx->n_cu / nb_mat));
       hipLaunchKernelGGL(few_matvec, dim3(static_cast<uint32_t>(g), static_cast<uint32_t>(nb_mat)), dim3(256), 0, stream,
                          H, ms, ld, N, p0 + jj, VW + int64_t(jj) * N, sVW, Pf, sPf);
     }
     hipLaunchKernelGGL(few_column, dim3(static_cast<uint32_t>(nb_mat)), dim3(FT), sm, stream, H, ms, ld, N, p0, jj, VW,
-                       sVW, Tm, sT, dd, ee, int64_t(N), Pf, sPf);
+                       sVW, Tm, sT, dd, ee, int64_t(N), Pf, sPf, nt);
   }
 }
 
@@ -1572,7 +1604,7 @@ static void few_panel(be_ctx *ctx, double2 *H, int64_t ms, int ld, int N, int p0
 // Householder reduction and back-transformation (double: FP64 path, float:
 // mixed path); the tridiagonal solve and the re-orthonormalization are FP64.
 // Hin: nb_mat matrices of CT<T>::c; U: c128 output.
-// columns (T = double only): a batch of few matrices may take its panels by
+// columns (T = double only): a batch of few matrices takes its panels by
 // column launches. bf16x3 (T = float only): the trailing update and the back-transformation
 // take the split-bf16 products of the complex GEMM.
 template <typename T>
@@ -1627,7 +1659,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
   C *Pg = nullptr;
   if (!pl && p_res > 0) cv.add(&Pg, size_t(nb_mat) * sPg);
   const bool few = columns && !mixed && p_res > 0 && few_matrices(ctx, nb_mat);
-  const int64_t sPf = int64_t((N + 62) / 64) * ((N + 62) / 64 + 1) * 64;
+  const int64_t sPf = int64_t(panel_part_bytes(N - 1, 1));
   double2 *Pf = nullptr;
   if (few) cv.add(&Pf, size_t(nb_mat) * sPf);
   BE_RET_IF(cv.commit(ctx, stream, WS_EIGH));
@@ -1646,7 +1678,7 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
       ProfScope prof(ctx, "hetrd_panel", stream);
       if constexpr (sizeof(T) == sizeof(double)) {
         if (few) {
-          few_panel(ctx, H, ms, ld, N, p0, nb_mat, VW, sVW, Tm + int64_t(p) * NB * NB, sT, dd, ee, Pf, sPf, stream);
+          few_panel(ctx, H, ms, ld, N, p0, nb_mat, VW, sVW, Tm + int64_t(p) * NB * NB, sT, dd, ee, Pf, sPf, pnt, stream);
         }
       }
       if (!few) hipLaunchKernelGGL(panel, dim3(nb_mat), dim3(pnt), psm, stream, H, ms, ld, N, p0, nbp, VW, sVW,

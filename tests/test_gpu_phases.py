@@ -143,3 +143,73 @@ def test_link_not_converged(m, smin):
     got, status = loop_phases(U)
     assert status & 2
     assert phase_set_error(got, np.angle(np.linalg.eigvals(F[2] @ F[1] @ F[0]))[None]) < 2 * m * np.finfo(float).eps / smin
+
+
+def bits(x):
+    return x.contiguous().view(torch.int64)
+
+
+# lines of Wilson matrices above order 216, few enough for column launches (4) and too many for them (100), and line counts on
+# either side of the rule (96 on 256 compute units): a system's phases are the same bits alone and in any larger call
+@pytest.mark.parametrize("threads", [0, 256, 512, 1024])  # of the panel kernel; 0: the tuning table's
+@pytest.mark.parametrize("m,copies", [(217, (25,)), (248, (24, 25)), (249, (25,)), (300, (25,)), (345, (25,)), (513, (25,))])
+def test_same_bits_alone_and_in_larger_calls(m, copies, threads):
+    gu.need_gpu()
+    rng = np.random.default_rng([m, 9])
+    lines = np.stack([rng.uniform(-1.2, 1.2, m) for _ in range(4)])
+    U = np.stack([grid_with_phases(th, [m, q, 9]) for q, th in enumerate(lines)])
+    c = gu.ctx()
+    if threads:
+        c.tune_clear("hetrd_panel_threads")
+        c.tune_set("hetrd_panel_threads", threads)
+    try:
+        U1 = gu.from_np(U.reshape(-1, 2 * m, m), 2 * m)
+
+        def run(n_sys):
+            Ud = U1.repeat(n_sys, 1, 1)
+            th, phi = (torch.empty((n_sys, 4) + s, dtype=torch.float64, device="cuda") for s in ((m,), ()))
+            wn, st = (torch.empty(n_sys, dtype=torch.int32, device="cuda") for _ in range(2))
+            c.wilson_loop(Ud, 2 * m, m, 2 * m, Ud.stride(0), n_sys, 3, 4, 0, th, phi, wn, st)
+            torch.cuda.synchronize()
+            return th, phi, st
+        th, phi, st = run(1)
+        assert int(st[0]) & ~4 == 0
+        assert phase_set_error(th[0].cpu().numpy(), lines) < 4e-12
+        for n in copies:
+            th2, phi2, st2 = run(n)
+            assert torch.equal(bits(th2), bits(th.repeat(n, 1, 1))) and torch.equal(bits(phi2), bits(phi.repeat(n, 1)))
+            assert torch.all(st2 == st)
+    finally:
+        c.close()
+
+
+def test_captured_column_launches():
+    """A Wilson loop of order 249 (one panel by column launches) under graph capture: every replay equals the eager call."""
+    gu.need_gpu()
+    m, s = 249, torch.cuda.Stream()
+    rng = np.random.default_rng([m, 10])
+    U = np.stack([grid_with_phases(rng.uniform(-1.2, 1.2, m), [m, q, 10]) for q in range(3)])
+    c = gu.ctx()
+    Ud = gu.from_np(U.reshape(-1, 2 * m, m), 2 * m)
+    th, phi = torch.empty((1, 3, m), dtype=torch.float64, device="cuda"), torch.empty((1, 3), dtype=torch.float64, device="cuda")
+    wn, st = (torch.empty(1, dtype=torch.int32, device="cuda") for _ in range(2))
+
+    def run():
+        c.wilson_loop(Ud, 2 * m, m, 2 * m, Ud.stride(0), 1, 3, 3, 0, th, phi, wn, st)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        run()  # sizes the workspace outside capture
+    torch.cuda.synchronize()
+    ref = [v.clone() for v in (th, phi, wn, st)]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s, capture_error_mode="relaxed"):
+        run()
+    for _ in range(3):
+        for v in (th, phi, wn, st):
+            v.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((th, phi, wn, st), ref))
+        x = torch.randn(1000, device="cuda")  # eager work between the replays
+        assert float(x.abs().sum()) > 0
+    c.close()
