@@ -690,6 +690,7 @@ __global__ __launch_bounds__(PT) void tri_invit(const double *d, const double *e
 // in lanes, larger ones by dot products from packed LDS: 2,304 projected spin
 // operators of order 200, clusters of 100, 15.5 ms; so 3.5).
 constexpr int GK = 8;         // largest group taken in lanes
+constexpr int GK2 = 32;       // largest group orthonormalized twice
 constexpr int GS_LDS = 8192;  // doubles: the lanes' Gram rows, or a panel's Gram parts, factor and S
 
 __host__ __device__ inline int gs_bins_max(int m) { return m / 33 + 2; }
@@ -835,11 +836,11 @@ __global__ __launch_bounds__(PT) void tri_gs(int N, int m, const double *lamg, d
   }
   // larger groups, by the whole workgroup in panels of 16 vectors on the matrix
   // cores: P -= Q (Q^T P) with the group's finished vectors Q, then Cholesky QR
-  // of the panel (G = P^T P = R^T R, P <- P R^-1). One pass: its loss of
-  // orthogonality (condition number times eps, squared inside a panel) is
-  // removed by the symmetric Newton-Schulz orthonormalization of all vectors
-  // that follows. S = Q^T P is in LDS while it fits, else in the matrix's m x m
-  // scratch.
+  // of the panel (G = P^T P = R^T R, P <- P R^-1). Two passes up to GK2 vectors, one
+  // for more: its loss of orthogonality (condition number times eps, squared inside
+  // a panel) is removed by the symmetric Newton-Schulz orthonormalization of all
+  // vectors that follows, in FP64 to 1e-14, on the mixed path where it is above
+  // 2e-7. S = Q^T P is in LDS while it fits, else in the matrix's m x m scratch.
   double *const Gw = gsm, *const R = gsm + nw * 256, *const rinv = R + 256, *const Sl = rinv + 16;
   const int li = lane & 15, lk = lane >> 4, wv = __builtin_amdgcn_readfirstlane(wave);
   const int nrt = (N + 15) / 16;  // row tiles
@@ -847,8 +848,9 @@ __global__ __launch_bounds__(PT) void tri_gs(int N, int m, const double *lamg, d
     const int c0 = mk_q[gi] & 0xffff, k = mk_q[gi] >> 16, c1 = c0 + k;
     if (k > GK) {
       double *const S = k * 16 + nw * 256 + 272 <= GS_LDS ? Sl : Gm + q * int64_t(m) * m;
-      for (int b = 0; 16 * b < k && !sfl[c0]; ++b) {
-        const int cb = c0 + 16 * b, w = min(16, c1 - cb);
+      const int nb = (k + 15) / 16, passes = k <= GK2 ? 2 : 1;
+      for (int t0 = 0; t0 < passes * nb && !sfl[c0]; ++t0) {
+        const int b = t0 < nb ? t0 : t0 - nb, cb = c0 + 16 * b, w = min(16, c1 - cb);
         const double *const Q = X + c0;
         double *const P = X + cb;
         for (int t = wv; t < b; t += nw) {  // S tile t = Q_t^T P
