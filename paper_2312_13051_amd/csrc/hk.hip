@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <type_traits>
 #include <utility>
 
@@ -246,13 +247,17 @@ int be_hk_plan_create(be_ctx *ctx, const be_hoplist *sys_h, int32_t n_sys, be_hk
   // one allocation and one copy for all arrays: each hipMalloc, synchronous
   // copy and hipFree costs a small model more than its kernels (ten of them:
   // 2-band model, whole call 299 us; one: 171 us)
-  std::vector<unsigned char> host;
-  std::vector<std::pair<void **, size_t>> at;
+  struct Array {
+    void **dst;
+    const void *src;
+    size_t bytes, off;
+  };
+  std::vector<Array> arrays;
+  size_t total = 0;
   auto add = [&](auto **dst, const void *src, size_t count) {
-    const size_t bytes = count * sizeof(**dst), off = host.size();
-    host.resize(off + ((std::max<size_t>(bytes, 16) + 255) & ~size_t(255)));
-    if (bytes) std::memcpy(host.data() + off, src, bytes);
-    at.emplace_back(reinterpret_cast<void **>(dst), off);
+    const size_t bytes = count * sizeof(**dst);
+    arrays.push_back({reinterpret_cast<void **>(dst), src, bytes, total});
+    total += (std::max<size_t>(bytes, 16) + 255) & ~size_t(255);
   };
   add(&P->d_pair_rc, pk.rc.data(), pk.rc.size());
   add(&P->d_pair_start, pk.start.data(), pk.start.size());
@@ -264,13 +269,16 @@ int be_hk_plan_create(be_ctx *ctx, const be_hoplist *sys_h, int32_t n_sys, be_hk
   add(&P->d_R, dr.R.data(), dr.R.size());
   add(&P->d_sys_R_off, dr.off.data(), dr.off.size());
   add(&P->d_sys_n_R, dr.count.data(), dr.count.size());
-  if (hipMalloc(&P->d_all, host.size()) != hipSuccess ||
-      hipMemcpy(P->d_all, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) {
+  const std::unique_ptr<unsigned char[]> host(new unsigned char[total]);  // padding stays as it is
+  for (const Array &x : arrays)
+    if (x.bytes) std::memcpy(host.get() + x.off, x.src, x.bytes);
+  if (hipMalloc(&P->d_all, total) != hipSuccess ||
+      hipMemcpy(P->d_all, host.get(), total, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipGetLastError();
     be_hk_plan_destroy(P);
     return set_err(ctx, BE_ENOMEM, "be_hk_plan_create: device upload failed");
   }
-  for (const auto &[dst, off] : at) *dst = static_cast<unsigned char *>(P->d_all) + off;
+  for (const Array &x : arrays) *x.dst = static_cast<unsigned char *>(P->d_all) + x.off;
   *plan = P;
   return BE_OK;
 }

@@ -85,6 +85,7 @@ inline std::string pack_system(int32_t N, int32_t dim, int64_t nnz, const int32_
   }
   std::sort(ents.begin(), ents.end(), key_less);
   std::vector<Ent> merged;
+  merged.reserve(ents.size());
   for (const Ent &x : ents) {
     if (!merged.empty() && key_eq(merged.back(), x)) {
       merged.back().tr += x.tr;
@@ -111,6 +112,11 @@ inline std::string pack_system(int32_t N, int32_t dim, int64_t nnz, const int32_
   size_t kept = 0;
   for (const Ent &x : merged) kept += x.i <= x.j;
   if (out.R.size() + kept > size_t(std::numeric_limits<int32_t>::max())) return "too many entries";
+  if (out.R.size() + kept > out.R.capacity()) {  // at least doubled: many systems follow one another
+    const size_t cap = std::max(out.R.size() + kept, 2 * out.R.capacity());
+    out.R.reserve(cap);
+    out.t.reserve(cap);
+  }
   int32_t np = 0;
   for (size_t a = 0; a < merged.size();) {
     const Ent &x = merged[a];
