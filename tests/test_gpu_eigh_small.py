@@ -88,3 +88,44 @@ def test_mixed_orders(N, precision):
         assert np.abs(U[q].conj().T @ U[q] - np.eye(m)).max() < bound
         if mixed:
             assert np.abs(H[q] @ U[q] - U[q] * ev[q, 1:m + 1]).max() <= 1e-4 * nrm
+
+
+# the flags of every small solver (FP64, the one-launch mixed one, the tridiagonal part alone from 17 on, the refined path on
+# either): none for separated levels, a closed gap where all levels are one, non-finite input flagged with NaN levels, and no
+# matrix touched by its neighbours' flags
+@pytest.mark.parametrize("precision", ["fp64", "mixed", "refined"])
+@pytest.mark.parametrize("N", [2, 4, 5, 8, 9, 15, 16, 17, 24, 32, 33])
+def test_status(N, precision):
+    gu.need_gpu()
+    from paper_2312_13051_amd import _lib as L
+    mixed, n, (lo, hi) = precision == "mixed", 9, (N // 4, N // 2 + (N > 2))
+    m = hi - lo
+    rng = np.random.default_rng([N, 11])
+    H = np.empty((n, N, N), complex)
+    for q in range(n):  # levels 1, 2, 3, ...
+        Q = np.linalg.qr(rng.standard_normal((N, N)) + 1j * rng.standard_normal((N, N)))[0]
+        H[q] = (Q * np.arange(1.0, N + 1)) @ Q.conj().T
+    H = 0.5 * (H + H.conj().transpose(0, 2, 1))
+    want = np.zeros(n, int)
+    for q, v in ((2, np.nan), (5, np.inf)):
+        H[q, N - 1, 0] = v
+        want[q] = L.ST_NAN_INF
+    H[7] = 1.5 * np.eye(N)
+    want[7] = L.ST_GAP_CLOSED
+    c = gu.ctx()
+    try:
+        dH = gu.from_np(H, N, torch.complex64 if mixed else torch.complex128)
+        U = gu.colmajor(n, N, m, N, fill=0)
+        ev = torch.empty((n, m + 2), dtype=torch.float64, device="cuda")
+        st = torch.full((n,), 77, dtype=torch.int32, device="cuda")
+        c.eigh_batched(dH, L.BE_C64 if mixed else L.BE_C128, N, N, dH.stride(0), n, lo, hi,
+                       {"fp64": L.BE_FP64, "mixed": L.BE_MIXED_FP32, "refined": L.BE_MIXED_FP32_REFINED}[precision], ev, U, N,
+                       U.stride(0), st)
+        ev, st = ev.cpu().numpy(), st.cpu().numpy()
+    finally:
+        c.close()
+    bad = want == L.ST_NAN_INF
+    assert np.array_equal(st[~bad], want[~bad]) and np.all(st[bad] & L.ST_NAN_INF)
+    assert np.all(np.isnan(ev[bad, 1:m + 1]))
+    good = ev[want == 0, 1:m + 1]
+    assert np.abs(good - np.arange(lo + 1, hi + 1)).max() <= (2e-5 if mixed else 1e-10) * N
