@@ -361,7 +361,9 @@ int be_profile_names(be_ctx *ctx, char *buf, size_t len);
  *                       or 1024 (default 512: two matrices per compute
  *                       unit overlap one's serial reflector steps with the
  *                       other's matrix-vector product).
- *                       Orders up to 16 always take one wave, and FP64
+ *                       FP32 orders 193 to 257 set to 512 take 256 in calls
+ *                       whose matrices then fill the device in fewer rounds
+ *                       (the same results). Orders up to 16 always take one wave, and FP64
  *                       reduces the last 216 rows and columns on chip,
  *                       without the panel kernel.
  *   "hetrd_panel_loads"  loads in flight per lane in the matrix-vector

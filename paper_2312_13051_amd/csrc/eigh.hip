@@ -1605,13 +1605,13 @@ static void few_panel(be_ctx *ctx, double2 *H, int64_t ms, int ld, int N, int p0
 // One sub-batch of nb_mat matrices. T is the working precision of the
 // Householder reduction and back-transformation (double: FP64 path, float:
 // mixed path); the tridiagonal solve and the re-orthonormalization are FP64.
-// Hin: nb_mat matrices of CT<T>::c; U: c128 output.
+// Hin: nb_mat matrices of CT<T>::c; U: c128 output. pnt: threads of the panel kernel.
 // columns (T = double only): a batch of few matrices takes its panels by
 // column launches. bf16x3 (T = float only): the trailing update and the back-transformation
 // take the split-bf16 products of the complex GEMM.
 template <typename T>
 static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t ms, int64_t nb_mat, int lo, int hi,
-                      double *evals, double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream,
+                      double *evals, double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream, int pnt,
                       double clu_rel = kCluRel, bool bf16x3 = false, bool columns = false) {
   typedef typename CT<T>::c C;
   typedef typename GemmOf<T>::type G;
@@ -1654,7 +1654,6 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
   if (mixed) cv.add(&Uw, size_t(nb_mat) * N * std::max(m, 1));
   // panel kernel: 256, 512 or 1024 threads per matrix; partial vectors of its
   // matrix-vector product in LDS or in global scratch
-  const int pnt = panel_threads(ctx, N, sizeof(C));
   const bool pl = panel_part_lds(N, sizeof(C), pnt);
   const size_t psm = panel_lds(N, sizeof(C), pnt);
   const int64_t sPg = pl ? 0 : int64_t(panel_part_bytes(N - 1, 1));
@@ -1923,13 +1922,12 @@ static int eigh_chunk(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t 
   return BE_OK;
 }
 
-// Matrices the panel kernel holds resident on the whole device at once (one
-// workgroup per matrix): CUs times resident workgroups per CU.
+// Matrices the panel kernel of pnt threads holds resident on the whole device at
+// once (one workgroup per matrix): CUs times resident workgroups per CU.
 template <typename T>
-static int64_t panel_slots(be_ctx *ctx, int N) {
+static int64_t panel_slots(be_ctx *ctx, int N, int pnt) {
   typedef typename CT<T>::c C;
   if (sizeof(T) == sizeof(double) && N <= kResidentOrder) return resident_slots(ctx, N);
-  const int pnt = panel_threads(ctx, N, sizeof(C));
   const size_t psm = panel_lds(N, sizeof(C), pnt);
   PanelFn<T> panel = panel_kernel<T>(pnt, panel_loads(ctx, N, sizeof(C), pnt), panel_part_lds(N, sizeof(C), pnt));
   int per_cu = 0;
@@ -1944,6 +1942,21 @@ static int64_t panel_slots(be_ctx *ctx, int N) {
   return int64_t(std::max(per_cu, 1)) * ctx->n_cu;
 }
 
+// Threads of the panel kernel for a call of n_mat matrices: the setting's, but
+// FP32 orders 193 to 257 set to 512 take 256 where that saves more than a quarter
+// of the device-wide rounds (more matrices resident, each slower). Up to order 257
+// a thread has one row at most, so both sum alike and give the same bits. Order
+// 200, bands 100, 512 -> 256 threads (768 and 1,280 resident): 256 matrices 4.1 ->
+// 4.9 ms, 768 6.3 -> 7.0, 1,024 9.6 -> 8.3, 1,280 10.9 -> 9.5, 1,536 12.2 -> 13.6,
+// 2,304 18.1 -> 17.3, 3,072 24.3 -> 27.0, 4,608 36.4 -> 34.5.
+template <typename T>
+static int call_panel_threads(be_ctx *ctx, int N, int64_t n_mat) {
+  const int nt = panel_threads(ctx, N, sizeof(typename CT<T>::c));
+  if (sizeof(T) != sizeof(float) || nt != 512 || N <= 192 || N > 257) return nt;
+  const int64_t s512 = panel_slots<T>(ctx, N, 512), s256 = panel_slots<T>(ctx, N, 256);
+  return 4 * ((n_mat + s256 - 1) / s256) < 3 * ((n_mat + s512 - 1) / s512) ? 256 : 512;
+}
+
 // The panel vectors and the tridiagonal solver's arrays live in LDS.
 static int check_eigh_lds(be_ctx *ctx, int N, int m, size_t cs) {
   const size_t lds_need = std::max({panel_lds(N, cs, panel_threads(ctx, N, cs)), (4 * size_t(N) + m + 4) * sizeof(double),
@@ -1953,9 +1966,9 @@ static int check_eigh_lds(be_ctx *ctx, int N, int m, size_t cs) {
   return BE_OK;
 }
 
-// Workspace bytes per matrix of eigh_chunk for order N and m bands.
+// Workspace bytes per matrix of eigh_chunk for order N, m bands and pnt panel threads.
 template <typename T>
-static size_t eigh_chunk_bytes(be_ctx *ctx, int N, int m) {
+static size_t eigh_chunk_bytes(int N, int m, int pnt) {
   const int P = (N + NB - 1) / NB;
   const int mp = std::max(64, (m + 63) / 64 * 64);
   const size_t cs = sizeof(typename CT<T>::c);
@@ -1963,7 +1976,7 @@ static size_t eigh_chunk_bytes(be_ctx *ctx, int N, int m) {
   return cs * ((panels ? size_t(N) * 3 * NB : 0) + (sizeof(T) == sizeof(double) ? size_t(N) : 0) +
                size_t(P) * NB * NB + 4 * size_t(NB) * std::max(m, 1) + 6 * size_t(NB) * NB +
                size_t(N) * std::max(m, 1)) +
-         (!panels || panel_part_lds(N, cs, panel_threads(ctx, N, cs)) ? 0 : panel_part_bytes(N - 1, cs)) +
+         (!panels || panel_part_lds(N, cs, pnt) ? 0 : panel_part_bytes(N - 1, cs)) +
          sizeof(double) * (3 * size_t(N) + size_t(m) + 1 +
                            (N <= kSmallOrder ? 0 : 4 * size_t(N) * mp + size_t(std::max(m, 1)) * std::max(m, 1))) +
          sizeof(int) * size_t(std::max(m, 1)) + 16 * 256;
@@ -1979,8 +1992,8 @@ static size_t eigh_chunk_bytes(be_ctx *ctx, int N, int m) {
 // short remainder costs a full round per panel (4,608 matrices of order 400
 // with 768 resident: six sub-batches of 768; 9,216: twelve).
 template <typename T>
-static int64_t eigh_sub_batch(be_ctx *ctx, int N, size_t per, size_t reusable, int64_t n_mat) {
-  const int64_t slots = panel_slots<T>(ctx, N);
+static int64_t eigh_sub_batch(be_ctx *ctx, int N, int pnt, size_t per, size_t reusable, int64_t n_mat) {
+  const int64_t slots = panel_slots<T>(ctx, N, pnt);
   int64_t cap = std::max<int64_t>(1, int64_t((size_t(4) << 30) / per));
   if (cap < slots) {
     size_t free_b = 0, total_b = 0;
@@ -2011,12 +2024,13 @@ static int eigh_run(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t ma
     return eigh_small_c64(ctx, H, N, ld, mat_stride, n_mat, band_lo, band_hi, evals, U, ldu, u_stride, status, stream,
                           clu_rel);
   }
-  const size_t per = eigh_chunk_bytes<T>(ctx, N, m);
-  const int64_t cap = eigh_sub_batch<T>(ctx, N, per, ctx->ws_bytes[WS_EIGH], n_mat);
+  const int pnt = call_panel_threads<T>(ctx, N, n_mat);
+  const size_t per = eigh_chunk_bytes<T>(N, m, pnt);
+  const int64_t cap = eigh_sub_batch<T>(ctx, N, pnt, per, ctx->ws_bytes[WS_EIGH], n_mat);
   for (int64_t b0 = 0; b0 < n_mat; b0 += cap) {
     const int64_t nb_mat = std::min<int64_t>(cap, n_mat - b0);
     BE_RET_IF(eigh_chunk<T>(ctx, H + b0 * mat_stride, N, ld, mat_stride, nb_mat, band_lo, band_hi, evals + b0 * (m + 2),
-                            U + b0 * u_stride, ldu, u_stride, status + b0, stream, clu_rel, bf16x3, columns));
+                            U + b0 * u_stride, ldu, u_stride, status + b0, stream, pnt, clu_rel, bf16x3, columns));
   }
   return BE_OK;
 }
@@ -2029,7 +2043,8 @@ static int eigh_run(be_ctx *ctx, typename CT<T>::c *H, int N, int ld, int64_t ma
 // Newton-Schulz orthonormalization of U_w. The error of the FP32 subspace
 // (~1e-6 relative) enters the result squared.
 static int eigh_refined_chunk(be_ctx *ctx, const double2 *H, int N, int ld, int64_t ms, int64_t nb, int lo, int hi,
-                              double *evals, double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream) {
+                              double *evals, double2 *U, int ldu, int64_t us, uint32_t *status, hipStream_t stream,
+                              int pnt) {
   const int m = hi - lo, nc = N - m;
   const int mm = std::max(m, 1);
   const int64_t NN = int64_t(N) * N, sGU = int64_t(N) * 2 * mm, sS2 = int64_t(std::max(nc, 1)) * 2 * mm;
@@ -2062,7 +2077,7 @@ static int eigh_refined_chunk(be_ctx *ctx, const double2 *H, int N, int ld, int6
   if (N <= kSmallMixed)
     BE_RET_IF(eigh_small_c64(ctx, Hc, N, N, NN, nb, 0, N, lam, Uall, N, NN, status, stream, kCluRel));
   else
-    BE_RET_IF(eigh_chunk<float>(ctx, Hc, N, N, NN, nb, 0, N, lam, Uall, N, NN, status, stream));
+    BE_RET_IF(eigh_chunk<float>(ctx, Hc, N, N, NN, nb, 0, N, lam, Uall, N, NN, status, stream, pnt));
   auto zg = [&](int M_, int N_, int K_, int opA, const double2 *A_, int lda_, int64_t sA_, const double2 *B_, int ldb_,
                 int64_t sB_, double2 *C_, int ldc_, int64_t sC_, double beta, const char *tag) {
     ZGemm g;
@@ -2197,13 +2212,14 @@ static int eigh_refined(be_ctx *ctx, const double2 *H, int N, int ld, int64_t ms
   const size_t own = 16 * (3 * size_t(N) * N + size_t(N) * 2 * mm + size_t(std::max(nc, 1)) * 2 * mm +
                            size_t(mm) * mm) -
                      8 * size_t(N) * N + 8 * (size_t(N) + 2) + 16 + 6 * 256;
-  const size_t per = eigh_chunk_bytes<float>(ctx, N, N) + own;
+  const int pnt = call_panel_threads<float>(ctx, N, n_mat);
+  const size_t per = eigh_chunk_bytes<float>(N, N, pnt) + own;
   const int64_t cap =
-      eigh_sub_batch<float>(ctx, N, per, ctx->ws_bytes[WS_EIGH] + ctx->ws_bytes[WS_MISC], n_mat);
+      eigh_sub_batch<float>(ctx, N, pnt, per, ctx->ws_bytes[WS_EIGH] + ctx->ws_bytes[WS_MISC], n_mat);
   for (int64_t b0 = 0; b0 < n_mat; b0 += cap) {
     const int64_t nb = std::min<int64_t>(cap, n_mat - b0);
     BE_RET_IF(eigh_refined_chunk(ctx, H + b0 * ms, N, ld, ms, nb, lo, hi, evals + b0 * (m + 2), U + b0 * us, ldu, us,
-                                 status + b0, stream));
+                                 status + b0, stream, pnt));
   }
   return BE_OK;
 }
@@ -2258,9 +2274,9 @@ extern "C" int be_eigh_round(be_ctx *ctx, int32_t N, int32_t precision, int64_t 
   BE_CHECK_ARG(ctx, ctx && round, "be_eigh_round: null argument");
   BE_CHECK_ARG(ctx, N >= 1, "be_eigh_round: N < 1");
   if (precision == BE_FP64) {
-    *round = panel_slots<double>(ctx, N);
+    *round = panel_slots<double>(ctx, N, panel_threads(ctx, N, sizeof(double2)));
   } else if (precision == BE_MIXED_FP32 || precision == BE_MIXED_FP32_REFINED || precision == BE_MIXED_BF16X) {
-    *round = panel_slots<float>(ctx, N);
+    *round = panel_slots<float>(ctx, N, panel_threads(ctx, N, sizeof(float2)));
   } else {
     return set_err(ctx, BE_EINVAL, "be_eigh_round: unknown precision");
   }

@@ -526,3 +526,31 @@ def test_eigh_split_bf16_bounds(name):
     st2 = torch.empty(n, dtype=torch.int32, device="cuda")
     with pytest.raises(L.BerryError):
         c.eigh_batched(z, L.BE_C128, N, N, z.stride(0), n, 0, m, L.BE_MIXED_BF16X, ev2, U2, N, U2.stride(0), st2)
+
+
+@pytest.mark.parametrize("N", [193, 200, 257])
+def test_same_bits_across_panel_threads_by_batch(N):
+    """FP32 orders 193 to 257: a call's batch decides between 256 and 512 panel threads (on 256 compute units 768 matrices take
+    512 threads, 1,024 take 256, 1,536 take 512); a matrix comes out the same bits in each and alone."""
+    gu.need_gpu()
+    from paper_2312_13051_amd import _lib as L
+    rng = np.random.default_rng([N, 21])
+    A = rng.standard_normal((2, N, N)) + 1j * rng.standard_normal((2, N, N))
+    H2 = gu.from_np(A + A.conj().transpose(0, 2, 1), N, torch.complex64)
+    m = 5
+    c = gu.ctx()
+    try:
+        def run(copies):
+            H = H2.repeat(copies, 1, 1)
+            n = H.shape[0]
+            U = gu.colmajor(n, N, m, N, fill=0)
+            ev = torch.empty((n, m + 2), dtype=torch.float64, device="cuda")
+            st = torch.empty(n, dtype=torch.int32, device="cuda")
+            c.eigh_batched(H, L.BE_C64, N, N, H.stride(0), n, 0, m, L.BE_MIXED_FP32, ev, U, N, U.stride(0), st)
+            torch.cuda.synchronize()
+            return ev[:, 1:m + 1].reshape(copies, 2, m), U.reshape(copies, 2, m, N), st.reshape(copies, 2)
+        one = run(1)
+        for copies in (384, 512, 768):
+            assert all(torch.equal(a, b.expand_as(a)) for a, b in zip(run(copies), one)), copies
+    finally:
+        c.close()
