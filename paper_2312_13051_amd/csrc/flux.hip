@@ -403,8 +403,8 @@ __global__ __launch_bounds__(DT) void k_det_phase(double2 *A, int m, int64_t sA,
   if (tid == 0) lsig[blockIdx.x] = la;
 }
 
-// The same factorization for orders up to NT: a thread per row of the panel,
-// which it holds in registers, so that a column costs two barriers, a search
+// The same factorization for orders up to NT: a thread per row of the panel of NB
+// columns, which it holds in registers, so that a column costs two barriers, a search
 // over lanes by moves between them and one LDS read of the pivot row. The
 // panel's interchanges reach the other columns as one gather (all rows of a
 // column loaded before any is stored), and the trailing update runs on the
@@ -414,9 +414,9 @@ __global__ __launch_bounds__(DT) void k_det_phase(double2 *A, int m, int64_t sA,
 // order 16 39 -> 25 us, 48 154 -> 91, 79 382 -> 188, 128 1,198 -> 376; 500 of
 // order 166 996 -> 637; 300 of order 256 2.42 -> 1.32 ms. lsig and phase as there (the sums over the
 // pivots in another order).
-template <int NT>
+template <int NT, int NB>
 __global__ __launch_bounds__(NT, 2) void k_det_phase_r(double2 *A, int m, int64_t sA, double *phase, double *lsig) {
-  constexpr int NB = 16, NW = NT / 64;
+  constexpr int NW = NT / 64, KT = NB / 4;  // KT: matrix-core steps of a panel's columns
   constexpr int LP = NB + 1;       // pitch: lanes that read a column of 16 rows meet different banks
   extern __shared__ double2 sL[];  // factored panel, row by row: sL[r * LP + c]
   __shared__ double2 s_row[2][NB];  // the pivot's row, the row it takes the place of
@@ -544,9 +544,9 @@ __global__ __launch_bounds__(NT, 2) void k_det_phase_r(double2 *A, int m, int64_
     const int nct = (C + 15) / 16, nrt = (rows - nbp + 15) / 16;
     for (int ct = wv; ct < nct; ct += NW) {
       const int jc = 16 * ct + li, j = j0 + min(jc, C - 1);
-      double2 u[4];
+      double2 u[KT];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) u[t] = M[int64_t(k0 + 4 * t + lk) * m + j];  // C > 0: nbp = NB
+      for (int t = 0; t < KT; ++t) u[t] = M[int64_t(k0 + 4 * t + lk) * m + j];  // C > 0: nbp = NB
       double2 *Mj = M + int64_t(j0) * m + j;
       const int rmax = rows - nbp - 1;
       double2 y[4];
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(NT, 2) void k_det_phase_r(double2 *A, int m, int64_
         for (int r = 0; r < 4; ++r) y[r] = Mj[int64_t(min(16 * (rt + 1) + lk + 4 * r, rmax)) * m];  // the next tile
         const double2 *Lr = sL + (nbp + min(16 * rt + li, rmax)) * LP + lk;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < KT; ++t) {
           const double2 l = Lr[4 * t];
           re = __builtin_amdgcn_mfma_f64_16x16x4f64(-l.x, u[t].x, re, 0, 0, 0);
           im = __builtin_amdgcn_mfma_f64_16x16x4f64(-l.x, u[t].y, im, 0, 0, 0);
@@ -605,6 +605,20 @@ __global__ __launch_bounds__(NT, 2) void k_det_phase_r(double2 *A, int m, int64_
 // Largest order of the kernel with a row per thread, and the panel width of the
 // other for order m (a panel of at most 160 KiB of LDS; 64 where that fits).
 constexpr int kDetRows = 256;
+// Panel columns of the kernel with a row per thread. A panel holds its columns in
+// registers and takes them all to their end, also those past the matrix: small
+// orders take the narrowest that covers them; narrow panels leave registers for
+// more links per compute unit, wide ones pass over the trailing matrix less often.
+// Whole calls, 16 -> 8 columns (4 at order 4): 10,240 links of order 4 94 -> 65 us,
+// 8 132 -> 94, 17 323 -> 233, 48 854 -> 774, 65 2.87 -> 2.39 ms, 80 3.16 -> 2.94, 96
+// 4.18 -> 4.21; 40,960 of 64 4.94 -> 5.25; 64 links of order 9 59 -> 62 us, 17 102 -> 87,
+// 65 323 -> 282, 128 678 -> 693.
+int det_panel_cols(int m) {
+  if (m <= 4) return 4;
+  if (m <= 8) return 8;
+  if (m <= 12) return 16;
+  return m <= 60 || (m > 64 && m <= 80) ? 8 : 16;
+}
 int det_panel_width(int m) {
   if (m <= 512) return 8;
   if (m <= 2544) return 4;
@@ -788,9 +802,13 @@ int flux_run(be_ctx *ctx, const void *U, int32_t N, int32_t m, int32_t ldu, int6
         double *ph = dir == 0 ? fs.ph_par : fs.ph_perp, *ls = dir == 0 ? fs.ls_par : fs.ls_perp;
         const dim3 grid(static_cast<uint32_t>(nk));
         if (m <= kDetRows) {
-          const size_t sm = size_t(std::max(m, 1)) * 17 * sizeof(double2);
-          const int nt = m <= 64 ? 64 : m <= 128 ? 128 : 256;
-          auto kern = nt == 64 ? &k_det_phase_r<64> : nt == 128 ? &k_det_phase_r<128> : &k_det_phase_r<256>;
+          const int nt = m <= 64 ? 64 : m <= 128 ? 128 : 256, nb = det_panel_cols(m);
+          const size_t sm = size_t(std::max(m, 1)) * (nb + 1) * sizeof(double2);
+          auto kern = nt == 256 ? &k_det_phase_r<256, 16>
+                      : nt == 128 ? (nb == 8 ? &k_det_phase_r<128, 8> : &k_det_phase_r<128, 16>)
+                      : nb == 4   ? &k_det_phase_r<64, 4>
+                      : nb == 8   ? &k_det_phase_r<64, 8>
+                                  : &k_det_phase_r<64, 16>;
           if (sm > 65536)
             BE_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(sm)));

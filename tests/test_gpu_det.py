@@ -42,3 +42,10 @@ def test_orders(m, near):
     if near and m > 1:  # plaquettes with a corner at that point have no flux
         ok[np.ix_([0, 1], [0, 1])] = False
     assert circ(f, ref["flux"])[ok].max() < 1e-9
+
+
+# every panel width at its first and last order, one panel and several with remainders
+@pytest.mark.parametrize("near", [False, True])
+@pytest.mark.parametrize("m", [3, 4, 5, 8, 9, 12, 13, 59, 60, 61, 66, 79, 80, 81])
+def test_panel_widths(m, near):
+    test_orders(m, near)
