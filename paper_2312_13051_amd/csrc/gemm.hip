@@ -365,8 +365,12 @@ int dispatch(be_ctx *ctx, GP<T> p, int opA, int opB, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0 || p.batch <= 0) return BE_OK;  // nothing to launch
   // FP64 from order 128 on: 64 x 64 tiles, whose idle wave sub-tiles are skipped
   // (2,304 products 400 x 200 by K = 200: 5.93 ms before, 5.50 in 32 x 32 tiles,
-  // 4.92 so; at 100 x 100 by 100 the small tiles stay even)
-  if (sizeof(T) == 8 && std::min(p.M, p.N) >= 48 && std::max(p.M, p.N) > 128)
+  // 4.92 so; at 100 x 100 by 100 the small tiles stay even), where they give every
+  // compute unit one: fewer leave the device idle (one product 400 x 200 by 400 42 ->
+  // 66 us, 200 x 200 by 200 32 -> 45, 16 of order 160 35 -> 40; 16 of order 200, 256
+  // tiles, 51 -> 47). Both add an element's terms in the same order: the same bits.
+  const int64_t t64 = int64_t((p.M + 63) / 64) * ((p.N + 63) / 64) * p.batch;
+  if (sizeof(T) == 8 && std::min(p.M, p.N) >= 48 && std::max(p.M, p.N) > 128 && t64 >= ctx->n_cu)
     return launch_cfg<T, 64, 64, 4, 2>(ctx, p, opA, opB, s);
   // Tile choice by output size; small outputs use one-wave tiles.
   // 64 x 64 tiles with 8 waves (each 16 x 32): fewer registers per wave than

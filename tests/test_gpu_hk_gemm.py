@@ -133,3 +133,24 @@ def test_zgemm_empty_batch(M, N):
     c.zgemm_strided("N", "N", M, N, 4, 1.0, A, M, A.stride(0), B, 4, B.stride(0), 0.0, C, M, C.stride(0), 0)
     torch.cuda.synchronize()
     assert torch.all(C == 1.0)
+
+
+# FP64 outputs with a side above 128: the tile size goes by the number of tiles in the launch; an item comes out the same bits in
+# a batch that takes 64 x 64 tiles and alone
+@pytest.mark.parametrize("opA,opB", [("N", "N"), ("C", "N"), ("N", "C")])
+@pytest.mark.parametrize("M,N,K", [(129, 48, 64), (130, 130, 33), (160, 160, 160), (200, 200, 17), (400, 200, 100)])
+def test_zgemm_same_bits_in_any_batch(M, N, K, opA, opB):
+    gu.need_gpu()
+    batch = 300
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    ra, ca = (M, K) if opA == "N" else (K, M)
+    rb, cb = (K, N) if opB == "N" else (N, K)
+    A = torch.randn((1, ca, ra), dtype=torch.complex128, device="cuda", generator=g).repeat(batch, 1, 1)
+    B = torch.randn((1, cb, rb), dtype=torch.complex128, device="cuda", generator=g).repeat(batch, 1, 1)
+    C = torch.zeros((batch, N, M), dtype=torch.complex128, device="cuda")
+    C1 = torch.zeros((1, N, M), dtype=torch.complex128, device="cuda")
+    c = gu.ctx()
+    for out, n in ((C, batch), (C1, 1)):
+        c.zgemm_strided(opA, opB, M, N, K, 1.0, A, ra, A.stride(0), B, rb, B.stride(0), 0.0, out, M, out.stride(0), n)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.view_as_real(C), torch.view_as_real(C1).expand(batch, -1, -1, -1))
