@@ -329,15 +329,24 @@ int be_build_hk(be_ctx *ctx, const be_hk_plan *P, int32_t sys_first, int32_t n_s
   // lanes per matrix; the phase table unless the list has too many distinct vectors for it
   int pp = 8;
   while (pp < 256 && pp < maxp) pp *= 2;
-  const int kb = pp == 256 && 4 * int64_t(max_R) <= kPhaseTable ? 4 : 1;
+  // workgroups (x, y) with kb k-points per entry read and r rounds of pairs per
+  // workgroup, which share its phases: four of each, fewer where that would leave
+  // compute units without work (order 1024, c64, one k-point: 22.5 us in hk_scatter,
+  // 26.8 with four, 23.6 so; 16: 46.2, 52.5, 47.7)
+  auto grid = [&](int kb, int r) {
+    const int64_t groups = (int64_t(n_sys_call) * ((n_kap + kb - 1) / kb) + 256 / pp - 1) / (256 / pp);
+    return dim3(static_cast<uint32_t>(std::max(1, (maxp + r * pp - 1) / (r * pp))),
+                static_cast<uint32_t>(std::min<int64_t>(groups, 65535)));
+  };
+  auto fills = [&](dim3 g) { return int64_t(g.x) * g.y >= 2 * ctx->n_cu; };
+  const int kb = pp == 256 && 4 * int64_t(max_R) <= kPhaseTable && fills(grid(4, 1)) ? 4 : 1;
+  int rounds = 4;
+  while (rounds > 1 && !fills(grid(kb, rounds))) rounds /= 2;
   auto go = [&](auto *Ht) {
     typedef std::remove_pointer_t<decltype(Ht)> OUT;
     const int64_t phases = (256 / pp) * int64_t(kb) * max_R;
     if (phases <= kPhaseTable) {
-      // up to four rounds of pairs per workgroup, which share its phases
-      const int64_t groups = (int64_t(n_sys_call) * ((n_kap + kb - 1) / kb) + 256 / pp - 1) / (256 / pp);
-      const dim3 g(static_cast<uint32_t>(std::max(1, (maxp + 4 * pp - 1) / (4 * pp))),
-                   static_cast<uint32_t>(std::min<int64_t>(groups, 65535)));
+      const dim3 g = grid(kb, rounds);
       auto kern = kb == 4 ? &hk_scatter_table<4, OUT> : &hk_scatter_table<1, OUT>;
       hipLaunchKernelGGL(kern, g, dim3(256), size_t(phases) * sizeof(double2), stream, Ht, mat_stride, ld, sys_first,
                          kappa, n_kap, n_sys_call, pp, max_R, P->d_pair_rc, P->d_pair_start, P->d_ent_R, P->d_ent_t,

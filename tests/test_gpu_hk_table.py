@@ -98,3 +98,20 @@ def test_every_element_written(N, share, dtype):
             assert np.abs(H - np.repeat(ref, 5, axis=0)).max(initial=0.0) <= (0.0 if dtype == 0 else 1e-6)
     finally:
         c.close()
+
+
+# the number of k-points decides how many share an entry's read and how many pairs a workgroup takes: the same bits for each
+# k-point alone, a few at a time and all together, with few entries a pair and many
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("model", ["sparse", "dense"])
+def test_same_bits_in_any_call(model, dtype):
+    gu.need_gpu()
+    hop = syn.bhz_disordered(16, 1.0, [3, 5]) if model == "sparse" else syn.wannier_like(40, [3, 6])
+    kappa = np.random.default_rng(7).uniform(-1, 1, (110, 3))
+    c = gu.ctx()
+    try:
+        H = build(c, [hop], kappa, dtype, 0)
+        for part in (slice(3, 4), slice(10, 17), slice(40, 105)):
+            assert np.array_equal(build(c, [hop], kappa[part], dtype, 0), H[part])
+    finally:
+        c.close()
