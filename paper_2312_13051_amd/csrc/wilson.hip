@@ -229,8 +229,13 @@ constexpr int kSmallN = 64;          // orbitals: a lane sums a whole overlap el
 constexpr int kSmallEntries = 3072;  // matrix entries of a line's factors held in LDS (48 KB)
 constexpr int kSmallThreads = 256;
 
-__host__ __device__ inline bool small_loop_fits(int N, int m, int n_loop) {
-  return m <= kSmallM && N <= kSmallN && int64_t(n_loop) * m * m <= kSmallEntries;
+// Without polar factors a line's overlaps are most of its work, and the general
+// path spreads them over the device: past 1,024 terms of them per lane it is the
+// faster one (order 8, 64 orbitals, 32 lines: 12 links 167 general, 156 here; 32
+// links 185, 201 us).
+inline bool small_loop_fits(int N, int m, int n_loop, bool polar) {
+  return m <= kSmallM && N <= kSmallN && int64_t(n_loop) * m * m <= kSmallEntries &&
+         (polar || m <= 4 || int64_t(N) * n_loop <= 1024);
 }
 
 template <int P>
@@ -1155,7 +1160,7 @@ static int wilson_core(be_ctx *ctx, Grid U, int N, int m, int64_t n_lines, int n
   if (m == 0) return BE_OK;
   const int64_t mm = int64_t(m) * m;
   const int64_t nm = n_lines * n_loop;
-  if (small_loop_fits(N, m, n_loop))
+  if (small_loop_fits(N, m, n_loop, mode == BE_OVL_POLAR))
     return small_loop(ctx, U, N, m, n_lines, n_loop, mode, theta_sorted, ldt, Zout, theta_raw, line_status, Fkeep,
                       stream, Wout);
   double2 *F = nullptr, *B1 = nullptr, *B2 = nullptr, *Hs = nullptr;
