@@ -90,3 +90,9 @@ def test_nested_loop_of_few_bands(ctx, n_par, n_perp):
         assert int(out["status"][0]) == ref["status"]
         if ref["theta"] is not None:
             assert phase_set_error(out["theta"][0, :, :ref["s"]].cpu().numpy(), ref["theta"]) < TOL
+
+
+# raw overlaps on either side of the 1,024 terms per lane that go over to the general path, above 4 bands
+@pytest.mark.parametrize("m, N, n_par", [(4, 64, 17), (5, 64, 16), (5, 64, 17), (8, 64, 16), (8, 64, 17)])
+def test_raw_loops_of_few_bands(ctx, m, N, n_par):
+    test_wilson_loop_of_few_bands(ctx, m, N, n_par, "raw")
