@@ -574,20 +574,19 @@ __global__ __launch_bounds__(PT) void tri_bisect(const double *d, const double *
       int u = 0;
       while (u < PT && s_cnt[u] <= k) ++u;
       double a = u == 0 ? gl : gl + double(u) * hstep, b = u == PT ? gu : gl + double(u + 1) * hstep;
-      bool conv = false, fine = false;
+      bool conv = false;
       for (int it = 0; it <= max_it; ++it) {
-        if (low && !fine) fine = widen_low(a, b, tn);
         const double mid = 0.5 * (a + b);
         conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + DBL_MIN, tol_abs) || mid <= a || mid >= b;
         if (conv || it == max_it) break;
-        const int cnt = fine             ? sturm_count(sd, se2, N, mid * isc, pivmin)
-                        : b - a > qwidth ? sturm_count_p(sde, N, mid)
-                                         : sturm_count_i(sde, N, mid);
-        if (cnt > k) b = mid;
+        if ((b - a > qwidth ? sturm_count_p(sde, N, mid) : sturm_count_i(sde, N, mid)) > k) b = mid;
         else a = mid;
       }
+      val = 0.5 * (a + b);
+      if (low && conv && fabs(val) <= kLowLevel)
+        val = low_level(sd, se2, N, k, val, tn, isc, pivmin, tol_abs, max_it, conv);
+      val *= isc;
       if (!conv) atomicOr(&status[q], BE_ST_NONCONVERGED);
-      val = 0.5 * (a + b) * isc;
     }
     slam[t] = val;
   }

@@ -374,51 +374,64 @@ __global__ __launch_bounds__(64) void eigh_small_kernel(IN *H, int64_t sH, int l
   }
   wave_lds_sync();
   // ---- bisection, a lane per eigenvalue (as tri_bisect, from the Gershgorin interval)
-  double gl = INFINITY, gu = -INFINITY, emax2 = 0.0;
+  double gl = INFINITY, gu = -INFINITY;
   for (int i = t; i < N; i += TPM) {
     const double rad = fabs(se[i]) + (i > 0 ? fabs(se[i - 1]) : 0.0);
     gl = fmin(gl, sd[i] - rad);
     gu = fmax(gu, sd[i] + rad);
-    emax2 = fmax(emax2, se2[i]);
   }
   gl = -grp_max<TPM>(-gl);
   gu = grp_max<TPM>(gu);
-  emax2 = grp_max<TPM>(emax2);
-  const double tnorm = fmax(fabs(gl), fabs(gu)), pivmin = DBL_MIN * fmax(1.0, emax2);
+  const double tnorm = fmax(fabs(gl), fabs(gu));
   const double sc = sturm_scale(tnorm), isc = 1.0 / sc, tn = tnorm * sc;
   double2 de[NM];  // the scaled pairs, every lane of the matrix all of them
-  bool low = false;  // T splits
 #pragma unroll
-  for (int i = 0; i < NM; ++i) {
-    const double e2 = i > 0 && i < N ? se2[i - 1] * sc * sc : 1.0;
-    low = low || below_floor(e2);
-    de[i] = i < N ? make_double2(sd[i] * sc, fmax(e2, kSturmE2)) : sturm_pad();
-  }
+  for (int i = 0; i < NM; ++i)
+    de[i] = i < N ? make_double2(sd[i] * sc, fmax(i > 0 ? se2[i - 1] * sc * sc : 0.0, kSturmE2)) : sturm_pad();
   gl = gl * sc - 2.0 * eps * tn - DBL_MIN;
   gu = gu * sc + 2.0 * eps * tn + DBL_MIN;
   const double tol_abs = eps * eps * tn;
   const int hi = lo + m;
-  for (int k0 = t; k0 < m + 4; k0 += TPM) {  // [lambda_0, lambda_{N-1}, lambda_{lo-1}, lambda_hi, lambda_lo ..]
-    const int k = k0 == 0 ? 0 : k0 == 1 ? N - 1 : k0 == 2 ? lo - 1 : k0 == 3 ? (hi < N ? hi : -1) : lo + k0 - 4;
+  auto index = [&](int k0) {  // [lambda_0, lambda_{N-1}, lambda_{lo-1}, lambda_hi, lambda_lo ..]
+    return k0 == 0 ? 0 : k0 == 1 ? N - 1 : k0 == 2 ? lo - 1 : k0 == 3 ? (hi < N ? hi : -1) : lo + k0 - 4;
+  };
+  for (int k0 = t; k0 < m + 4; k0 += TPM) {
+    const int k = index(k0);
     double val = NAN;
     if (k >= 0) {
       double a = gl, b = gu;
-      bool conv = false, fine = false;
+      bool conv = false;
       for (int it = 0; it <= max_it; ++it) {
-        if (low && !fine) fine = widen_low(a, b, tn);
         const double mid = 0.5 * (a + b);
         conv = b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)) + DBL_MIN, tol_abs) || mid <= a || mid >= b;
         if (conv || it == max_it) break;
-        const int cnt = fine                                ? sturm_count(sd, se2, N, mid * isc, pivmin)
-                        : FULL || b - a > kQuotientWidth ? sturm_count_p(de, mid)
-                                                         : sturm_count_i(de, mid);
-        if (cnt > k) b = mid;
+        if ((FULL || b - a > kQuotientWidth ? sturm_count_p(de, mid) : sturm_count_i(de, mid)) > k) b = mid;
         else a = mid;
       }
       if (!conv) st |= BE_ST_NONCONVERGED;
       val = 0.5 * (a + b) * isc;
     }
     slam[k0] = val;
+  }
+  // ---- near zero, the levels of a T that splits, after the loop and from what LDS
+  // holds: values kept in registers beside the pairs would leave orders 17 to 32 two
+  // waves per SIMD instead of three
+  const double s1 = sturm_scale(tnorm);
+  double emax2 = 0.0, floored = 0.0;
+  for (int i = t; i < N; i += TPM) {
+    emax2 = fmax(emax2, se2[i]);
+    if (i + 1 < N && below_floor(se2[i] * s1 * s1)) floored = 1.0;
+  }
+  const double pivmin = DBL_MIN * fmax(1.0, grp_max<TPM>(emax2));
+  if (grp_max<TPM>(floored) != 0.0) {
+#pragma unroll 1
+    for (int k0 = t; k0 < m + 4; k0 += TPM) {
+      const double v = slam[k0] * s1, i1 = 1.0 / s1, n1 = tnorm * s1;
+      bool conv = true;
+      if (fabs(v) <= kLowLevel)
+        slam[k0] = low_level(sd, se2, N, index(k0), v, n1, i1, pivmin, eps * eps * n1, max_it, conv) * i1;
+      if (!conv) st |= BE_ST_NONCONVERGED;
+    }
   }
   wave_lds_sync();
   const double *lam = slam + 4;

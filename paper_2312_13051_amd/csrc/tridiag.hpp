@@ -140,15 +140,25 @@ constexpr double kQuotientWidth = 0x1p-38;
 
 // Couplings below the minors' floor are raised to it there, which moves a level by
 // up to 2e-18 ||T||: below the rounding of the levels themselves down to 2^-6 ||T||,
-// but not of the levels near zero of a T that splits. From kQuotientWidth on those
-// are found by quotients on T as it is, in an interval wide enough for that move.
-constexpr double kLowLevel = 0x1p-6, kLowMove = 8e-18;  // relative to the norm tn of a T scaled as above
+// but not of the levels near zero of a T that splits. Those are found again by
+// quotients on T as it is, from an interval around v wide enough for that move. (v,
+// tn: of the T scaled as above; k: the level's index.)
+constexpr double kLowLevel = 0x1p-6, kLowMove = 8e-18;  // relative to the norm tn
 __device__ __forceinline__ bool below_floor(double e2) { return e2 < kSturmE2; }
-__device__ __forceinline__ bool widen_low(double &a, double &b, double tn) {
-  if (b - a > kQuotientWidth || fmax(fabs(a), fabs(b)) > kLowLevel) return false;
-  a -= kLowMove * tn;
-  b += kLowMove * tn;
-  return true;
+__device__ __forceinline__ double low_level(const double *sd, const double *se2, int N, int k, double v, double tn,
+                                            double isc, double pivmin, double tol_abs, int max_it, bool &conv) {
+  const double w = kLowMove * tn + 4.0 * DBL_EPSILON * fabs(v);
+  double a = v - w, b = v + w;
+  conv = false;
+#pragma unroll 1
+  for (int it = 0; it <= max_it; ++it) {
+    const double mid = 0.5 * (a + b);
+    conv = b - a <= fmax(2.0 * DBL_EPSILON * fmax(fabs(a), fabs(b)) + DBL_MIN, tol_abs) || mid <= a || mid >= b;
+    if (conv || it == max_it) break;
+    if (sturm_count(sd, se2, N, mid * isc, pivmin) > k) b = mid;
+    else a = mid;
+  }
+  return 0.5 * (a + b);
 }
 
 // Power of two that takes a norm into [1/2, 1) (1 for a zero or non-finite norm;
