@@ -330,16 +330,19 @@ int be_build_hk(be_ctx *ctx, const be_hk_plan *P, int32_t sys_first, int32_t n_s
   int pp = 8;
   while (pp < 256 && pp < maxp) pp *= 2;
   // workgroups (x, y) with kb k-points per entry read and r rounds of pairs per
-  // workgroup, which share its phases: four of each, fewer where that would leave
-  // compute units without work (order 1024, c64, one k-point: 22.5 us in hk_scatter,
-  // 26.8 with four, 23.6 so; 16: 46.2, 52.5, 47.7)
+  // workgroup, which share its phases. Four k-points where the entries' reads bound
+  // the sums, lists of four entries a pair and more (48 orbitals, 256 k-points 38 us,
+  // 59 with one), else where they leave every compute unit work, and as many rounds,
+  // up to four, as do (order 1024, five entries for four pairs, c64, one k-point: 22.5
+  // us in hk_scatter, 26.8 with four of each, 23.6 so; 16: 46.2, 52.5, 47.7)
   auto grid = [&](int kb, int r) {
     const int64_t groups = (int64_t(n_sys_call) * ((n_kap + kb - 1) / kb) + 256 / pp - 1) / (256 / pp);
     return dim3(static_cast<uint32_t>(std::max(1, (maxp + r * pp - 1) / (r * pp))),
                 static_cast<uint32_t>(std::min<int64_t>(groups, 65535)));
   };
   auto fills = [&](dim3 g) { return int64_t(g.x) * g.y >= 2 * ctx->n_cu; };
-  const int kb = pp == 256 && 4 * int64_t(max_R) <= kPhaseTable && fills(grid(4, 1)) ? 4 : 1;
+  const bool many = P->total_ents >= 4 * P->total_pairs && n_kap >= 4;  // entries
+  const int kb = pp == 256 && 4 * int64_t(max_R) <= kPhaseTable && (many || fills(grid(4, 1))) ? 4 : 1;
   int rounds = 4;
   while (rounds > 1 && !fills(grid(kb, rounds))) rounds /= 2;
   auto go = [&](auto *Ht) {
