@@ -77,6 +77,7 @@ __global__ __launch_bounds__(RT, NA <= 3 ? 4 : 2) void hetrd_resident_kernel(dou
   const bool on0 = tx == ty, on1 = tx == ty + 16, up0 = tx < ty, up1 = tx < ty + 16;
 
   double2 m[NA * (NA + 1)];
+  double mx = 0.0;
   unrolled<2 * NA>([&](auto B) {
     constexpr int b = B, a0 = b / 2;
     unrolled<NA - a0>([&](auto D) {
@@ -86,6 +87,7 @@ __global__ __launch_bounds__(RT, NA <= 3 ? 4 : 2) void hetrd_resident_kernel(dou
       if (i < nb && k <= i) v = Aq[S + i + int64_t(S + k) * lda];
       if (i == k) v.y = 0.0;
       m[blk(NA, a, b)] = v;
+      mx = fmax(mx, fmax(fabs(v.x), fabs(v.y)));
       if (b == 0 && S == 0 && ty == 0) sx[i] = v;
     });
   });
@@ -94,57 +96,64 @@ __global__ __launch_bounds__(RT, NA <= 3 ? 4 : 2) void hetrd_resident_kernel(dou
     double2 v = make_double2(0.0, 0.0);
     if (i >= k) v = Aq[i + int64_t(k) * lda];
     if (i == k) v.y = 0.0;
+    mx = fmax(mx, fmax(fabs(v.x), fabs(v.y)));
     strip[t] = v;
   }
   for (int i = tid; i < NX; i += RT) yS[i] = make_double2(0.0, 0.0);
+  mx = fold_max<16>(fold_max<32>(mx));
+  mx = fmax(mx, lane_xor<8>(mx));
+  mx = fmax(mx, lane_xor<4>(mx));
+  mx = fmax(mx, lane_xor<2>(mx));
+  mx = fmax(mx, lane_xor<1>(mx));
+  if (lane == 0) sq[wave] = mx;
   __syncthreads();
+  // Products of three factors of u, A and u below would leave the range of FP64 for
+  // matrices of norm 1e103 or 1e-105: one that far from one is reduced scaled by a
+  // power of two (d and e are scaled back). A column of norm below 2^-450 then counts
+  // as zero: the square of scal would leave the range, and leaving it out changes the
+  // matrix by 2^-350 of its norm at most.
+  for (int w2 = 0; w2 < RWV; ++w2) mx = fmax(mx, sq[w2]);
+  const int ex = __builtin_amdgcn_frexp_exp(mx);  // 0 for zero and non-finite values
+  const int sh = ex > 100 || ex < -100 ? -ex : 0;
+  if (sh != 0) {
+    unrolled<2 * NA>([&](auto B) {
+      constexpr int b = B, a0 = b / 2;
+      unrolled<NA - a0>([&](auto D) {
+        constexpr int a = a0 + D;
+        double2 &v = m[blk(NA, a, b)];
+        v = make_double2(__builtin_amdgcn_ldexp(v.x, sh), __builtin_amdgcn_ldexp(v.y, sh));
+        if (b == 0 && S == 0 && ty == 0) sx[32 * a + tx] = v;
+      });
+    });
+    for (int t = tid; t < S * n; t += RT)
+      strip[t] = make_double2(__builtin_amdgcn_ldexp(strip[t].x, sh), __builtin_amdgcn_ldexp(strip[t].y, sh));
+    __syncthreads();
+  }
   if (S > 0 && tid < n) sx[tid] = strip[tid];  // column 0 (else written with the loads)
   __syncthreads();
   for (int j = 0; j + 1 < n; ++j) {
-    // ---- reflector of column j (every wave by itself); u = 2^sh (x - beta e_{j+1}) of
-    // norm about one, v = scal u: products of three factors of u, A and u, and the
-    // square of scal, would leave the range of FP64 for matrices of norm 1e103 or
-    // 1e-105 already, and for columns of norm 1e-154
+    // ---- reflector of column j (every wave by itself); u = x - beta e_{j+1}, v = scal u
     double xn = 0.0;
     for (int i = j + 2 + lane; i < n; i += 64) {
       const double2 x = sx[i];
       xn = fma(x.x, x.x, fma(x.y, x.y, xn));
     }
     xn = wave_sum(xn);
-    double2 alpha = sx[j + 1];
+    const double2 alpha = sx[j + 1];
     double2 tau = make_double2(0.0, 0.0), scal = tau, ub = tau;
-    double beta = alpha.x, nn = alpha.x * alpha.x + alpha.y * alpha.y + xn;
-    int sh = 0;
-    if (!(nn >= 0x1p-900 && nn <= 0x1p900)) {  // the squares may have left the range: again, scaled by the largest entry
-      double mx = 0.0;
-      for (int i = j + 1 + lane; i < n; i += 64) mx = fmax(mx, fmax(fabs(sx[i].x), fabs(sx[i].y)));
-      for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-      sh = -__builtin_amdgcn_frexp_exp(mx);
-      xn = 0.0;
-      for (int i = j + 2 + lane; i < n; i += 64) {
-        const double x = __builtin_amdgcn_ldexp(sx[i].x, sh), y = __builtin_amdgcn_ldexp(sx[i].y, sh);
-        xn = fma(x, x, fma(y, y, xn));
-      }
-      xn = wave_sum(xn);
-      alpha = make_double2(__builtin_amdgcn_ldexp(alpha.x, sh), __builtin_amdgcn_ldexp(alpha.y, sh));
-      nn = alpha.x * alpha.x + alpha.y * alpha.y + xn;
-    }
-    if (xn != 0.0 || alpha.y != 0.0) {
-      const double nrm = sqrt(nn), b = alpha.x >= 0.0 ? -nrm : nrm;
-      const int ex = -__builtin_amdgcn_frexp_exp(nrm);
-      beta = __builtin_amdgcn_ldexp(b, -sh);
-      tau = make_double2((b - alpha.x) / b, -alpha.y / b);
-      ub = make_double2(__builtin_amdgcn_ldexp(alpha.x - b, ex), __builtin_amdgcn_ldexp(alpha.y, ex));
+    double beta = alpha.x;
+    const double nn = alpha.x * alpha.x + alpha.y * alpha.y + xn;
+    if ((xn != 0.0 || alpha.y != 0.0) && !(nn < 0x1p-900)) {
+      const double nrm = sqrt(nn);
+      beta = alpha.x >= 0.0 ? -nrm : nrm;
+      tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
+      ub = make_double2(alpha.x - beta, alpha.y);
       const double den = ub.x * ub.x + ub.y * ub.y;
       scal = make_double2(ub.x / den, -ub.y / den);
-      sh += ex;
     }
     if (tid < NX) {
       double2 u = make_double2(0.0, 0.0);
-      if (tid > j && tid < n) {
-        u = sx[tid];
-        u = tid == j + 1 ? ub : make_double2(__builtin_amdgcn_ldexp(u.x, sh), __builtin_amdgcn_ldexp(u.y, sh));
-      }
+      if (tid > j && tid < n) u = tid == j + 1 ? ub : sx[tid];
       su[tid] = u;
     }
     lds_barrier();
@@ -267,8 +276,8 @@ __global__ __launch_bounds__(RT, NA <= 3 ? 4 : 2) void hetrd_resident_kernel(dou
     }
     for (int r = tid; r < p0; r += RT) Aq[r - p0 + int64_t(j) * lda] = make_double2(0.0, 0.0);
     if (tid == 0) {
-      d[q * sDE + p0 + j] = sx[j].x;
-      e[q * sDE + p0 + j] = beta;
+      d[q * sDE + p0 + j] = __builtin_amdgcn_ldexp(sx[j].x, -sh);
+      e[q * sDE + p0 + j] = __builtin_amdgcn_ldexp(beta, -sh);
       taus[q * N + p0 + j] = tau;
     }
     lds_barrier();
@@ -322,7 +331,7 @@ __global__ __launch_bounds__(RT, NA <= 3 ? 4 : 2) void hetrd_resident_kernel(dou
   }
   // last column: no reflector
   if (tid == 0) {
-    d[q * sDE + N - 1] = sx[n - 1].x;
+    d[q * sDE + N - 1] = __builtin_amdgcn_ldexp(sx[n - 1].x, -sh);
     taus[q * N + N - 1] = make_double2(0.0, 0.0);
   }
   for (int r = tid; r < N; r += RT) Aq[r - p0 + int64_t(n - 1) * lda] = make_double2(0.0, 0.0);
