@@ -67,7 +67,7 @@ struct GP {
   cplx alpha, beta;
   int64_t batch;
   int tiles_m, tiles_n;
-  int herm;  // Hermitian C: lower tiles only, strictly lower tiles mirrored into the upper triangle (if mirror)
+  int herm;  // Hermitian C: lower tiles only, the lower triangle mirrored into the upper one (if mirror)
   int mirror;
   int four_mult;  // complex products in the four-product form
   const int *act;  // per batch item: 0 skips the item (its C is left untouched), or null
@@ -295,7 +295,9 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
       }
   }
 
-  // ---- epilogue: lane holds C(i = i_base + li, j = j_base + row(lk, r))
+  // ---- epilogue: lane holds C(i = i_base + li, j = j_base + row(lk, r)). Hermitian C:
+  // the lower triangle, and the upper from it (the Gauss form's two halves of a
+  // diagonal tile are not exact conjugates: C would depend on the tile size)
   const bool use_beta = (p.beta.x != T(0)) || (p.beta.y != T(0));
 #pragma unroll
   for (int a = 0; a < TM; ++a)
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         int gj = j0 + wn * (BN / WN) + b * 16 + MF<T>::row(lk, r);
-        if (gi < p.M && gj < p.N) {
+        if (gi < p.M && gj < p.N && !(p.herm && gi < gj)) {
           T xr = accr[a][b][r], xi = acci[a][b][r];
           cplx out;
           out.x = p.alpha.x * xr - p.alpha.y * xi;
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(64 * WM * WN) void zgemm_kernel(GP<T> p) {
             out.y += p.beta.x * c.y + p.beta.y * c.x;
           }
           C[idx] = out;
-          if (p.herm && p.mirror && tm > tn) {
+          if (p.herm && p.mirror && gi > gj) {
             cplx o2 = out;
             o2.y = -out.y;
             C[gj + int64_t(gi) * p.ldc] = o2;
