@@ -953,26 +953,26 @@ __global__ __launch_bounds__(256) void k_herm_of_unitary(const double2 *W, int m
 
 // Phases from the eigenpairs of A. W is a product of polar factors, unitary to
 // some 1e-14 per link: W = rho U with rho_n = |W v_n| / |v_n| to the second order
-// in that, whatever mix of eigenvectors v_n is. c_n (the eigenvalue, from
-// bisection: complete and accurate whatever the vectors) over rho_n fixes
-// |theta_n - phi| = acos(c_n / rho_n), which loses eps / |sin|; s_n =
-// Im(e^{-i phi} v_n^H (W v_n)) gives the sign, and atan2(s_n, c_n) the phase to
-// eps where v_n is an eigenvector. A vector inside a cluster of nearly equal
-// phases may be any mix of the cluster's eigenvectors (W matrices of disordered
-// supercells hold hundreds of phases within 1e-9 of 0): its s_n keeps the common
-// sign and |s_n| stays at rho sin, which is checked (a mix of a pair theta, 2 phi
-// - theta would break it), but its quotient is a mean of the cluster's phases. A
-// rho more than 1e-9 from one is a line whose links did not converge: its W is
-// not normal, and A's eigenvectors are not W's.
-// Hence atan2 wherever it lies within the cosine's own uncertainty of acos (8 eps
-// / |sin|), else acos. On the CPU, orders 13 to 200, W unitary to 1e-13: without
-// rho, cosines alone, 4e-12 to 1e-11 off; so 4e-16 to 2e-14, and 1e-13 in crowds
-// of phases 3e-14 apart and in pairs. Within 0.005 of the branch points (sin ~ 0),
-// and whenever eigenvectors are returned, theta_n = phi + atan2(s_n, c_n) from a
-// vector whose residual |W v - e^{i theta} v| must be below 1e-10 (and the
-// eigensolver's status clear). Ascending sort; optional raw phases and
-// eigenvectors. One workgroup per matrix, a wave per column. fb[q] = 1 where the
-// QR kernel must take over.
+// in that, whatever mix of eigenvectors v_n is. The quotient z_n = e^{-i phi} v_n^H
+// (W v_n) / v_n^H v_n gives both parts to eps where v_n is an eigenvector. Its real
+// part holds too where v_n mixes a pair theta, 2 phi - theta of nearly equal
+// cosines; inside a cluster of nearly equal phases (W matrices of disordered
+// supercells hold hundreds within 1e-9 of 0) v_n may be any mix and z_n a mean of
+// theirs. So c_n is the real part where the eigenvalue (from bisection: complete and
+// accurate to some 9 eps whatever the vectors) confirms it to 16 eps, else the
+// eigenvalue. |theta_n - phi| = acos(c_n / rho_n) loses eps / |sin|: the phase is
+// atan2(s_n, c_n), s_n the imaginary part, wherever that lies within 8 eps / |sin| of
+// acos, else (crowds, pairs) acos with s_n's sign. |s_n| stays at rho sin but for a
+// mix of a pair, which is checked. A rho more than 1e-9 from one is a line whose
+// links did not converge: its W is not normal, and A's eigenvectors are not W's. On
+// the CPU, orders 13 to 200, W unitary to 1e-13, eigenvalues 4 eps off: acos of the
+// eigenvalues alone 2e-12 to 1e-11 off; so 2e-16 to 2e-14, and 1e-13 in crowds of
+// phases 3e-14 apart and in pairs whose cosines agree to 1e-9. Within 0.005 of the
+// branch points (sin ~ 0), and whenever eigenvectors are returned, theta_n = phi
+// + atan2(s_n, c_n) from a vector whose residual |W v - e^{i theta} v| must be
+// below 1e-10 (and the eigensolver's status clear). Ascending sort; optional raw
+// phases and eigenvectors. One workgroup per matrix, a wave per column. fb[q] = 1
+// where the QR kernel must take over.
 __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uint32_t *est, const double2 *V,
                                                      const double2 *WV, int m, int64_t n_mat, double *theta_sorted,
                                                      int ldt, double *theta_raw, double2 *Zout, int *fb) {
@@ -1003,10 +1003,10 @@ __global__ __launch_bounds__(256) void k_herm_phases(const double *ev, const uin
       vv += __shfl_xor(vv, o, 64);
       ww += __shfl_xor(ww, o, 64);
     }
-    // Im(e^{-i phi} v^H W v) / v^H v (the vectors of a crowd of nearly equal
-    // phases need not come out normalized), and both parts over rho
+    // (the vectors of a crowd of nearly equal phases need not come out normalized)
     const double rho = sqrt(ww / vv), s = (cs * pi - sn * pr) / (vv * rho);
-    const double c = fmin(1.0, fmax(-1.0, ev[q * (m + 2) + 1 + n] / rho));
+    const double ce = ev[q * (m + 2) + 1 + n], cz = (cs * pr + sn * pi) / vv;
+    const double c = fmin(1.0, fmax(-1.0, (fabs(cz - ce) <= 16.0 * DBL_EPSILON ? cz : ce) / rho));
     const double sabs = sqrt(fmax(0.0, 1.0 - c * c));
     const bool by_cos = !vectors && sabs >= 0.005;
     double x = atan2(s, c);
