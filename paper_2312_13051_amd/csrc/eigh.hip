@@ -2275,7 +2275,7 @@ extern "C" int be_eigh_round(be_ctx *ctx, int32_t N, int32_t precision, int64_t 
   if (precision == BE_FP64) {
     *round = panel_slots<double>(ctx, N, panel_threads(ctx, N, sizeof(double2)));
   } else if (precision == BE_MIXED_FP32 || precision == BE_MIXED_FP32_REFINED || precision == BE_MIXED_BF16X) {
-    *round = panel_slots<float>(ctx, N, panel_threads(ctx, N, sizeof(float2)));
+    *round = panel_slots<float>(ctx, N, call_panel_threads<float>(ctx, N, int64_t(1) << 30));
   } else {
     return set_err(ctx, BE_EINVAL, "be_eigh_round: unknown precision");
   }
