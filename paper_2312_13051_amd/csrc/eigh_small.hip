@@ -12,7 +12,7 @@
 // lane per eigenvalue, and the columns of the reduction), hence as many matrices
 // per wave as have rows for its lanes. FP64, half the bands, general path ->
 // this one: order 4, 10,000 matrices 945 -> 50 us; 16, 4,096: 1,416 -> 126; 32,
-// 12, all bands: 247; 8,192: 6,547 -> 1,566. The Sturm counts read T from
+// 12, all bands: 613 -> 255; 8,192: 6,547 -> 1,566. The Sturm counts read T from
 // registers (from LDS: 62, 158, 287 and 1,833 us).
 // Mixed path up to order 16, likewise: order 4, 52,500 matrices (a quarter of
 // the nested loops of 21 planes) 460 -> 123 us, of which the panel kernel took

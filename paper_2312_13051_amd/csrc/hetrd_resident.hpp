@@ -6,7 +6,7 @@
 namespace be {
 
 // Largest order the kernel reduces: 192 rows and columns in registers and up
-// to 24 further columns in LDS (all 160 KB of it).
+// to 24 further columns in LDS (131 KB with the vectors and partial sums).
 constexpr int kResidentOrder = 216;
 
 // Reduces the trailing matrices H(p0:N, p0:N) of order N - p0 <= kResidentOrder

@@ -11,6 +11,9 @@ ranges split at the midpoints between measured orders, plus the raw timings.
 
     python -m paper_2312_13051_amd.tune --orders 128,256,400,576,800,1024,1568,2304 --out tuning.json
 
+FP64 reduces its last 216 rows and columns on chip: the rows of FP64 orders up
+to 216 are measured as all others but have no effect.
+
 The matrices are random Hermitian ones (the kernels' work does not depend on
 the values); the timed call is the library's ``be_eigh_batched`` with bands
 [0, N/2).
