@@ -141,14 +141,16 @@ constexpr double kQuotientWidth = 0x1p-38;
 // Couplings below the minors' floor are raised to it there, which moves a level by
 // up to 2e-18 ||T||: below the rounding of the levels themselves down to 2^-6 ||T||,
 // but not of the levels near zero of a T that splits. Those are found again by
-// quotients on T as it is, from an interval around v wide enough for that move. (v,
-// tn: of the T scaled as above; k: the level's index.)
+// quotients on T as it is, from an interval around v wide enough for that move: four
+// cells of a power of two's grid, whose halvings are the same whatever v is, so that
+// equal levels come out equal and all in order. (v, tn: of the T scaled as above; k:
+// the level's index.)
 constexpr double kLowLevel = 0x1p-6, kLowMove = 8e-18;  // relative to the norm tn
 __device__ __forceinline__ bool below_floor(double e2) { return e2 < kSturmE2; }
 __device__ __forceinline__ double low_level(const double *sd, const double *se2, int N, int k, double v, double tn,
                                             double isc, double pivmin, double tol_abs, int max_it, bool &conv) {
-  const double w = kLowMove * tn + 4.0 * DBL_EPSILON * fabs(v);
-  double a = v - w, b = v + w;
+  const double w = __builtin_amdgcn_ldexp(1.0, __builtin_amdgcn_frexp_exp(kLowMove * tn + 4.0 * DBL_EPSILON * fabs(v)));
+  double a = (floor(v / w) - 1.0) * w, b = a + 4.0 * w;
   conv = false;
 #pragma unroll 1
   for (int it = 0; it <= max_it; ++it) {

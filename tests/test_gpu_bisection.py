@@ -68,3 +68,50 @@ def test_levels_of_decoupled_blocks(N, precision):
     near, far = got[n0:n0 + w2.size], np.concatenate([got[:n0], got[n0 + w2.size:]])
     assert np.abs(far - w1).max() <= 3 * N * eps * np.abs(w1).max()
     assert np.abs(near - w2 * small).max() <= 3 * N * eps * np.abs(w2).max() * small + 4 * eps ** 2 * np.abs(w1).max()
+
+
+# uncoupled chains of three sites, one zero level each: the same value for all of them, bit for bit (the bisection of each sees
+# the same counts), as the refined path's correction, which divides by differences of levels and skips those of zero, needs
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("N", [6, 9, 15, 18, 33, 60, 300])
+def test_equal_levels_of_decoupled_blocks(N, precision):
+    gu.need_gpu()
+    from paper_2312_13051_amd import _lib as L
+    mixed = precision == "mixed"
+    e = np.where(np.arange(1, N) % 3 == 0, 0.0, 0.75)
+    H = (np.diag(e, 1) + np.diag(e, -1)).astype(complex)[None]
+    c = gu.ctx()
+    try:
+        dH = gu.from_np(H, N, torch.complex64 if mixed else torch.complex128)
+        U = gu.colmajor(1, N, N, N, fill=0)
+        ev = torch.empty((1, N + 2), dtype=torch.float64, device="cuda")
+        st = torch.empty(1, dtype=torch.int32, device="cuda")
+        c.eigh_batched(dH, L.BE_C64 if mixed else L.BE_C128, N, N, dH.stride(0), 1, 0, N,
+                       L.BE_MIXED_FP32 if mixed else L.BE_FP64, ev, U, N, U.stride(0), st)
+        zero = ev[0, 1 + N // 3:1 + 2 * (N // 3)].cpu().numpy()
+    finally:
+        c.close()
+    assert np.abs(zero).max() <= 4 * np.finfo(float).eps ** 2
+    assert np.all(zero == zero[0])
+
+
+# a window that cuts the pair of zero levels of a ring of four sites: flagged for its gap, and a basis all the same
+@pytest.mark.parametrize("lo,hi", [(0, 2), (1, 2), (2, 4)])
+def test_refined_window_through_equal_levels(lo, hi):
+    gu.need_gpu()
+    from paper_2312_13051_amd import _lib as L
+    P = np.roll(np.eye(4), 1, 0)
+    m = hi - lo
+    c = gu.ctx()
+    try:
+        dH = gu.from_np((P + P.T).astype(complex)[None], 4)
+        U = gu.colmajor(1, 4, m, 4, fill=0)
+        ev = torch.empty((1, m + 2), dtype=torch.float64, device="cuda")
+        st = torch.empty(1, dtype=torch.int32, device="cuda")
+        c.eigh_batched(dH, L.BE_C128, 4, 4, dH.stride(0), 1, lo, hi, L.BE_MIXED_FP32_REFINED, ev, U, 4, U.stride(0), st)
+        V, status, w = U[0].cpu().numpy().T, int(st[0]), ev[0, 1:-1].cpu().numpy()
+    finally:
+        c.close()
+    assert status == L.ST_GAP_CLOSED
+    assert np.abs(V.conj().T @ V - np.eye(m)).max() < 1e-13
+    assert np.abs(w - np.array([-2.0, 0.0, 0.0, 2.0])[lo:hi]).max() < 1e-12
