@@ -223,7 +223,9 @@ __global__ void k_carry_last(const double2 *src, int n_src, double2 *dst, int n_
 // (general -> this path): Wilson loop of 1 band on 64 x 64 points 757 -> 540 us,
 // nested loop of 2 bands on 100 x 100 points 2.45 -> 1.20 ms, on 21 such planes
 // 27.0 -> 17.8 ms (with k_transport_small). Same steps, tests and flags as
-// k_ns_prep. Fout (optional) receives the factors; theta/phase outputs for m = 1.
+// k_ns_prep, except that a non-finite overlap counts as one that did not converge
+// (there its W alone is flagged). Fout (optional) receives the factors; theta/phase
+// outputs for m = 1.
 constexpr int kSmallM = 8;           // bands
 constexpr int kSmallN = 64;          // orbitals: a lane sums a whole overlap element
 constexpr int kSmallEntries = 3072;  // matrix entries of a line's factors held in LDS (48 KB)
